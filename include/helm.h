@@ -83,13 +83,19 @@ typedef struct helm_precond_opts {
                               this many supernodes of <= 64 pivots (and
                               64-row tiles) solves those with one wave per
                               supernode instead of one per tile; 0 = 6144,
-                              -1 = never                                  */
+                              -1 = never.  A positive value also keeps one
+                              launch per level on operators of at most 3e8
+                              panel entries, whose single-vector sweeps
+                              otherwise share one launch (workgroups wait for
+                              the tiles they depend on)                   */
   int32_t batches;         /* the subdomains as 1 .. 4 consecutive batches
                               of about equal factor size whose level
                               sweeps run concurrently, each on a stream of
                               its own (one after the other while
-                              helm_profile is on); 0 = 2; other values
-                              fail with HELM_EINVAL                       */
+                              helm_profile is on; single-vector sweeps of
+                              operators of at most 3e8 panel entries take
+                              all batches in one launch); 0 = 2; other
+                              values fail with HELM_EINVAL                */
   int32_t perturb_pivots;  /* a pivot with |p| <= 1000 eps max|a_ij| of its
                               matrix (16 FP32 eps in a complex64
                               factorisation; zero to working precision, after
@@ -98,9 +104,11 @@ typedef struct helm_precond_opts {
                               1: replace it by sqrt(eps) max|a_ij| instead,
                               count it in helm_precond_stats.n_perturbed
                               and return HELM_OK                          */
-  int32_t coarse_launch;   /* coarse solve: 0 = the faster of the two forms
-                              as timed at setup; 1 = one launch per level;
-                              2 = one cooperative launch with a grid
+  int32_t coarse_launch;   /* coarse solve: 0 = one launch whose workgroups
+                              wait for the tiles they depend on (factors of
+                              more than 3e8 entries: the faster of the other
+                              two forms as timed at setup); 1 = one launch
+                              per level; 2 = one cooperative launch with a grid
                               barrier per level (HELM_EINVAL where the
                               device cannot co-schedule it).  The
                               cooperative form is used only after its
@@ -225,8 +233,8 @@ typedef struct helm_precond_stats {
   double factor_flops;     /* complex multiply-adds x 8 in the factorisation */
   int32_t factor_c64;      /* fine factor precision as run: 0, 1 or 2 (see
                               helm_precond_opts.factor_c64)               */
-  int32_t coarse_grid;     /* workgroups of the one-launch cooperative coarse
-                              solve; 0 = one launch per level              */
+  int32_t coarse_grid;     /* workgroups of the cooperative coarse solve; 0 =
+                              another form (see coarse_launch)             */
   int32_t n_perturbed;     /* tiny pivots replaced by sqrt(eps) max|a_ij|
                               (only with perturb_pivots)                  */
   double factor_seconds;   /* wall time of the numeric factorisation       */

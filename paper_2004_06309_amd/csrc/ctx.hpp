@@ -58,6 +58,7 @@ struct BatchHost {
   int64_t npos = 0;                  // total positions (sum of matrix orders)
   std::vector<int32_t> c0, w, uoff, frow0;
   std::vector<int64_t> roff;
+  std::vector<int32_t> parent;  // supernode -> its parent in the assembly tree, -1 for roots
   std::vector<int32_t> rows, bidx, fcon_ptr, fcon_idx;
   // per front row its first two child-update indices (-1: none), or
   // (-2 - list start, 0) for a row with more than two (int2 pairs)
@@ -163,6 +164,21 @@ struct BatchDev {
   }
 };
 
+// Both single-vector sweeps of one or more batches as one task list in level
+// order (dev::flow); nf: forward tasks, n: all.
+struct Flow {
+  DVec<dev::FlowTask> tasks;
+  DVec<uint32_t> cnt;
+  int nf = 0, n = 0;
+  int chunk = 0;
+  bool ready() const { return n > 0; }
+  void reset() {
+    tasks.reset();
+    cnt.reset();
+    nf = n = chunk = 0;
+  }
+};
+
 // Event pairs around kernel launches; harvested at synchronisation points.
 struct Profiler {
   bool on = false;
@@ -179,6 +195,7 @@ struct Profiler {
 
 // Subdomain batches whose local solves run concurrently, at most.
 constexpr int kMaxBatches = 4;
+static_assert(kMaxBatches == dev::kFlowBatches, "a flow holds every batch");
 
 struct Ctx {
   int device = -1;
@@ -224,6 +241,11 @@ struct Ctx {
   BatchDev fine[kMaxBatches];
   int32_t nbatch = 1;
   BatchDev coarse;
+  // single-vector solves of all fine batches, and of the coarse batch (empty
+  // where another form was asked for); the allocation-free coarse correction
+  // keeps counters of its own, as its work vectors are
+  Flow flow_fine, flow_coarse;
+  DVec<uint32_t> flow_cnt_noalloc;
   DVec<int64_t> pro_ptr;   // prolongation: global dof -> (position, weight)
   DVec<int32_t> pro_idx;
   DVec<double> pro_w;

@@ -51,24 +51,49 @@ __device__ __forceinline__ float2 ldp(const float2* p) {
   return make_float2(v.x, v.y);
 }
 
-// Streams columns k0, k0 + ks, ... (< k1) of a tile (column-major, ld = nr)
-// against vin, eight independent loads in flight per lane.
+// The first eight of a lane's columns k0, k0 + ks, ... (< k1) of a tile
+// (column-major, ld rows apart); columns past k1 re-read the last one.
 template <class PT>
-__device__ __forceinline__ void tile_dot(const PT* __restrict__ p, int nr, const double2* vin, int k0, int k1, int ks,
-                                        double& ar, double& ai) {
+__device__ __forceinline__ void tile_load(const PT* __restrict__ p, int ld, int k0, int k1, int ks, PT (&a)[8]) {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) a[u] = ldp(p + (int64_t)min(k0 + u * ks, k1 - 1) * ld);
+}
+
+// Streams the columns k0, k0 + ks, ... (< k1) of a tile against vin, the
+// first eight already in a (tile_load).  Eight loads stay in flight per lane:
+// each register is refilled right after its column is used, instead of eight
+// loads being issued and drained in turn (a chain of short levels, the coarse
+// correction: 192 -> 168 us; large levels, bound by HBM, 1-2 %).  Whole groups of eight sum into two
+// accumulators alternately, the rest into the first.
+template <class PT>
+__device__ __forceinline__ void tile_dot(const PT* __restrict__ p, int ld, const double2* vin, int k0, int k1, int ks,
+                                         PT (&a)[8], double& ar, double& ai) {
+  int n = (k1 - k0 + ks - 1) / ks;  // columns from k on
   int k = k0;
   double br = 0, bi = 0;
-  for (; k + 7 * ks < k1; k += 8 * ks) {
-    PT a[8];
+  if (n >= 8) {
+    for (; n >= 16; n -= 8, k += 8 * ks) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] = ldp(p + (int64_t)(k + u * ks) * nr);
+      for (int u = 0; u < 8; u += 2) {
+        cfma(ar, ai, widen(a[u]), vin[k + u * ks]);
+        a[u] = ldp(p + (int64_t)(k + (u + 8) * ks) * ld);
+        cfma(br, bi, widen(a[u + 1]), vin[k + (u + 1) * ks]);
+        a[u + 1] = ldp(p + (int64_t)(k + (u + 9) * ks) * ld);
+      }
+    }
+    n -= 8;
 #pragma unroll
     for (int u = 0; u < 8; u += 2) {
       cfma(ar, ai, widen(a[u]), vin[k + u * ks]);
+      if (u < n) a[u] = ldp(p + (int64_t)(k + (u + 8) * ks) * ld);
       cfma(br, bi, widen(a[u + 1]), vin[k + (u + 1) * ks]);
+      if (u + 1 < n) a[u + 1] = ldp(p + (int64_t)(k + (u + 9) * ks) * ld);
     }
+    k += 8 * ks;
   }
-  for (; k < k1; k += ks) cfma(ar, ai, widen(ldp(p + (int64_t)k * nr)), vin[k]);
+#pragma unroll
+  for (int u = 0; u < 7; ++u)
+    if (u < n) cfma(ar, ai, widen(a[u]), vin[k + u * ks]);
   ar += br;
   ai += bi;
 }
@@ -161,9 +186,14 @@ __device__ __forceinline__ void fwd_task(const Task& task, const Batch& b, const
     }
     __syncthreads();
     if (sp.has && row_l < t.nrows && grp < G) {
+      const PT* __restrict__ Pp = P + (int64_t)cb * t.nrows;
       const int per = (cn + sp.wpt - 1) / sp.wpt;
-      const int k0 = sp.part * per, k1 = min(cn, k0 + per);
-      tile_dot(P + (int64_t)cb * t.nrows, t.nrows, vt, k0 + grp, k1, G, ar, ai);
+      const int k0 = sp.part * per + grp, k1 = min(cn, sp.part * per + per);
+      if (k0 < k1) {
+        PT a[8];
+        tile_load(Pp, t.nrows, k0, k1, G, a);
+        tile_dot(Pp, t.nrows, vt, k0, k1, G, a, ar, ai);
+      }
     }
     __syncthreads();
   }
@@ -208,9 +238,14 @@ __device__ __forceinline__ void bwd_task(const Task& task, const Batch& b, doubl
     }
     __syncthreads();
     if (sp.has && row_l < t.nrows && grp < G) {
+      const PT* __restrict__ Pp = P + (int64_t)cb * t.nrows;
       const int per = (cn + sp.wpt - 1) / sp.wpt;
-      const int k0 = sp.part * per, k1 = min(cn, k0 + per);
-      tile_dot(P + (int64_t)cb * t.nrows, t.nrows, vt, k0 + grp, k1, G, ar, ai);
+      const int k0 = sp.part * per + grp, k1 = min(cn, sp.part * per + per);
+      if (k0 < k1) {
+        PT a[8];
+        tile_load(Pp, t.nrows, k0, k1, G, a);
+        tile_dot(Pp, t.nrows, vt, k0, k1, G, a, ar, ai);
+      }
     }
     __syncthreads();
   }
@@ -251,6 +286,279 @@ __global__ __launch_bounds__(kWG) void bwd_level_kernel(const Task* __restrict__
   for (int t = blockIdx.x; t < ntasks; t += gridDim.x) {
     bwd_task<PT>(tasks[t], b, vin, red, chunk);
     __syncthreads();
+  }
+}
+
+// ---- both sweeps in one launch ----------------------------------------------
+// A sweep level by level costs a launch per level, and every level ends in a
+// tail of a few workgroups while the next one's panels wait; on an operator
+// whose levels do not fill the device several times over that is most of the
+// time.  Here one launch takes all tasks of both sweeps, of all batches, in
+// level order.  A workgroup draws the next task from a counter (and its record
+// one task ahead), loads what does not depend on other tasks (indices, inputs
+// from the caller, the first panel columns), waits for the tiles it does
+// depend on, and streams its panel.
+//
+// Dependencies: counters per supernode.  A forward tile waits until every
+// forward tile of its supernode's children has finished (they hold the
+// updates it gathers), a backward tile until every backward tile of the parent
+// has (the ancestors' results are then complete, since the parent waited for
+// its own parent), a root's backward tiles for its forward tiles.  Counters
+// only grow: a sweep raises each one by a known amount, so the target of sweep
+// number e is (e + 1) times that amount (modulo 2^32) and nothing is cleared
+// between sweeps; e sits in device memory, so a captured launch replays
+// correctly.
+//
+// Progress: a task's dependencies have smaller numbers, and numbers are drawn
+// in order by workgroups already running, so the smallest unfinished task
+// never waits for one that no workgroup holds, whatever the number of
+// resident workgroups.  The wait is bounded all the same; a workgroup that
+// gives up writes NaN, which the solvers report.
+//
+// Memory: what tasks pass to each other (y, x, the update vectors) is written
+// and read with agent-scope accesses, coherent across the XCDs' L2s without
+// writing back or invalidating them; a wave adds to a counter once its stores
+// have completed.  Everything else is constant during the launch.
+//
+// Measured (MI355X): one hop between workgroups (poll, load, store, add) 1.06
+// us, a level of the 16,810-unknown coarse solve 9 us against 11 us with a
+// launch per level (coarse correction 194 -> 168 us), the local solves of
+// 4,913 unknowns in 8 subdomains 156 -> 76 us, of 168,075 unknowns in 30
+// (complex64 panels, 1.05 GB) 461 -> 345 us.  What bounds it now is the chain
+// of latencies in a task (indices, inputs, hop, children's updates, panel,
+// reduction, stores), about 5 us per level on the small operator.
+constexpr int kFlowPolls = 1 << 22;
+
+__device__ __forceinline__ double2 ld_agent(const double2* p) {
+  const double* d = reinterpret_cast<const double*>(p);
+  return make_double2(__hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                      __hip_atomic_load(d + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void st_agent(double2* p, double2 v) {
+  double* d = reinterpret_cast<double*>(p);
+  __hip_atomic_store(d, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(d + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t cnt_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t cnt_add(uint32_t* p) {
+  return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void cnt_store(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits until the counters of the task's tiles have reached their targets
+// (modulo 2^32): lane u of the first wave polls tile u's counter, since a
+// thousand workgroups polling from every wave slow down the additions they
+// wait for (same-address traffic: 11 ns per access).  False if it gave up.
+__device__ __forceinline__ bool flow_wait(const FlowTask& task, uint32_t* cnt, uint32_t sweep) {
+  const int u = threadIdx.x;
+  const int32_t c = u < 4 ? task.t[u].wait : -1;
+  const uint32_t target = u < 4 ? task.t[u].need * (sweep + 1) : 0;
+  const uint32_t* p = cnt + kFlowHead + (int64_t)kFlowPad * c;
+  for (int i = 0; i < kFlowPolls; ++i) {
+    bool done = true;
+    if (c >= 0) done = (int32_t)(cnt_load(p) - target) >= 0;
+    if (__all(done)) return true;
+    if ((i & 1023) == 1023 && cnt_load(cnt + 3)) return false;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  cnt_store(cnt + 3, 1u);
+  return false;
+}
+
+// Sum over the children's update entries of front row fr, whose index pair
+// is c (list order, as for_children).
+__device__ __forceinline__ double2 flow_children(const FlowBatch& b, int fr, int2 c) {
+  const double2* ub = reinterpret_cast<const double2*>(b.ubuf);
+  double2 e = make_double2(0.0, 0.0);
+  if (c.x >= 0) {
+    e = ld_agent(ub + c.x);
+    if (c.y >= 0) {
+      const double2 u = ld_agent(ub + c.y);
+      e.x += u.x;
+      e.y += u.y;
+    }
+  } else if (c.x < -1) {
+    for (int q = -2 - c.x; q < b.fcon_ptr[fr + 1]; ++q) {
+      const double2 u = ld_agent(ub + b.fcon_idx[q]);
+      e.x += u.x;
+      e.y += u.y;
+    }
+  }
+  return e;
+}
+
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// task: in LDS.  nx: the number drawn for the next task (first lane of the
+// workgroup); *word: this lane's word of that task's record (first wave).
+template <class PT, bool kBwd>
+__device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& a, const FlowBatch& b,
+                                          const double2* __restrict__ bin, double2* vin, int2* vidx,
+                                          double2 (*red)[64], int* gave_up, uint32_t sweep, int nx_bound, uint32_t nx,
+                                          const FlowTask* __restrict__ tasks, uint32_t& word) {
+  const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
+  const int wpt = uni(task.t[0].wpt), my = wv / wpt, part = wv % wpt, region = a.chunk / (4 / wpt);
+  const FlowTile& t = task.t[my];
+  const int nrows = uni(t.nrows), ncols = uni(t.ncols), ld = uni(t.ld), c0 = uni(t.c0), w = uni(t.w), aux = uni(t.aux),
+            col0 = uni(t.col0), row0 = uni(t.row0);
+  const int64_t off = ((int64_t)uni((int)(t.off >> 32)) << 32) | (uint32_t)uni((int)t.off);
+  const bool waits = uni(task.t[0].waits) != 0;
+  double2* vt = vin + my * region;
+  int2* it = vidx + my * region;
+  const int R = row_group(nrows), G = 64 / R, grp = lane / R, row_l = lane % R;
+  const PT* __restrict__ P = reinterpret_cast<const PT*>(kBwd ? b.pb : b.pf) + off + row_l;
+  const double2* __restrict__ ub = reinterpret_cast<const double2*>(b.ubuf);
+  const bool out = part == 0 && lane < nrows;
+  const bool dots = row_l < nrows && grp < G;
+  const int row = row0 + lane;
+  const bool upd = !kBwd && out && row >= w;
+  const int npass = wpt == 4 ? (ncols + a.chunk - 1) / a.chunk : 1;
+  const int ks = part * 64 + lane, kst = 64 * wpt;
+  const int2 co = upd ? b.fcon2[aux + row] : make_int2(-1, -1);
+  double er = 0, ei = 0;
+  double ar = 0, ai = 0;
+  for (int pass = 0; pass < npass; ++pass) {
+    const int cb = pass * region, cn = min(region, ncols - cb);
+    // before the wait: the indices of this pass's inputs, the caller's entries
+    // (forward), and the first eight panel columns of every lane
+    for (int k = ks; k < cn; k += kst) {
+      if (kBwd) {
+        const int c = col0 + cb + k;
+        it[k].x = c < w ? c0 + c : -1 - b.rows[(int64_t)aux + (c - w)];
+      } else {
+        it[k] = b.fcon2[aux + cb + k];
+        vt[k] = bin[b.bidx[c0 + cb + k]];
+      }
+    }
+    const int per = (cn + wpt - 1) / wpt;
+    const int kb = part * per + grp, ke = min(cn, part * per + per);
+    const PT* __restrict__ Pp = P + (int64_t)cb * ld;
+    PT pre[8] = {};
+    if (dots && kb < ke) tile_load(Pp, ld, kb, ke, G, pre);
+    if (pass == 0) {
+      if (waits) {
+        if (wv == 0) {
+          const bool ok = flow_wait(task, a.cnt, sweep);
+          if (lane == 0) *gave_up = ok ? 0 : 1;
+        }
+        __syncthreads();
+      }
+      asm volatile("" ::: "memory");  // no load of the other tasks' results above the wait
+      if (upd) {
+        const double2 e = flow_children(b, aux + row, co);
+        er = e.x;
+        ei = e.y;
+      }
+    }
+    // each lane completes the entries it began
+    for (int k = ks; k < cn; k += kst) {
+      if (kBwd) {
+        const int i = it[k].x;
+        vt[k] = ld_agent(i >= 0 ? reinterpret_cast<const double2*>(b.y) + i
+                                : reinterpret_cast<const double2*>(b.x) + (-1 - i));
+      } else {
+        const int2 c2 = it[k];
+        if (c2.x >= 0) {
+          const double2 u = ld_agent(ub + c2.x);
+          double2 v = vt[k];
+          v.x -= u.x;
+          v.y -= u.y;
+          if (c2.y >= 0) {
+            const double2 u2 = ld_agent(ub + c2.y);
+            v.x -= u2.x;
+            v.y -= u2.y;
+          }
+          vt[k] = v;
+        } else if (c2.x < -1) {
+          double2 v = vt[k];
+          for (int q = -2 - c2.x; q < b.fcon_ptr[aux + cb + k + 1]; ++q) {
+            const double2 u = ld_agent(ub + b.fcon_idx[q]);
+            v.x -= u.x;
+            v.y -= u.y;
+          }
+          vt[k] = v;
+        }
+      }
+    }
+    if (pass == 0 && wv == 0) {  // the next task's record
+      const int n = uni((int)nx);
+      if (n < nx_bound) word = reinterpret_cast<const uint32_t*>(tasks + n)[lane];
+    }
+    __syncthreads();
+    if (dots && kb < ke) tile_dot(Pp, ld, vt, kb, ke, G, pre, ar, ai);
+    if (npass > 1) __syncthreads();
+  }
+  red[wv][lane] = make_double2(ar, ai);
+  __syncthreads();
+  if (nrows > 0 && part == 0) {
+    if (out) {
+      double rr = 0, ii = 0;
+      for (int q = 0; q < wpt; ++q)
+        for (int g = lane; g < G * R; g += R) {
+          rr += red[wv + q][g].x;
+          ii += red[wv + q][g].y;
+        }
+      if (waits && *gave_up) rr = ii = __builtin_nan("");
+      double2* dst;
+      if (kBwd)
+        dst = reinterpret_cast<double2*>(b.x) + c0 + row;
+      else
+        dst = row < w ? reinterpret_cast<double2*>(b.y) + c0 + row
+                      : reinterpret_cast<double2*>(b.ubuf) + t.uoff + (row - w);
+      st_agent(dst, make_double2(rr + er, ii + ei));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores have reached the coherence point
+    if (lane == 0) cnt_add(a.cnt + kFlowHead + (int64_t)kFlowPad * t.sig);
+  }
+}
+
+template <class PT, int kCoarse>
+__global__ __launch_bounds__(kWG) void flow_kernel(FlowArgs a, int t0, int t1, int last,
+                                                   const double2* __restrict__ bin) {
+  extern __shared__ double2 vin[];
+  __shared__ double2 red[4][64];
+  __shared__ FlowTask rec[2];
+  __shared__ int next, gave_up;
+  int2* vidx = reinterpret_cast<int2*>(vin + a.chunk);
+  const FlowTask* __restrict__ tasks = a.tasks + t0;
+  const int n = t1 - t0;
+  const uint32_t sweep = uni((int)cnt_load(a.cnt + 2));
+  if (threadIdx.x < 64) {
+    uint32_t d = 0;
+    if (threadIdx.x == 0) next = (int)(d = cnt_add(a.cnt));
+    const int t = uni((int)d);
+    if (t < n)
+      reinterpret_cast<uint32_t*>(&rec[0])[threadIdx.x] = reinterpret_cast<const uint32_t*>(tasks + t)[threadIdx.x];
+  }
+  __syncthreads();
+  int t = uni(next);
+  for (int cur = 0; t < n; cur ^= 1) {
+    // the next task is drawn, and its record loaded, while this one runs
+    uint32_t nx = 0, word = 0;
+    if (threadIdx.x == 0) nx = cnt_add(a.cnt);
+    const FlowTask& task = rec[cur];
+    const FlowBatch& b = a.b[uni(task.t[0].batch)];
+    if (uni(task.t[0].bwd))
+      flow_task<PT, true>(task, a, b, bin, vin, vidx, red, &gave_up, sweep, n, nx, tasks, word);
+    else
+      flow_task<PT, false>(task, a, b, bin, vin, vidx, red, &gave_up, sweep, n, nx, tasks, word);
+    if (threadIdx.x < 64) reinterpret_cast<uint32_t*>(&rec[cur ^ 1])[threadIdx.x] = word;
+    if (threadIdx.x == 0) next = (int)nx;
+    __syncthreads();  // vin and red are rewritten by the next task
+    t = uni(next);
+  }
+  // the last workgroup to finish readies the state for the next launch
+  if (threadIdx.x == 0 && cnt_add(a.cnt + 1) == gridDim.x - 1) {
+    cnt_store(a.cnt, 0);
+    cnt_store(a.cnt + 1, 0);
+    if (last) {
+      cnt_store(a.cnt + 2, sweep + 1);
+      cnt_store(a.cnt + 3, 0);
+    }
   }
 }
 
@@ -1093,6 +1401,18 @@ void bwd_level(const Batch& b, int64_t task0, int64_t ntasks, int chunk, bool co
     level_go(bwd_level_kernel<float2, 0>, ntasks, lds, s, k, nt, b, chunk);
   else
     level_go(bwd_level_kernel<double2, 0>, ntasks, lds, s, k, nt, b, chunk);
+}
+
+void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, bool last, const double* bin, hipStream_t s) {
+  if (t1 <= t0) return;
+  const double2* in = reinterpret_cast<const double2*>(bin);
+  const size_t lds = (sizeof(double2) + sizeof(int2)) * (size_t)a.chunk;
+  if (coarse)
+    level_go(flow_kernel<double2, 1>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
+  else if (c64)
+    level_go(flow_kernel<float2, 0>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
+  else
+    level_go(flow_kernel<double2, 0>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
 }
 
 int coop_grid() {

@@ -149,6 +149,45 @@ void factor_fronts_split(const FrontJob* jobs, int njobs, int mmax, int wmax, vo
 // Fronts of at least this many rows take factor_fronts_split by default.
 constexpr int kSplitFrontMin = 256;
 
+// ---- both single-vector sweeps in one launch ---------------------------------
+// A tile of the forward or backward sweep, or a row range of one, with the
+// counter it waits for and the counter its completion adds to.
+struct FlowTile {
+  int64_t off;                     // first panel entry
+  int32_t ld;                      // rows of the stored tile (column stride)
+  int32_t nrows, ncols, row0, col0;
+  int32_t c0, w, aux;              // as in Tile
+  int32_t uoff;                    // the supernode's update vector in ubuf
+  int32_t wait;                    // counter to wait for (-1: none) ...
+  uint32_t need;                   // ... until it has grown by this much in this sweep
+  int32_t sig;                     // counter to add one to
+  int8_t wpt, batch, bwd, waits;   // of the task: waves per tile, batch, direction, some tile waits
+  int32_t pad;
+};
+// A workgroup's share of the sweeps: 4 / wpt tiles (unused ones have no rows).
+struct FlowTask {
+  FlowTile t[4];
+};
+static_assert(sizeof(FlowTask) == 256, "a wave loads a task with one word per lane");
+// Arrays of one batch that the sweeps touch.
+struct FlowBatch {
+  const void *pf, *pb;
+  const int32_t *rows, *bidx, *fcon_ptr, *fcon_idx;
+  const int2* fcon2;
+  double *ubuf, *y, *x;
+};
+constexpr int kFlowBatches = 4;
+struct FlowArgs {
+  const FlowTask* tasks;
+  uint32_t* cnt;                   // kFlowHead words of state, then the counters
+  int chunk;                       // LDS entries for the input columns
+  FlowBatch b[kFlowBatches];
+};
+constexpr int kFlowHead = 32;      // next task, finished workgroups, sweeps done, gave up (one cache line)
+constexpr int kFlowPad = 16;       // words per counter: few share a cache line, so polling one does not slow another
+// Tasks [t0, t1); last: the launch that ends the backward sweep.
+void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, bool last, const double* bin, hipStream_t s);
+
 // Task ranges of every level of a batch (a kernel argument).
 constexpr int kMaxLevels = 40;
 struct LevelRanges {

@@ -12,6 +12,7 @@
 #include <omp.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
@@ -81,6 +82,9 @@ void Ctx::free_precond() {
   xall_b.reset();
   xall_b_S = 0;
   coarse.reset();
+  flow_fine.reset();
+  flow_coarse.reset();
+  flow_cnt_noalloc.reset();
   pro_ptr.reset();
   pro_idx.reset();
   pro_w.reset();
@@ -209,6 +213,7 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
   B.uoff.resize(nsn);
   B.frow0.resize(nsn);
   B.roff.resize(nsn);
+  B.parent.resize(nsn);
   B.rows.resize(B.nu);
   B.bidx.assign(B.npos, 0);
   std::vector<std::vector<dev::Tile>> lf(maxlev_f + 1), lb(maxlev_b + 1);
@@ -230,6 +235,7 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
       B.w[g] = w;
       B.uoff[g] = (int32_t)(u0[i] + S.sn_rptr[s]);
       B.roff[g] = u0[i] + S.sn_rptr[s];
+      B.parent[g] = S.sn_parent[s] < 0 ? -1 : (int32_t)(sn0[i] + S.sn_parent[s]);
       frl[s] = fr;
       B.frow0[g] = (int32_t)(fr0[i] + fr);
       fr += w + r;
@@ -598,6 +604,200 @@ void build_batch(const std::vector<const Csr*>& As, const std::vector<const Symb
   Dv.x.alloc(2 * std::max<int64_t>(B.npos, 1));
 }
 
+// Workgroups of dev::flow the device holds at once (four per CU), and the
+// columns per lane below which a tile is not split further.
+constexpr int64_t kFlowSlots = 1024;
+constexpr double kFlowLaneCols = 12;
+// Panel entries up to which the sweeps take one launch (dev::flow) instead of
+// one per level.  Local solves of the thrust model, flow against levels, us:
+//   entries    complex128     complex64
+//     2.6M      78 / 153       83 / 147
+//      38M     226 / 313      199 / 333
+//     118M     423 / 474      338 / 431
+//     246M     792 / 809      555 / 593
+//     418M    1242 / 1218     832 / 767
+//    1295M    3646 / 3562    2178 / 2023
+// Beyond the line every level fills the device several times over, two
+// batches hide each other's tails, and plain accesses beat coherent ones.
+constexpr int64_t kFlowEntries = 300000000;
+
+// Collects the tiles of a set of batches (in their solve layout) and makes the
+// task list of their single-vector sweeps.
+struct FlowHost {
+  struct Item {
+    dev::Tile t;
+    int32_t batch;
+    int64_t sn;  // supernode over all batches
+  };
+  bool c64 = false;
+  std::vector<std::vector<Item>> lf, lb;  // tiles per level
+  std::vector<int32_t> uoff;
+  std::vector<int64_t> parent;
+
+  void add(const BatchHost& B, int batch) {
+    const int64_t base = (int64_t)parent.size(), nsn = (int64_t)B.w.size();
+    for (int64_t s = 0; s < nsn; ++s) {
+      parent.push_back(B.parent[s] < 0 ? -1 : base + B.parent[s]);
+      uoff.push_back(B.uoff[s]);
+    }
+    auto take = [&](const std::vector<dev::Task>& K, const std::vector<dev::Tile>& T, const std::vector<int64_t>& lev,
+                    std::vector<std::vector<Item>>& out) {
+      if (out.size() + 1 < lev.size()) out.resize(lev.size() - 1);
+      for (size_t l = 0; l + 1 < lev.size(); ++l)
+        for (int64_t q = lev[l]; q < lev[l + 1]; ++q)
+          for (int u = 0; u < K[q].ntile; ++u) {
+            const dev::Tile& t = T[K[q].tile0 + u];
+            out[l].push_back({t, batch, base + t.sn});
+          }
+    };
+    take(B.kf, B.tf, B.lev_f, lf);
+    take(B.kb, B.tb, B.lev_b, lb);
+  }
+
+  void build(Flow& F) {
+    const int64_t nsn = (int64_t)parent.size();
+    if (3 * nsn >= INT32_MAX / dev::kFlowPad) fail(HELM_EINVAL, "batch too large for 32-bit solve indices");
+    // LDS input entries: a tile that shares its workgroup fits its share, a
+    // wide one is taken in passes
+    int64_t chunk = 64;
+    for (auto* L : {&lf, &lb})
+      for (auto& l : *L)
+        for (auto& i : l) chunk = std::max<int64_t>(chunk, i.t.ncols);
+    chunk = std::min<int64_t>((std::max<int64_t>(chunk, 4 * std::min<int64_t>(chunk, 192)) + 63) / 64 * 64, 1024);
+    F.chunk = (int)chunk;
+    // waves per tile where a level has tiles to spare: by width, so a wave has
+    // columns enough to hide its gather (a complex64 column is half the bytes)
+    auto wpt_of = [&](int32_t ncols) {
+      int w = ncols <= (c64 ? 192 : 96) ? 1 : ncols <= (c64 ? 512 : 384) ? 2 : 4;
+      while (w < 4 && (4 / w) * (int64_t)ncols > chunk) w *= 2;
+      return w;
+    };
+    std::vector<dev::FlowTask> tasks;
+    std::vector<std::array<int64_t, 4>> of;  // supernodes of a task's tiles
+    std::vector<uint32_t> ntf(nsn, 0), ntb(nsn, 0), need(nsn, 0);
+    struct Cut {
+      dev::FlowTile t;
+      int64_t sn;
+    };
+    // One level: its tiles are split over more waves, then into ranges of
+    // fewer rows (which need only the panel columns their own rows reach),
+    // while the tasks stay within one per workgroup of the device and a lane
+    // keeps a dozen columns: a task costs about ten microseconds of
+    // latencies whatever its size.
+    auto emit = [&](const std::vector<Item>& l, bool bwd) {
+      const int64_t n = (int64_t)l.size();
+      int hmin = 64, wmax = 1;
+      while (wmax < 4 && n * wmax * 2 <= 4 * kFlowSlots) wmax *= 2;
+      while (hmin > 16 && n * (64 / hmin) * 2 <= kFlowSlots) hmin /= 2;
+      std::vector<Cut> v;
+      for (auto& i : l) {
+        const dev::Tile& t = i.t;
+        int h = 64, w = wpt_of(t.ncols);
+        auto per_lane = [&] {
+          const int r = std::min(h, t.nrows);
+          return (double)t.ncols / (w * (r <= 32 ? 64 / r : 1));
+        };
+        while (w < wmax && per_lane() > kFlowLaneCols) w *= 2;
+        while (h > hmin && per_lane() > kFlowLaneCols) h /= 2;
+        for (int32_t r = 0; r < t.nrows; r += h) {
+          dev::FlowTile f{};
+          f.ld = t.nrows;
+          f.nrows = std::min(h, t.nrows - r);
+          f.row0 = t.row0 + r;
+          f.c0 = t.c0;
+          f.w = t.w;
+          f.aux = t.aux;
+          f.uoff = uoff[i.sn];
+          f.wpt = (int8_t)w;
+          f.batch = (int8_t)i.batch;
+          f.bwd = bwd ? 1 : 0;
+          if (bwd) {
+            f.off = t.off + r + (int64_t)r * t.nrows;
+            f.col0 = t.col0 + r;
+            f.ncols = t.ncols - r;
+          } else {
+            f.off = t.off + r;
+            f.col0 = t.col0;
+            f.ncols = std::min(t.ncols, f.row0 + f.nrows);
+          }
+          v.push_back({f, i.sn});
+          (bwd ? ntb : ntf)[i.sn]++;
+        }
+      }
+      std::stable_sort(v.begin(), v.end(), [](const Cut& x, const Cut& y) { return x.t.wpt > y.t.wpt; });
+      for (size_t q = 0; q < v.size();) {
+        const dev::FlowTile f = v[q].t;
+        dev::FlowTask k{};
+        std::array<int64_t, 4> s{-1, -1, -1, -1};
+        int u = 0;
+        for (; q < v.size() && u < 4 / f.wpt && v[q].t.wpt == f.wpt && v[q].t.batch == f.batch; ++q, ++u) {
+          k.t[u] = v[q].t;
+          s[u] = v[q].sn;
+        }
+        for (; u < 4; ++u) {
+          k.t[u].wpt = f.wpt;
+          k.t[u].batch = f.batch;
+          k.t[u].bwd = f.bwd;
+          k.t[u].ld = 1;
+        }
+        tasks.push_back(k);
+        of.push_back(s);
+      }
+    };
+    for (auto& l : lf) emit(l, false);
+    F.nf = (int)tasks.size();
+    for (auto& l : lb) emit(l, true);
+    if (tasks.size() >= (size_t)INT32_MAX / 2) fail(HELM_EINVAL, "batch too large for 32-bit solve indices");
+    F.n = (int)tasks.size();
+    // counters: [s] forward tiles of the children of s done, [nsn + s]
+    // backward tiles of s, [2 nsn + s] forward tiles of a root s
+    for (int64_t s = 0; s < nsn; ++s)
+      if (parent[s] >= 0) need[parent[s]] += ntf[s];
+    for (size_t k = 0; k < tasks.size(); ++k) {
+      int8_t waits = 0;
+      for (int u = 0; u < 4; ++u) {
+        dev::FlowTile& t = tasks[k].t[u];
+        const int64_t s = of[k][u], p = s >= 0 ? parent[s] : -1;
+        t.wait = -1;
+        if (s < 0) continue;
+        t.need = !t.bwd ? need[s] : p >= 0 ? ntb[p] : ntf[s];
+        if (t.need) t.wait = (int32_t)(!t.bwd ? s : p >= 0 ? nsn + p : 2 * nsn + s), waits = 1;
+        t.sig = (int32_t)(t.bwd ? nsn + s : p >= 0 ? p : 2 * nsn + s);
+      }
+      for (auto& t : tasks[k].t) t.waits = waits;
+    }
+    // what every wait relies on: taken in this order, a counter has been
+    // raised to exactly the awaited amount by earlier tasks, and by no later one
+    std::vector<uint32_t> seen(3 * nsn, 0), end(3 * nsn, 0);
+    for (size_t k = 0; k < tasks.size(); ++k) {
+      for (int u = 0; u < 4; ++u) {
+        const dev::FlowTile& t = tasks[k].t[u];
+        if (t.wait < 0) continue;
+        if (seen[t.wait] != t.need) fail(HELM_EINVAL, "internal: a solve task would wait for a later one");
+        end[t.wait] = t.need;
+      }
+      for (int u = 0; u < 4; ++u)
+        if (of[k][u] >= 0) seen[tasks[k].t[u].sig]++;
+    }
+    for (int64_t q = 0; q < 3 * nsn; ++q)
+      if (end[q] && seen[q] != end[q]) fail(HELM_EINVAL, "internal: a solve counter misses its target");
+    F.tasks.upload(tasks);
+    F.cnt.upload(std::vector<uint32_t>(dev::kFlowHead + (size_t)dev::kFlowPad * 3 * nsn, 0));
+  }
+};
+
+dev::FlowBatch flow_view(const dev::Batch& v) {
+  return {v.pf, v.pb, v.rows, v.bidx, v.fcon_ptr, v.fcon_idx, v.fcon2, v.ubuf, v.y, v.x};
+}
+
+dev::FlowArgs flow_args(const Flow& F, uint32_t* cnt) {
+  dev::FlowArgs a{};
+  a.tasks = F.tasks.p;
+  a.cnt = cnt;
+  a.chunk = F.chunk;
+  return a;
+}
+
 // Forward then backward level sweeps; with profiling on, every level launch
 // of the fine batch is timed (the coarse batch is timed as a whole).
 // Coarse-batch solve (forward and backward sweeps) through a view whose
@@ -612,7 +812,14 @@ bool coop_solve(const BatchDev& b, const dev::Batch& v, const double* in, hipStr
   return false;
 }
 
-void batch_solve_view(const BatchDev& b, const dev::Batch& v, const double* in, hipStream_t s) {
+void batch_solve_view(const BatchDev& b, const dev::Batch& v, const Flow& F, uint32_t* cnt, const double* in,
+                      hipStream_t s) {
+  if (F.ready()) {
+    dev::FlowArgs a = flow_args(F, cnt);
+    a.b[0] = flow_view(v);
+    dev::flow(a, false, true, 0, F.n, true, in, s);
+    return;
+  }
   if (b.coop > 0 && coop_solve(b, v, in, s)) return;
   for (size_t l = 0; l + 1 < b.lev_f.size(); ++l) {
     dev::fwd_level(v, b.lev_f[l], b.ktile_f[l], in, b.chunk_f[l], true, s);
@@ -1033,6 +1240,8 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
     st.factor_scratch_bytes = std::max(st.factor_scratch_bytes, sb);
     fsec += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   }
+  FlowHost fh;
+  fh.c64 = c64;
   for (int32_t k = 0; k < nb; ++k) {
     BatchHost fb;
     int32_t np = 0;
@@ -1043,6 +1252,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
                 on_device, prec, split_min, snb, fb, c.fine[k], np, fs, num_all.empty() ? nullptr : &pre);
     npert += np;
     fsec += fs;
+    if (on_device) fh.add(fb, k);
     st.factor_entries += fb.nf + fb.nb;
     st.levels_fwd = std::max(st.levels_fwd, (int32_t)fb.lev_f.size() - 1);
     st.levels_bwd = std::max(st.levels_bwd, (int32_t)fb.lev_b.size() - 1);
@@ -1050,6 +1260,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
     st.factor_flops += fb.flops;
     npos_all += fb.npos;
   }
+  if (on_device && st.factor_entries <= kFlowEntries && !(opts && opts->sn_jobs_min > 0)) fh.build(c.flow_fine);
   if (nb > 1) {
     // one output vector in subdomain order, as the prolongation map expects
     c.xall.alloc(2 * (size_t)npos_all);
@@ -1209,7 +1420,14 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
         dev::coarse_update(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.AZ_ptr.p, c.AZ_col.p, c.AZ_val.p, x.p, x.p,
                            y.p, x2.p, G, nullptr);
       });
-      choose_coarse_launch(c, cmode);
+      if (cmode == 0 && cb.nf + cb.nb <= kFlowEntries) {
+        FlowHost ch;
+        ch.add(cb, 0);
+        ch.build(c.flow_coarse);
+        c.flow_cnt_noalloc.upload(std::vector<uint32_t>(c.flow_coarse.cnt.n, 0));
+      } else {
+        choose_coarse_launch(c, cmode);
+      }
       st.coarse_grid = c.coarse.coop;
     }
   }
@@ -1269,7 +1487,7 @@ void apply_coarse_scratch(Ctx& c, const double* r, double* q, hipStream_t s, voi
   v.y = y;
   v.x = x;
   v.ubuf = ub;
-  batch_solve_view(c.coarse, v, cv, s);
+  batch_solve_view(c.coarse, v, c.flow_coarse, c.flow_cnt_noalloc.p, cv, s);
   dev::spmv_real(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, x, q, c.g_Zp, s);
 }
 
@@ -1277,7 +1495,7 @@ void apply_coarse(Ctx& c, const double* r, double* q, hipStream_t s) {
   const bool p = c.prof.on;
   if (p) c.prof.begin(s);
   dev::spmv_real(c.ZT.n, c.ZT_ptr.p, c.ZT_col.p, c.ZT_val.p, r, c.cvec.p, c.g_ZT, s);
-  batch_solve(c.coarse, c.cvec.p, s, &c.prof, false);
+  batch_solve_view(c.coarse, c.coarse.view(), c.flow_coarse, c.flow_coarse.cnt.p, c.cvec.p, s);
   dev::spmv_real(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.coarse.x.p, q, c.g_Zp, s);
   if (p) {
     const double zb = 2.0 * (12.0 * (double)c.Z.col.size() + 8.0 * c.D.n) + 16.0 * (c.D.n + c.E.n);
@@ -1307,9 +1525,28 @@ void for_batches(Ctx& c, hipStream_t s, F&& f) {
 }
 
 void apply_oras(Ctx& c, const double* r, double* z, const double* q, hipStream_t s) {
-  Profiler* prof = c.prof.on ? &c.prof : nullptr;
-  for_batches(c, s, [&](BatchDev& b, hipStream_t sk) { batch_solve(b, r, sk, prof, true); });
   const bool p = c.prof.on;
+  const Flow& F = c.flow_fine;
+  if (F.ready()) {
+    dev::FlowArgs a = flow_args(F, F.cnt.p);
+    for (int k = 0; k < c.nbatch; ++k) a.b[k] = flow_view(c.fine[k].view());
+    const bool c64 = c.fine[0].c64 != 0;
+    if (p) {
+      // the two sweeps apart, each timed
+      double bf = 0, bb = 0;
+      for (int k = 0; k < c.nbatch; ++k) bf += sum(c.fine[k].bytes_f), bb += sum(c.fine[k].bytes_b);
+      c.prof.begin(s);
+      dev::flow(a, c64, false, 0, F.nf, false, r, s);
+      c.prof.end(HELM_K_TRSV_FWD, bf, s);
+      c.prof.begin(s);
+      dev::flow(a, c64, false, F.nf, F.n, true, r, s);
+      c.prof.end(HELM_K_TRSV_BWD, bb, s);
+    } else {
+      dev::flow(a, c64, false, 0, F.n, true, r, s);
+    }
+  } else {
+    for_batches(c, s, [&](BatchDev& b, hipStream_t sk) { batch_solve(b, r, sk, &c.prof, true); });
+  }
   if (p) c.prof.begin(s);
   dev::prolong(c.D.n, c.pro_ptr.p, c.pro_idx.p, c.pro_w.p, c.fine[0].xout(), q, z, s);
   if (p) c.prof.end(HELM_K_PROLONG, 12.0 * c.pro_w.n + 28.0 * c.pro_w.n + 16.0 * c.D.n * (q ? 2 : 1) + 8.0 * c.D.n, s);
@@ -1325,7 +1562,7 @@ void precond_stage1(Ctx& c, const double* r, hipStream_t s) {
   const bool p = c.prof.on;
   if (p) c.prof.begin(s);
   dev::spmv_real(c.ZT.n, c.ZT_ptr.p, c.ZT_col.p, c.ZT_val.p, r, c.cvec.p, c.g_ZT, s);
-  batch_solve(c.coarse, c.cvec.p, s, &c.prof, false);
+  batch_solve_view(c.coarse, c.coarse.view(), c.flow_coarse, c.flow_coarse.cnt.p, c.cvec.p, s);
   dev::coarse_update(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.AZ_ptr.p, c.AZ_col.p, c.AZ_val.p, c.coarse.x.p, r,
                      c.q.p, c.t.p, c.g_AZ, s);
   if (p) {

@@ -273,8 +273,8 @@ class Helm:
         default, -1: never); batches: 1 to 4 subdomain batches whose level
         sweeps run concurrently (0: 2); perturb_pivots: replace zero or tiny
         pivots and count them instead of failing with HELM_ESINGULAR;
-        coarse_launch: 0 timed, 1 per-level launches, 2 one cooperative
-        launch for the coarse solve; split_front_rows: fronts of at least
+        coarse_launch: 0 one launch of tasks that wait for each other, 1
+        per-level launches, 2 one cooperative launch for the coarse solve; split_front_rows: fronts of at least
         this many rows factorised by several workgroups each (0: 256, -1:
         never)."""
         part = np.ascontiguousarray(part, dtype=np.int32)
