@@ -268,11 +268,12 @@ void scale_by_inv_set(int nr, int64_t n, const PtrSetC& w, const PtrSetC& nrm, c
 
 // ---- block (multi-right-hand-side) operations, S in {2, 4, 8, 16},
 //      interleaved n x S vectors (device_block.hip) ----
-// one wavefront per tile: tiles [tile0, tile0 + ntiles) of the level
-void fwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int S, const double* bin, double* yb, double* ubb,
+// S in {2, 4, 8}: tiles [tile0, tile0 + ntiles) of a level, the first nwide of
+// them wide (four waves each)
+void fwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int64_t nwide, int S, const double* bin, double* yb,
+                     double* ubb, bool coarse, hipStream_t s);
+void bwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int64_t nwide, int S, const double* yb, double* xb,
                      bool coarse, hipStream_t s);
-void bwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int S, const double* yb, double* xb, bool coarse,
-                     hipStream_t s);
 // 16 right-hand sides on MFMA.  Forward: stage every supernode's input
 // block of the level once (gather kernel, one workgroup per supernode of
 // `sns`, gy workgroups per supernode each taking every gy-th run of 256

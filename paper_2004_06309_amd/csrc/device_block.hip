@@ -4,8 +4,8 @@
 //
 // Block vectors are interleaved: entry (i, r) of an n x S block sits at
 // i * S + r, so every gather of a row fetches S contiguous complex values.
-// The level kernels stream each panel tile once for all S columns: one
-// wavefront per tile, a lane per tile row holding S accumulators.
+// The level kernels stream each panel tile once for all S columns, as small
+// dense contractions on MFMA.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -18,7 +18,6 @@ namespace dev {
 namespace {
 
 constexpr int kWG = 256;
-constexpr int kBlkLds = 1024;  // complex entries of the staged input block
 
 __device__ __forceinline__ void cfma(double& ar, double& ai, double2 a, double2 v) {
   ar = fma(a.x, v.x, ar);
@@ -28,123 +27,6 @@ __device__ __forceinline__ void cfma(double& ar, double& ai, double2 a, double2 
 }
 __device__ __forceinline__ double2 widen(double2 a) { return a; }
 __device__ __forceinline__ double2 widen(float2 a) { return make_double2((double)a.x, (double)a.y); }
-
-template <class PT, int S, int kCoarse>
-__global__ __launch_bounds__(64) void fwd_block_kernel(const Tile* __restrict__ tiles, Batch b,
-                                                       const double2* __restrict__ bin, double2* __restrict__ yb,
-                                                       double2* __restrict__ ubb) {
-  __shared__ double2 vin[kBlkLds];
-  constexpr int CB = kBlkLds / S;
-  const Tile t = tiles[blockIdx.x];
-  const int lane = threadIdx.x;
-  const int sn = t.sn, c0 = b.sn_c0[sn], w = b.sn_w[sn], frow0 = b.sn_frow0[sn];
-  const PT* __restrict__ P = reinterpret_cast<const PT*>(b.pf) + t.off + lane;
-  double ar[S], ai[S];
-#pragma unroll
-  for (int r = 0; r < S; ++r) ar[r] = ai[r] = 0;
-  for (int cb = 0; cb < t.ncols; cb += CB) {
-    const int cn = min(CB, t.ncols - cb);
-    for (int e = lane; e < cn * S; e += 64) {
-      const int k = e / S, r = e % S, kk = cb + k;
-      double2 v = bin[(int64_t)b.bidx[c0 + kk] * S + r];
-      const int fr = frow0 + kk;
-      for (int q = b.fcon_ptr[fr]; q < b.fcon_ptr[fr + 1]; ++q) {
-        const double2 u = ubb[(int64_t)b.fcon_idx[q] * S + r];
-        v.x -= u.x;
-        v.y -= u.y;
-      }
-      vin[e] = v;
-    }
-    __syncthreads();
-    if (lane < t.nrows) {
-      const PT* p = P + (int64_t)cb * t.nrows;
-      int k = 0;
-      for (; k + 2 <= cn; k += 2) {
-        const double2 a0 = widen(p[(int64_t)k * t.nrows]);
-        const double2 a1 = widen(p[(int64_t)(k + 1) * t.nrows]);
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-          cfma(ar[r], ai[r], a0, vin[k * S + r]);
-          cfma(ar[r], ai[r], a1, vin[(k + 1) * S + r]);
-        }
-      }
-      for (; k < cn; ++k) {
-        const double2 a0 = widen(p[(int64_t)k * t.nrows]);
-#pragma unroll
-        for (int r = 0; r < S; ++r) cfma(ar[r], ai[r], a0, vin[k * S + r]);
-      }
-    }
-    __syncthreads();
-  }
-  if (lane < t.nrows) {
-    const int row = t.row0 + lane;
-    if (row < w) {
-#pragma unroll
-      for (int r = 0; r < S; ++r) yb[(int64_t)(c0 + row) * S + r] = make_double2(ar[r], ai[r]);
-    } else {
-      const int fr = frow0 + row;
-      for (int q = b.fcon_ptr[fr]; q < b.fcon_ptr[fr + 1]; ++q) {
-        const int64_t src = (int64_t)b.fcon_idx[q] * S;
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-          const double2 u = ubb[src + r];
-          ar[r] += u.x;
-          ai[r] += u.y;
-        }
-      }
-      const int64_t dst = (int64_t)(b.sn_uoff[sn] + row - w) * S;
-#pragma unroll
-      for (int r = 0; r < S; ++r) ubb[dst + r] = make_double2(ar[r], ai[r]);
-    }
-  }
-}
-
-template <class PT, int S, int kCoarse>
-__global__ __launch_bounds__(64) void bwd_block_kernel(const Tile* __restrict__ tiles, Batch b,
-                                                       const double2* __restrict__ yb, double2* __restrict__ xb) {
-  __shared__ double2 vin[kBlkLds];
-  constexpr int CB = kBlkLds / S;
-  const Tile t = tiles[blockIdx.x];
-  const int lane = threadIdx.x;
-  const int sn = t.sn, c0 = b.sn_c0[sn], w = b.sn_w[sn];
-  const int64_t roff = b.sn_roff[sn];
-  const PT* __restrict__ P = reinterpret_cast<const PT*>(b.pb) + t.off + lane;
-  double ar[S], ai[S];
-#pragma unroll
-  for (int r = 0; r < S; ++r) ar[r] = ai[r] = 0;
-  for (int cb = 0; cb < t.ncols; cb += CB) {
-    const int cn = min(CB, t.ncols - cb);
-    for (int e = lane; e < cn * S; e += 64) {
-      const int k = e / S, r = e % S, c = t.col0 + cb + k;
-      vin[e] = c < w ? yb[(int64_t)(c0 + c) * S + r] : xb[(int64_t)b.rows[roff + (c - w)] * S + r];
-    }
-    __syncthreads();
-    if (lane < t.nrows) {
-      const PT* p = P + (int64_t)cb * t.nrows;
-      int k = 0;
-      for (; k + 2 <= cn; k += 2) {
-        const double2 a0 = widen(p[(int64_t)k * t.nrows]);
-        const double2 a1 = widen(p[(int64_t)(k + 1) * t.nrows]);
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-          cfma(ar[r], ai[r], a0, vin[k * S + r]);
-          cfma(ar[r], ai[r], a1, vin[(k + 1) * S + r]);
-        }
-      }
-      for (; k < cn; ++k) {
-        const double2 a0 = widen(p[(int64_t)k * t.nrows]);
-#pragma unroll
-        for (int r = 0; r < S; ++r) cfma(ar[r], ai[r], a0, vin[k * S + r]);
-      }
-    }
-    __syncthreads();
-  }
-  if (lane < t.nrows) {
-    const int64_t dst = (int64_t)(c0 + t.row0 + lane) * S;
-#pragma unroll
-    for (int r = 0; r < S; ++r) xb[dst + r] = make_double2(ar[r], ai[r]);
-  }
-}
 
 // ---- MFMA form for 16 right-hand sides --------------------------------------
 // A tile (<= 64 rows x ncols) times the 16-column input block is a small
@@ -456,8 +338,8 @@ __global__ __launch_bounds__(kWG, sizeof(T) == 4 ? 5 : 4) void level_mfma_narrow
 }
 
 // Stages a pass of a tile's input block into G: entries e = base + q stride
-// (q < 8) of the cn columns from cb, entry e being column col0 + cb + e / 16
-// and right-hand side e % 16.  Forward: the restricted right-hand side,
+// (q < 8) of the cn columns from cb, entry e being column col0 + cb + e / S
+// and right-hand side e % S.  Forward: the restricted right-hand side,
 // gathered through bidx (restriction, nested-dissection permutation and
 // pivot order in one index), minus the children's updates routed to the
 // column's front row (at most two, read through fcon2; longer lists through
@@ -467,7 +349,7 @@ __global__ __launch_bounds__(kWG, sizeof(T) == 4 ? 5 : 4) void level_mfma_narrow
 // loads, so a pass costs two memory round trips.  The backward loads are
 // unconditional (entries past the pass read a valid dummy address and are
 // not stored), so no load waits behind a branch.
-template <class T, int kFwd>
+template <class T, int kFwd, int S = 16>
 __device__ __forceinline__ void stage_pass(const Batch& b, const Tile& t, int cb, int cn, int base, int stride,
                                            typename Mf<T>::C2* G, const double2* __restrict__ src,
                                            const double2* aux) {
@@ -478,24 +360,24 @@ __device__ __forceinline__ void stage_pass(const Batch& b, const Tile& t, int cb
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       const int e = base + q * stride;
-      const int c = t.col0 + cb + (e >> 4);
+      const int c = t.col0 + cb + e / S;
       // an ancestor column reads its position from the row list; the
       // others read bidx[0] (any valid address) and ignore it
-      const bool up = e < cn * 16 && c >= t.w;
+      const bool up = e < cn * S && c >= t.w;
       rv[q] = *(up ? b.rows + t.aux + (c - t.w) : b.bidx);
     }
     double2 v[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       const int e = base + q * stride;
-      const int c = t.col0 + cb + (e >> 4), r = e & 15;
-      const bool in = e < cn * 16;
-      v[q] = *(!in ? src + r : (c < t.w ? src + (int64_t)(t.c0 + c) * 16 + r : aux + (int64_t)rv[q] * 16 + r));
+      const int c = t.col0 + cb + e / S, r = e % S;
+      const bool in = e < cn * S;
+      v[q] = *(!in ? src + r : (c < t.w ? src + (int64_t)(t.c0 + c) * S + r : aux + (int64_t)rv[q] * S + r));
     }
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       const int e = base + q * stride;
-      if (e < cn * 16) G[e] = C2{(T)v[q].x, (T)v[q].y};
+      if (e < cn * S) G[e] = C2{(T)v[q].x, (T)v[q].y};
     }
   } else {
     int idx[kQ];
@@ -503,36 +385,50 @@ __device__ __forceinline__ void stage_pass(const Batch& b, const Tile& t, int cb
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       const int e = base + q * stride;
-      const bool in = e < cn * 16;
-      const int c = t.col0 + cb + (e >> 4);
-      idx[q] = in ? b.bidx[t.c0 + c] : 0;
-      ch[q] = in ? b.fcon2[t.aux + c] : make_int2(-1, -1);
+      const bool in = e < cn * S;
+      const int c = in ? t.col0 + cb + e / S : 0;  // column 0 is always there
+      idx[q] = b.bidx[t.c0 + c];
+      const int2 f = b.fcon2[t.aux + c];
+      ch[q] = in ? f : make_int2(-1, -1);
     }
+    // the inputs and the (at most two) updates of four entries at a time, all
+    // loads before the first use; missing updates read the input instead
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      const int e = base + q * stride;
-      if (e >= cn * 16) continue;
-      const int r = e & 15;
-      double2 v = src[(int64_t)idx[q] * 16 + r];
-      const int2 c2 = ch[q];
-      if (c2.x >= 0) {
-        const double2 u0 = aux[(int64_t)c2.x * 16 + r];
-        v.x -= u0.x;
-        v.y -= u0.y;
-        if (c2.y >= 0) {
-          const double2 u1 = aux[(int64_t)c2.y * 16 + r];
-          v.x -= u1.x;
-          v.y -= u1.y;
-        }
-      } else if (c2.x < -1) {
-        const int fr = t.aux + t.col0 + cb + (e >> 4);
-        for (int k = -2 - c2.x; k < b.fcon_ptr[fr + 1]; ++k) {
-          const double2 u = aux[(int64_t)b.fcon_idx[k] * 16 + r];
-          v.x -= u.x;
-          v.y -= u.y;
-        }
+    for (int h = 0; h < kQ; h += kQ / 2) {
+      double2 v[kQ / 2], u0[kQ / 2], u1[kQ / 2];
+#pragma unroll
+      for (int q = 0; q < kQ / 2; ++q) {
+        const int r = (base + (h + q) * stride) % S;
+        const int2 c2 = ch[h + q];
+        const double2* in = src + (int64_t)idx[h + q] * S + r;
+        v[q] = *in;
+        u0[q] = *(c2.x >= 0 ? aux + (int64_t)c2.x * S + r : in);
+        u1[q] = *(c2.y >= 0 ? aux + (int64_t)c2.y * S + r : in);
       }
-      G[e] = C2{(T)v.x, (T)v.y};
+#pragma unroll
+      for (int q = 0; q < kQ / 2; ++q) {
+        const int e = base + (h + q) * stride;
+        if (e >= cn * S) continue;
+        const int r = e % S;
+        const int2 c2 = ch[h + q];
+        double2 w = v[q];
+        if (c2.x >= 0) {
+          w.x -= u0[q].x;
+          w.y -= u0[q].y;
+          if (c2.y >= 0) {
+            w.x -= u1[q].x;
+            w.y -= u1[q].y;
+          }
+        } else if (c2.x < -1) {
+          const int fr = t.aux + t.col0 + cb + e / S;
+          for (int k = -2 - c2.x; k < b.fcon_ptr[fr + 1]; ++k) {
+            const double2 u = aux[(int64_t)b.fcon_idx[k] * S + r];
+            w.x -= u.x;
+            w.y -= u.y;
+          }
+        }
+        G[e] = C2{(T)w.x, (T)w.y};
+      }
     }
   }
 }
@@ -656,6 +552,207 @@ __global__ __launch_bounds__(kWG, 3) void level_fused_kernel(const Tile* __restr
     for (int j = 0; j < 4; ++j) {
       const int rloc = 16 * rb + Mf<T>::row(lk, j);
       if (rloc < nr) put_row<kFwd>(b, t, rloc, lr, (double)dre[rb][j], (double)dim[rb][j], out, ubb);
+    }
+  }
+}
+
+// ---- MFMA form for 2, 4 and 8 right-hand sides ------------------------------
+// With at most eight right-hand sides the 16 columns of an MFMA hold the real
+// and the imaginary parts side by side: with B1 = [Bre | Bim] and
+// B2 = [-Bim | Bre], D = Are B1 + Aim B2 = [Dre | Dim], two MFMAs per four
+// columns and 16 rows instead of four.  Always FP64 MFMA, also for complex64
+// panels (widened in registers): these widths accumulate in FP64.
+// Measured at 8 columns, 168,075 unknowns, complex64 panels (1.05 GB), one
+// forward or backward level of one of two batches: 76 / 131 us with one lane
+// per tile row and FP64 vector arithmetic, 22 / 20 us so (five right-hand sides
+// solved together: 37.4 -> 12.2 ms).  Bound by latencies on operators of that
+// size (staging, panel, epilogue), by HBM on large ones.
+//
+// Streams the k-steps k0 = ks0, ks0 + kst, ... < cn of a panel tile (nr rows,
+// ld apart, at most NRB 16-row blocks) against the staged block Bk (S
+// right-hand sides per column).  D k-steps of panel loads stay in flight, each
+// register set refilled right after its MFMAs; addresses are clamped as in
+// mfma_stream.  (With two k-steps in flight a level of a small operator took
+// 20-25 us, most of it panel latency.)
+template <class PT, int S, int NRB, int D>
+__device__ __forceinline__ void mfma_stream_small(const PT* __restrict__ P, int ld, int nr, int cn,
+                                                  const double2* __restrict__ Bk, int ks0, int kst, dv4* d) {
+  if (ks0 >= cn) return;  // uniform: the wave has no k-step
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, r = lr & 7;
+  const bool im = lr >= 8, used = r < S;
+  const int rs = used ? r : 0;
+  int roff[NRB];
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb) roff[rb] = min(16 * rb + lr, nr - 1);
+  PT a[D][NRB];
+  auto load = [&](int k0, PT (&w)[NRB]) {
+    const PT* pc = P + (int64_t)min(k0 + lk, cn - 1) * ld;
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) w[rb] = ldp(pc + roff[rb]);
+  };
+  auto step = [&](int k0, const PT (&w)[NRB]) {
+    const double2 b = Bk[min(k0 + lk, cn - 1) * S + rs];
+    const bool in = used && k0 + lk < cn;
+    const double b1 = in ? (im ? b.y : b.x) : 0.0, b2 = in ? (im ? b.x : -b.y) : 0.0;
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+      if (rb == 0 || 16 * rb < nr) {  // uniform
+        const double2 v = widen(w[rb]);
+        d[rb] = Mf<double>::mma(v.x, b1, d[rb]);
+        d[rb] = Mf<double>::mma(v.y, b2, d[rb]);
+      }
+  };
+#pragma unroll
+  for (int u = 0; u < D; ++u) load(ks0 + u * kst, a[u]);
+  int n = (cn - ks0 + kst - 1) / kst, k0 = ks0;  // k-steps from k0 on
+  for (; n >= 2 * D; n -= D, k0 += D * kst) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      step(k0 + u * kst, a[u]);
+      load(k0 + (u + D) * kst, a[u]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  for (; n > 0; n -= D, k0 += D * kst) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      if (u < n) step(k0 + u * kst, a[u]);
+      if (u + D < n) load(k0 + (u + D) * kst, a[u]);
+    }
+  }
+}
+
+// Stores the rows row0 + 4 j + lk (j < 4, those below nr) of a tile, component
+// c = 2 r + (0: real, 1: imaginary) of the interleaved block rows: forward
+// pivot rows and backward rows go to out; forward update rows add the
+// children's updates and go to the supernode's update vector.  Index pairs,
+// then values, then stores.
+template <int kFwd, int S>
+__device__ __forceinline__ void put_small(const Batch& b, const Tile& t, int uoff, int rloc0, int nr, int c, double* v,
+                                          double* out, double* ubb) {
+  const int lk = (threadIdx.x & 63) >> 4;
+  if constexpr (!kFwd) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int rloc = rloc0 + 4 * j + lk;
+      if (rloc < nr) out[(int64_t)(t.c0 + t.row0 + rloc) * (2 * S) + c] = v[j];
+    }
+  } else {
+    int2 c2[4];
+    double u0[4], u1[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int rloc = rloc0 + 4 * j + lk, row = t.row0 + rloc;
+      const bool upd = rloc < nr && row >= t.w;
+      const int2 f = b.fcon2[t.aux + (upd ? row : 0)];
+      c2[j] = upd ? f : make_int2(-1, -1);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {  // a missing child reads out's first row instead
+      u0[j] = *(c2[j].x >= 0 ? ubb + (int64_t)c2[j].x * (2 * S) + c : out + c);
+      u1[j] = *(c2[j].y >= 0 ? ubb + (int64_t)c2[j].y * (2 * S) + c : out + c);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int rloc = rloc0 + 4 * j + lk, row = t.row0 + rloc;
+      if (rloc >= nr) continue;
+      double x = v[j];
+      if (row < t.w) {
+        out[(int64_t)(t.c0 + row) * (2 * S) + c] = x;
+        continue;
+      }
+      if (c2[j].x >= 0) {
+        x += u0[j];
+        if (c2[j].y >= 0) x += u1[j];
+      } else if (c2[j].x < -1) {
+        for (int e = -2 - c2[j].x; e < b.fcon_ptr[t.aux + row + 1]; ++e)
+          x += ubb[(int64_t)b.fcon_idx[e] * (2 * S) + c];
+      }
+      ubb[(int64_t)(uoff + row - t.w) * (2 * S) + c] = x;
+    }
+  }
+}
+
+// One level of a sweep for S right-hand sides.  Workgroups [0, nwide split),
+// split = 4 / NRB, take a wide tile's rows in ranges of NRB 16-row blocks (1, 2
+// or 4: levels of few tiles spread over the device), the k-steps shared by the
+// four waves, partial sums added through LDS; with NRB = 4 the others take four
+// narrow tiles, a wave each.  Every workgroup stages its tile's inputs in LDS, a pass of
+// columns at a time (eight entries per thread).
+template <class PT, int kFwd, int S, int kCoarse, int NRB>
+__global__ __launch_bounds__(kWG, 3) void level_small_kernel(const Tile* __restrict__ tiles, int64_t ntiles,
+                                                             int64_t nwide, Batch b, const double2* __restrict__ src,
+                                                             const double2* aux,
+                                                             double* out, double* ubb) {
+  constexpr int kC = 8 * kWG / S, kCn = kC / 4;  // columns per pass: wide tile, narrow tile
+  constexpr int split = 4 / NRB, D = 8 / NRB;
+  __shared__ double2 G[8 * kWG];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15,
+            lk = lane >> 4, r = lr & 7;
+  const int c = 2 * r + (lr >> 3);  // component of this lane's MFMA column
+  const PT* __restrict__ panels = reinterpret_cast<const PT*>(kFwd ? b.pf : b.pb);
+  dv4 d[NRB];
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb) d[rb] = dv4{0, 0, 0, 0};
+  if ((int64_t)blockIdx.x < nwide * split) {
+    const Tile t = tiles[blockIdx.x / split];
+    constexpr int h = 64 / split;
+    const int r0 = (int)(blockIdx.x % split) * h, nr = min(h, t.nrows - r0);
+    if (nr <= 0) return;  // the whole workgroup
+    const int uoff = kFwd ? b.sn_uoff[t.sn] : 0;
+    for (int cb = 0; cb < t.ncols; cb += kC) {
+      const int cn = min(kC, t.ncols - cb);
+      stage_pass<double, kFwd, S>(b, t, cb, cn, threadIdx.x, kWG, G, src, aux);
+      __syncthreads();
+      mfma_stream_small<PT, S, NRB, D>(panels + t.off + (int64_t)cb * t.nrows + r0, t.nrows, nr, cn, G, 4 * wv, 16, d);
+      __syncthreads();
+    }
+    // partial sums of the four waves: [wave][rb][j][lane] (4 x 4 x 4 x 64
+    // doubles = the staging buffer)
+    double (*red)[4][4][64] = reinterpret_cast<double (*)[4][4][64]>(G);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) red[wv][rb][j][lane] = d[rb][j];
+    __syncthreads();
+    // wave q sums and stores row block q (row = 4 j + l / 16)
+    if (r < S && 16 * wv < nr) {
+      double v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[j] = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[j] += red[q][wv][j][lane];
+      }
+      put_small<kFwd, S>(b, t, uoff, r0 + 16 * wv, r0 + nr, c, v, out, ubb);
+    }
+    return;
+  }
+  if constexpr (NRB == 4) {
+  const int64_t g0 = nwide + ((int64_t)blockIdx.x - nwide * split) * 4;
+  const int64_t ti = g0 + wv;
+  const bool has = ti < ntiles;
+  Tile t{};
+  if (has) t = tiles[ti];
+  int np = 0;  // passes: the most any tile of the workgroup needs (uniform)
+  for (int q = 0; q < 4; ++q)
+    if (g0 + q < ntiles) np = max(np, (tiles[g0 + q].ncols + kCn - 1) / kCn);
+  double2* Gw = G + wv * kCn * S;
+  const int uoff = kFwd && has ? b.sn_uoff[t.sn] : 0;
+  for (int p = 0; p < np; ++p) {
+    const int cb = p * kCn;
+    const int cn = has ? max(0, min(kCn, t.ncols - cb)) : 0;
+    stage_pass<double, kFwd, S>(b, t, cb, cn, lane, 64, Gw, src, aux);
+    __syncthreads();
+    mfma_stream_small<PT, S, NRB, D>(panels + t.off + (int64_t)cb * t.nrows, t.nrows, t.nrows, cn, Gw, 0, 4, d);
+    __syncthreads();
+  }
+  if (!has || r >= S) return;
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb)
+    if (16 * rb < t.nrows) {
+      double v[4] = {d[rb][0], d[rb][1], d[rb][2], d[rb][3]};
+      put_small<kFwd, S>(b, t, uoff, 16 * rb, t.nrows, c, v, out, ubb);
     }
   }
 }
@@ -869,39 +966,57 @@ void with_width(int S, F&& f) {
 
 }  // namespace
 
-void fwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int S, const double* bin, double* yb, double* ubb,
-                     bool coarse, hipStream_t s) {
-  if (ntiles <= 0) return;
-  const Tile* t = b.tf + tile0;
-  auto in = reinterpret_cast<const double2*>(bin);
-  auto y = reinterpret_cast<double2*>(yb);
-  auto u = reinterpret_cast<double2*>(ubb);
-  with_width(S, [&](auto w) {
-    constexpr int W = decltype(w)::value;
-    if (coarse)
-      fwd_block_kernel<double2, W, 1><<<(unsigned)ntiles, 64, 0, s>>>(t, b, in, y, u);
-    else if (b.c64)
-      fwd_block_kernel<float2, W, 0><<<(unsigned)ntiles, 64, 0, s>>>(t, b, in, y, u);
-    else
-      fwd_block_kernel<double2, W, 0><<<(unsigned)ntiles, 64, 0, s>>>(t, b, in, y, u);
-  });
+// Launch of level_small_kernel: all tiles take four waves on levels of at most
+// 2048 tiles (a wave per tile would leave most of the 1024 SIMDs idle), and a
+// tile's rows are split over workgroups while those stay within 512, two per
+// CU (a level of 128 tiles: 24 us unsplit, 14 us in four).
+template <class PT, int kFwd, int S, int kCoarse>
+static void small_go(const Batch& b, const Tile* tiles, int64_t ntiles, int64_t nwide, const double* src,
+                     const double* aux, double* out, double* ubb, hipStream_t s) {
+  if (ntiles <= 2048) nwide = ntiles;
+  auto in = reinterpret_cast<const double2*>(src);
+  auto au = reinterpret_cast<const double2*>(aux);
+  if (ntiles <= 128)
+    level_small_kernel<PT, kFwd, S, kCoarse, 1><<<(unsigned)(4 * ntiles), kWG, 0, s>>>(tiles, ntiles, nwide, b, in, au, out, ubb);
+  else if (ntiles <= 256)
+    level_small_kernel<PT, kFwd, S, kCoarse, 2><<<(unsigned)(2 * ntiles), kWG, 0, s>>>(tiles, ntiles, nwide, b, in, au, out, ubb);
+  else
+    level_small_kernel<PT, kFwd, S, kCoarse, 4><<<(unsigned)(nwide + (ntiles - nwide + 3) / 4), kWG, 0, s>>>(
+        tiles, ntiles, nwide, b, in, au, out, ubb);
 }
 
-void bwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int S, const double* yb, double* xb, bool coarse,
-                     hipStream_t s) {
+template <int kFwd, int S>
+static void small_launch(const Batch& b, const Tile* tiles, int64_t ntiles, int64_t nwide, const double* src,
+                         const double* aux, double* out, double* ubb, bool coarse, hipStream_t s) {
+  if (coarse)
+    small_go<double2, kFwd, S, 1>(b, tiles, ntiles, nwide, src, aux, out, ubb, s);
+  else if (b.c64)
+    small_go<float2, kFwd, S, 0>(b, tiles, ntiles, nwide, src, aux, out, ubb, s);
+  else
+    small_go<double2, kFwd, S, 0>(b, tiles, ntiles, nwide, src, aux, out, ubb, s);
+}
+
+template <int kFwd>
+static void level_small(const Batch& b, const Tile* tiles, int64_t ntiles, int64_t nwide, int S, const double* src,
+                        const double* aux, double* out, double* ubb, bool coarse, hipStream_t s) {
+  if (S == 2)
+    small_launch<kFwd, 2>(b, tiles, ntiles, nwide, src, aux, out, ubb, coarse, s);
+  else if (S == 4)
+    small_launch<kFwd, 4>(b, tiles, ntiles, nwide, src, aux, out, ubb, coarse, s);
+  else
+    small_launch<kFwd, 8>(b, tiles, ntiles, nwide, src, aux, out, ubb, coarse, s);
+}
+
+void fwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int64_t nwide, int S, const double* bin, double* yb,
+                     double* ubb, bool coarse, hipStream_t s) {
   if (ntiles <= 0) return;
-  const Tile* t = b.tb + tile0;
-  auto y = reinterpret_cast<const double2*>(yb);
-  auto x = reinterpret_cast<double2*>(xb);
-  with_width(S, [&](auto w) {
-    constexpr int W = decltype(w)::value;
-    if (coarse)
-      bwd_block_kernel<double2, W, 1><<<(unsigned)ntiles, 64, 0, s>>>(t, b, y, x);
-    else if (b.c64)
-      bwd_block_kernel<float2, W, 0><<<(unsigned)ntiles, 64, 0, s>>>(t, b, y, x);
-    else
-      bwd_block_kernel<double2, W, 0><<<(unsigned)ntiles, 64, 0, s>>>(t, b, y, x);
-  });
+  level_small<1>(b, b.tf + tile0, ntiles, nwide, S, bin, ubb, yb, ubb, coarse, s);
+}
+
+void bwd_level_block(const Batch& b, int64_t tile0, int64_t ntiles, int64_t nwide, int S, const double* yb, double* xb,
+                     bool coarse, hipStream_t s) {
+  if (ntiles <= 0) return;
+  level_small<0>(b, b.tb + tile0, ntiles, nwide, S, yb, xb, xb, nullptr, coarse, s);
 }
 
 // Tiles [tile0, tile0 + nwide) go to the 4-wave kernel, the rest (narrow,

@@ -2035,7 +2035,8 @@ void batch_solve_block(BatchDev& b, int S, const double* in, hipStream_t s, Prof
                           b.tiles_f[l + 1] - b.tiles_f[l], b.nw16_f[l], in, b.y_b.p, b.ubuf_b.p, b.stage.p, !fine,
                           s);
     else
-      dev::fwd_level_block(v, b.tiles_f[l], b.tiles_f[l + 1] - b.tiles_f[l], S, in, b.y_b.p, b.ubuf_b.p, !fine, s);
+      dev::fwd_level_block(v, b.tiles_f[l], b.tiles_f[l + 1] - b.tiles_f[l], b.nwide_f[l], S, in, b.y_b.p,
+                           b.ubuf_b.p, !fine, s);
     if (each) prof->end(HELM_K_TRSV_FWD, b.pbytes_f[l] + S * (b.bytes_f[l] - b.pbytes_f[l]), s);
   }
   for (size_t l = 0; l + 1 < b.tiles_b.size(); ++l) {
@@ -2044,7 +2045,8 @@ void batch_solve_block(BatchDev& b, int S, const double* in, hipStream_t s, Prof
       dev::bwd_level_mfma(v, b.tiles_b[l], b.tiles_b[l + 1] - b.tiles_b[l], b.nw16_b[l], b.y_b.p, b.xout_b(), !fine,
                           s);
     else
-      dev::bwd_level_block(v, b.tiles_b[l], b.tiles_b[l + 1] - b.tiles_b[l], S, b.y_b.p, b.xout_b(), !fine, s);
+      dev::bwd_level_block(v, b.tiles_b[l], b.tiles_b[l + 1] - b.tiles_b[l], b.nwide_b[l], S, b.y_b.p, b.xout_b(),
+                           !fine, s);
     if (each) prof->end(HELM_K_TRSV_BWD, b.pbytes_b[l] + S * (b.bytes_b[l] - b.pbytes_b[l]), s);
   }
 }
