@@ -106,7 +106,7 @@ typedef struct helm_precond_opts {
                               and return HELM_OK                          */
   int32_t coarse_launch;   /* coarse solve: 0 = one launch whose workgroups
                               wait for the tiles they depend on (factors of
-                              more than 3e8 entries: the faster of the other
+                              more than 1.2e7 entries: the faster of the other
                               two forms as timed at setup); 1 = one launch
                               per level; 2 = one cooperative launch with a grid
                               barrier per level (HELM_EINVAL where the

@@ -323,8 +323,10 @@ __global__ __launch_bounds__(kWG) void bwd_level_kernel(const Task* __restrict__
 // Measured (MI355X): one hop between workgroups (poll, load, store, add) 1.06
 // us, a level of the 16,810-unknown coarse solve 9 us against 11 us with a
 // launch per level (coarse correction 194 -> 168 us), the local solves of
-// 4,913 unknowns in 8 subdomains 156 -> 76 us, of 168,075 unknowns in 30
-// (complex64 panels, 1.05 GB) 461 -> 345 us.  What bounds it now is the chain
+// 4,913 unknowns in 8 subdomains 156 -> 71 us, of 168,075 unknowns in 30
+// (complex64 panels, 1.05 GB) 461 -> 330 us (76 and 345 us with the input
+// indices in LDS and a loop of dependent loads after the wait, instead of
+// registers and four loads at once).  What bounds it now is the chain
 // of latencies in a task (indices, inputs, hop, children's updates, panel,
 // reduction, stores), about 5 us per level on the small operator.
 constexpr int kFlowPolls = 1 << 22;
@@ -397,7 +399,7 @@ __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlan
 // workgroup); *word: this lane's word of that task's record (first wave).
 template <class PT, bool kBwd>
 __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& a, const FlowBatch& b,
-                                          const double2* __restrict__ bin, double2* vin, int2* vidx,
+                                          const double2* __restrict__ bin, double2* vin,
                                           double2 (*red)[64], int* gave_up, uint32_t sweep, int nx_bound, uint32_t nx,
                                           const FlowTask* __restrict__ tasks, uint32_t& word) {
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
@@ -408,7 +410,6 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
   const int64_t off = ((int64_t)uni((int)(t.off >> 32)) << 32) | (uint32_t)uni((int)t.off);
   const bool waits = uni(task.t[0].waits) != 0;
   double2* vt = vin + my * region;
-  int2* it = vidx + my * region;
   const int R = row_group(nrows), G = 64 / R, grp = lane / R, row_l = lane % R;
   const PT* __restrict__ P = reinterpret_cast<const PT*>(kBwd ? b.pb : b.pf) + off + row_l;
   const double2* __restrict__ ub = reinterpret_cast<const double2*>(b.ubuf);
@@ -423,15 +424,23 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
   double ar = 0, ai = 0;
   for (int pass = 0; pass < npass; ++pass) {
     const int cb = pass * region, cn = min(region, ncols - cb);
-    // before the wait: the indices of this pass's inputs, the caller's entries
-    // (forward), and the first eight panel columns of every lane
-    for (int k = ks; k < cn; k += kst) {
+    // before the wait: the indices of this pass's inputs (at most four per
+    // lane), the caller's entries (forward), and the first eight panel
+    // columns of every lane
+    int2 ci[4];
+    double2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = ks + q * kst;
+      ci[q] = make_int2(-1, -1);
+      v[q] = make_double2(0.0, 0.0);
+      if (k >= cn) continue;
       if (kBwd) {
         const int c = col0 + cb + k;
-        it[k].x = c < w ? c0 + c : -1 - b.rows[(int64_t)aux + (c - w)];
+        ci[q].x = c < w ? c0 + c : -1 - b.rows[(int64_t)aux + (c - w)];
       } else {
-        it[k] = b.fcon2[aux + cb + k];
-        vt[k] = bin[b.bidx[c0 + cb + k]];
+        ci[q] = b.fcon2[aux + cb + k];
+        v[q] = bin[b.bidx[c0 + cb + k]];
       }
     }
     const int per = (cn + wpt - 1) / wpt;
@@ -454,36 +463,41 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
         ei = e.y;
       }
     }
-    // each lane completes the entries it began
-    for (int k = ks; k < cn; k += kst) {
-      if (kBwd) {
-        const int i = it[k].x;
-        vt[k] = ld_agent(i >= 0 ? reinterpret_cast<const double2*>(b.y) + i
-                                : reinterpret_cast<const double2*>(b.x) + (-1 - i));
-      } else {
-        const int2 c2 = it[k];
-        if (c2.x >= 0) {
-          const double2 u = ld_agent(ub + c2.x);
-          double2 v = vt[k];
-          v.x -= u.x;
-          v.y -= u.y;
-          if (c2.y >= 0) {
-            const double2 u2 = ld_agent(ub + c2.y);
-            v.x -= u2.x;
-            v.y -= u2.y;
+    // then the other tasks' results, all loads before the first use
+    if (kBwd) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (ks + q * kst < cn)
+          v[q] = ld_agent(ci[q].x >= 0 ? reinterpret_cast<const double2*>(b.y) + ci[q].x
+                                       : reinterpret_cast<const double2*>(b.x) + (-1 - ci[q].x));
+    } else {
+      double2 u[4], u2[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (ci[q].x >= 0) u[q] = ld_agent(ub + ci[q].x);
+        if (ci[q].x >= 0 && ci[q].y >= 0) u2[q] = ld_agent(ub + ci[q].y);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (ci[q].x >= 0) {
+          v[q].x -= u[q].x;
+          v[q].y -= u[q].y;
+          if (ci[q].y >= 0) {
+            v[q].x -= u2[q].x;
+            v[q].y -= u2[q].y;
           }
-          vt[k] = v;
-        } else if (c2.x < -1) {
-          double2 v = vt[k];
-          for (int q = -2 - c2.x; q < b.fcon_ptr[aux + cb + k + 1]; ++q) {
-            const double2 u = ld_agent(ub + b.fcon_idx[q]);
-            v.x -= u.x;
-            v.y -= u.y;
+        } else if (ci[q].x < -1) {
+          for (int e = -2 - ci[q].x; e < b.fcon_ptr[aux + cb + ks + q * kst + 1]; ++e) {
+            const double2 x = ld_agent(ub + b.fcon_idx[e]);
+            v[q].x -= x.x;
+            v[q].y -= x.y;
           }
-          vt[k] = v;
         }
       }
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (ks + q * kst < cn) vt[ks + q * kst] = v[q];
     if (pass == 0 && wv == 0) {  // the next task's record
       const int n = uni((int)nx);
       if (n < nx_bound) word = reinterpret_cast<const uint32_t*>(tasks + n)[lane];
@@ -523,7 +537,6 @@ __global__ __launch_bounds__(kWG) void flow_kernel(FlowArgs a, int t0, int t1, i
   __shared__ double2 red[4][64];
   __shared__ FlowTask rec[2];
   __shared__ int next, gave_up;
-  int2* vidx = reinterpret_cast<int2*>(vin + a.chunk);
   const FlowTask* __restrict__ tasks = a.tasks + t0;
   const int n = t1 - t0;
   const uint32_t sweep = uni((int)cnt_load(a.cnt + 2));
@@ -543,9 +556,9 @@ __global__ __launch_bounds__(kWG) void flow_kernel(FlowArgs a, int t0, int t1, i
     const FlowTask& task = rec[cur];
     const FlowBatch& b = a.b[uni(task.t[0].batch)];
     if (uni(task.t[0].bwd))
-      flow_task<PT, true>(task, a, b, bin, vin, vidx, red, &gave_up, sweep, n, nx, tasks, word);
+      flow_task<PT, true>(task, a, b, bin, vin, red, &gave_up, sweep, n, nx, tasks, word);
     else
-      flow_task<PT, false>(task, a, b, bin, vin, vidx, red, &gave_up, sweep, n, nx, tasks, word);
+      flow_task<PT, false>(task, a, b, bin, vin, red, &gave_up, sweep, n, nx, tasks, word);
     if (threadIdx.x < 64) reinterpret_cast<uint32_t*>(&rec[cur ^ 1])[threadIdx.x] = word;
     if (threadIdx.x == 0) next = (int)nx;
     __syncthreads();  // vin and red are rewritten by the next task
@@ -1406,7 +1419,7 @@ void bwd_level(const Batch& b, int64_t task0, int64_t ntasks, int chunk, bool co
 void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, bool last, const double* bin, hipStream_t s) {
   if (t1 <= t0) return;
   const double2* in = reinterpret_cast<const double2*>(bin);
-  const size_t lds = (sizeof(double2) + sizeof(int2)) * (size_t)a.chunk;
+  const size_t lds = sizeof(double2) * (size_t)a.chunk;
   if (coarse)
     level_go(flow_kernel<double2, 1>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
   else if (c64)

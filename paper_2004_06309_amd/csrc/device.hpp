@@ -180,9 +180,10 @@ constexpr int kFlowBatches = 4;
 struct FlowArgs {
   const FlowTask* tasks;
   uint32_t* cnt;                   // kFlowHead words of state, then the counters
-  int chunk;                       // LDS entries for the input columns
+  int chunk;                       // LDS entries for the input columns (at most kFlowChunk)
   FlowBatch b[kFlowBatches];
 };
+constexpr int kFlowChunk = 1024;   // four per thread
 constexpr int kFlowHead = 32;      // next task, finished workgroups, sweeps done, gave up (one cache line)
 constexpr int kFlowPad = 16;       // words per counter: few share a cache line, so polling one does not slow another
 // Tasks [t0, t1); last: the launch that ends the backward sweep.

@@ -620,6 +620,11 @@ constexpr double kFlowLaneCols = 12;
 // Beyond the line every level fills the device several times over, two
 // batches hide each other's tails, and plain accesses beat coherent ones.
 constexpr int64_t kFlowEntries = 300000000;
+// The same line for the coarse matrix, whose short tiles (16 rows) make many
+// small tasks: coarse correction, flow against levels, us: 1,024 unknowns (0.3M
+// entries) 34 / 42, 7,688 (3.7M) 98 / 105, 16,810 (10M) 168 / 174, 27,048 (17M)
+// 194 / 188, 38,416 (30M) 256 / 241.
+constexpr int64_t kFlowCoarseEntries = 12000000;
 
 // Collects the tiles of a set of batches (in their solve layout) and makes the
 // task list of their single-vector sweeps.
@@ -663,7 +668,7 @@ struct FlowHost {
     for (auto* L : {&lf, &lb})
       for (auto& l : *L)
         for (auto& i : l) chunk = std::max<int64_t>(chunk, i.t.ncols);
-    chunk = std::min<int64_t>((std::max<int64_t>(chunk, 4 * std::min<int64_t>(chunk, 192)) + 63) / 64 * 64, 1024);
+    chunk = std::min<int64_t>((std::max<int64_t>(chunk, 4 * std::min<int64_t>(chunk, 192)) + 63) / 64 * 64, dev::kFlowChunk);
     F.chunk = (int)chunk;
     // waves per tile where a level has tiles to spare: by width, so a wave has
     // columns enough to hide its gather (a complex64 column is half the bytes)
@@ -1420,7 +1425,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
         dev::coarse_update(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.AZ_ptr.p, c.AZ_col.p, c.AZ_val.p, x.p, x.p,
                            y.p, x2.p, G, nullptr);
       });
-      if (cmode == 0 && cb.nf + cb.nb <= kFlowEntries) {
+      if (cmode == 0 && cb.nf + cb.nb <= kFlowCoarseEntries) {
         FlowHost ch;
         ch.add(cb, 0);
         ch.build(c.flow_coarse);
