@@ -51,49 +51,138 @@ __device__ __forceinline__ float2 ldp(const float2* p) {
   return make_float2(v.x, v.y);
 }
 
-// The first eight of a lane's columns k0, k0 + ks, ... (< k1) of a tile
-// (column-major, ld rows apart); columns past k1 re-read the last one.
-template <class PT>
-__device__ __forceinline__ void tile_load(const PT* __restrict__ p, int ld, int k0, int k1, int ks, PT (&a)[8]) {
-#pragma unroll
-  for (int u = 0; u < 8; ++u) a[u] = ldp(p + (int64_t)min(k0 + u * ks, k1 - 1) * ld);
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uni64(int64_t x) {
+  return ((int64_t)uni((int)(x >> 32)) << 32) | (uint32_t)uni((int)x);
 }
 
-// Streams the columns k0, k0 + ks, ... (< k1) of a tile against vin, the
-// first eight already in a (tile_load).  Eight loads stay in flight per lane:
-// each register is refilled right after its column is used, instead of eight
-// loads being issued and drained in turn (a chain of short levels, the coarse
-// correction: 192 -> 168 us; large levels, bound by HBM, 1-2 %).  Whole groups of eight sum into two
-// accumulators alternately, the rest into the first.
+// Panel tiles are read through buffer loads: the tile's base and the column
+// offset are scalar, a lane adds one constant offset, and a lane whose entry is
+// not wanted (rows past the tile, columns past its share, the zero triangle of
+// a diagonal block) passes an offset past the buffer, which returns zero and
+// fetches nothing.  The hardware tests lane offset >= size - scalar offset, so
+// the scalar offset must not pass the size either (the difference would wrap):
+// it is clamped to it, where every lane offset is out of range.
+// The sweeps of a large operator are bound by HBM: without the zero triangles
+// (6 % of the panel entries at one million unknowns in 64 subdomains) they fetch
+// 21.3 GB instead of 22.9, and the address arithmetic leaves the vector unit:
+// local solves 3.57 -> 3.45 ms, with complex64 panels 2.02 -> 1.98 ms.
+typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
+constexpr int kBufNt = 2;                 // cache policy: non-temporal
+constexpr int kBufSkip = 0x7ffffff0;      // an offset no tile reaches
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const void* p, int64_t off, int bytes) {
+  // raw buffer: no stride, range checked in bytes
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(p)) + uni64(off), 0,
+                                           uni(bytes), 0x00020000);
+}
 template <class PT>
-__device__ __forceinline__ void tile_dot(const PT* __restrict__ p, int ld, const double2* vin, int k0, int k1, int ks,
-                                         PT (&a)[8], double& ar, double& ai) {
-  int n = (k1 - k0 + ks - 1) / ks;  // columns from k on
-  int k = k0;
-  double br = 0, bi = 0;
-  if (n >= 8) {
-    for (; n >= 16; n -= 8, k += 8 * ks) {
+__device__ __forceinline__ PT ldb(__amdgpu_buffer_rsrc_t r, int voff, int soff);
+template <>
+__device__ __forceinline__ double2 ldb<double2>(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kBufNt));
+}
+template <>
+__device__ __forceinline__ float2 ldb<float2>(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, kBufNt));
+}
+
+// x / d for 0 <= x < 4096 and 1 <= d <= 64 as one multiplication: floor(x m /
+// 2^20) with m = floor(2^20 / d) + 1 (the error x / 2^20 stays below 1 / d).
+// The compiler's division by a run-time value is some thirty vector
+// instructions and a short task had ten of them: local solves of 168,075
+// unknowns 343 -> 328 us.
+struct DivTable {
+  uint32_t m[65];
+  constexpr DivTable() : m() {
+    for (uint32_t d = 1; d <= 64; ++d) m[d] = (1u << 20) / d + 1;
+  }
+};
+__constant__ const DivTable kDiv{};
+__device__ __forceinline__ int div20(int x, uint32_t m) { return (int)(((uint32_t)x * m) >> 20); }
+
+// Lanes of a tile: a tile with few rows spreads its columns over G = 64 / R
+// lane groups of R = nrows lanes (the last 64 mod R lanes idle).
+struct Lanes {
+  int R, G, grp, row;
+  uint32_t mg;  // divides by G
+  __device__ __forceinline__ explicit Lanes(int nrows) {
+    const int lane = threadIdx.x & 63;
+    R = nrows <= 32 ? max(nrows, 1) : 64;
+    const uint32_t mr = kDiv.m[R];
+    G = div20(64, mr);
+    grp = div20(lane, mr);
+    row = lane - grp * R;
+    mg = kDiv.m[G];
+  }
+};
+
+// A wave's share of a tile's panel: columns kbeg .. kend - 1 of a tile stored
+// column-major, ld rows apart; a lane takes columns kbeg + grp, kbeg + grp + G,
+// ... and keeps those in [lo, hi).
+template <class PT>
+struct Panel {
+  __amdgpu_buffer_rsrc_t r;
+  int bytes;       // of the buffer (uniform)
+  int voff;        // of this lane in a group of G columns
+  int step;        // bytes per group of G columns (uniform)
+  int base;        // bytes of column kbeg (uniform)
+  int n;           // groups (uniform)
+  int i0;          // this lane's first group ...
+  unsigned cnt;    // ... and number of groups
+  __device__ __forceinline__ Panel(__amdgpu_buffer_rsrc_t rs, int size, int ld, int kbeg, int kend, const Lanes& l,
+                                   bool on, int lo, int hi) {
+    r = rs;
+    bytes = uni(size);
+    voff = (l.grp * ld + l.row) * (int)sizeof(PT);
+    step = uni(l.G * ld * (int)sizeof(PT));
+    base = uni(kbeg * ld * (int)sizeof(PT));
+    n = uni(kend > kbeg ? div20(kend - kbeg + l.G - 1, l.mg) : 0);
+    const int first = kbeg + l.grp;  // column of group 0
+    hi = min(hi, kend);
+    i0 = div20(max(lo - first + l.G - 1, 0), l.mg);
+    const int e = div20(max(hi - first + l.G - 1, 0), l.mg);
+    cnt = on && e > i0 ? (unsigned)(e - i0) : 0u;
+  }
+  __device__ __forceinline__ PT load(int i) const {
+    return ldb<PT>(r, (unsigned)(i - i0) < cnt ? voff : kBufSkip, min(base + i * step, bytes));
+  }
+};
+
+// The first eight groups of a panel share.
+template <class PT>
+__device__ __forceinline__ void tile_load(const Panel<PT>& p, PT (&a)[8]) {
 #pragma unroll
-      for (int u = 0; u < 8; u += 2) {
-        cfma(ar, ai, widen(a[u]), vin[k + u * ks]);
-        a[u] = ldp(p + (int64_t)(k + (u + 8) * ks) * ld);
-        cfma(br, bi, widen(a[u + 1]), vin[k + (u + 1) * ks]);
-        a[u + 1] = ldp(p + (int64_t)(k + (u + 9) * ks) * ld);
-      }
-    }
-    n -= 8;
+  for (int u = 0; u < 8; ++u) a[u] = p.load(u);
+}
+
+// Streams a panel share against vin (vin[0] is the entry of the share's first
+// column for this lane group, G entries per group; kmax: its last entry), the
+// first eight groups already in a.  Eight loads stay in flight per lane: each
+// register is refilled right after its column is used, instead of eight loads
+// being issued and drained in turn (a chain of short levels, the coarse
+// correction: 192 -> 168 us).  Groups sum into two accumulators alternately.
+template <class PT>
+__device__ __forceinline__ void tile_dot(const Panel<PT>& p, const double2* vin, int G, int kmax, PT (&a)[8],
+                                         double& ar, double& ai) {
+  double br = 0, bi = 0;
+  int i = 0;
+  for (; i + 8 < p.n; i += 8) {
 #pragma unroll
     for (int u = 0; u < 8; u += 2) {
-      cfma(ar, ai, widen(a[u]), vin[k + u * ks]);
-      if (u < n) a[u] = ldp(p + (int64_t)(k + (u + 8) * ks) * ld);
-      cfma(br, bi, widen(a[u + 1]), vin[k + (u + 1) * ks]);
-      if (u + 1 < n) a[u + 1] = ldp(p + (int64_t)(k + (u + 9) * ks) * ld);
+      cfma(ar, ai, widen(a[u]), vin[(i + u) * G]);
+      a[u] = p.load(i + u + 8);
+      cfma(br, bi, widen(a[u + 1]), vin[(i + u + 1) * G]);
+      a[u + 1] = p.load(i + u + 9);
     }
-    k += 8 * ks;
   }
+  // the last group; entries past the last column meet zero panel entries
 #pragma unroll
-  for (int u = 0; u < 7; ++u)
-    if (u < n) cfma(ar, ai, widen(a[u]), vin[k + u * ks]);
+  for (int u = 0; u < 8; u += 2) {
+    if (i + u >= p.n) break;  // uniform
+    cfma(ar, ai, widen(a[u]), vin[min((i + u) * G, kmax)]);
+    cfma(br, bi, widen(a[u + 1]), vin[min((i + u + 1) * G, kmax)]);
+  }
   ar += br;
   ai += bi;
 }
@@ -112,29 +201,28 @@ __device__ __forceinline__ void for_children(const Batch& b, int fr, F&& f) {
   }
 }
 
-// Lanes per tile row group: a tile with few rows spreads its columns over
-// 64 / R lane groups of R = nrows lanes (the last 64 mod R lanes idle).
-__device__ __forceinline__ int row_group(int nrows) { return nrows <= 32 ? max(nrows, 1) : 64; }
-
 // Work split of a workgroup (4 waves) over the tiles of its task.
 struct Split {
   int my;      // tile slot of this wave
   int part;    // this wave's share of the tile's columns
-  int wpt;     // waves per tile
+  int wpt, sh; // waves per tile (1, 2 or 4), its logarithm
   int region;  // LDS entries per tile slot
   bool has;    // the slot holds a tile
+  // ceil(n / wpt)
+  __device__ __forceinline__ int share(int n) const { return (n + wpt - 1) >> sh; }
 };
 
-__device__ __forceinline__ Split split_of(const Task& task, int chunk) {
+__device__ __forceinline__ Split split_of(int wpt, int ntile, int chunk) {
   Split sp;
   // the wave index is the same on all lanes: scalar, so the wave's tile
   // descriptor is a scalar load
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  sp.wpt = task.wpt;
-  sp.my = wv / sp.wpt;
-  sp.part = wv % sp.wpt;
-  sp.region = chunk / (4 / sp.wpt);
-  sp.has = sp.my < task.ntile;
+  sp.wpt = wpt;
+  sp.sh = wpt >> 1;
+  sp.my = wv >> sp.sh;
+  sp.part = wv & (wpt - 1);
+  sp.region = chunk >> (2 - sp.sh);
+  sp.has = sp.my < ntile;
   return sp;
 }
 
@@ -144,14 +232,15 @@ __device__ __forceinline__ Split split_of(const Task& task, int chunk) {
 template <class PT>
 __device__ __forceinline__ void fwd_task(const Task& task, const Batch& b, const double2* __restrict__ bin,
                                          double2* vin, double2 (*red)[64], int chunk) {
-  const Split sp = split_of(task, chunk);
+  const Split sp = split_of(task.wpt, task.ntile, chunk);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Tile t{};
   if (sp.has) t = b.tf[task.tile0 + sp.my];
   const int s = t.sn, c0 = t.c0, w = t.w, frow0 = t.aux;
   double2* vt = vin + sp.my * sp.region;
-  const int R = row_group(t.nrows), G = 64 / R, grp = lane / R, row_l = lane % R;
-  const PT* __restrict__ P = reinterpret_cast<const PT*>(b.pf) + t.off + row_l;
+  const Lanes l(t.nrows);
+  const int bytes = t.nrows * t.ncols * (int)sizeof(PT);
+  const __amdgpu_buffer_rsrc_t rs = panel_rsrc(b.pf, t.off * (int64_t)sizeof(PT), bytes);
   const double2* __restrict__ ub = reinterpret_cast<const double2*>(b.ubuf);
   // the children's updates to this lane's output row (rows past the pivot
   // block) are fetched before the panel, off the critical path
@@ -170,9 +259,7 @@ __device__ __forceinline__ void fwd_task(const Task& task, const Batch& b, const
   double ar = 0, ai = 0;
   // all waves of a workgroup run the same number of passes: one, unless the
   // workgroup holds a single wide tile
-  const int npass = sp.wpt == 4 ? (t.ncols + chunk - 1) / chunk : 1;
-  for (int pass = 0; pass < npass; ++pass) {
-    const int cb = pass * sp.region;
+  for (int cb = 0; cb == 0 || (sp.wpt == 4 && cb < t.ncols); cb += sp.region) {
     const int cn = sp.has ? min(sp.region, t.ncols - cb) : 0;
     for (int k = sp.part * 64 + lane; k < cn; k += 64 * sp.wpt) {
       const int kk = cb + k;
@@ -185,15 +272,13 @@ __device__ __forceinline__ void fwd_task(const Task& task, const Batch& b, const
       vt[k] = v;
     }
     __syncthreads();
-    if (sp.has && row_l < t.nrows && grp < G) {
-      const PT* __restrict__ Pp = P + (int64_t)cb * t.nrows;
-      const int per = (cn + sp.wpt - 1) / sp.wpt;
-      const int k0 = sp.part * per + grp, k1 = min(cn, sp.part * per + per);
-      if (k0 < k1) {
-        PT a[8];
-        tile_load(Pp, t.nrows, k0, k1, G, a);
-        tile_dot(Pp, t.nrows, vt, k0, k1, G, a, ar, ai);
-      }
+    {
+      const int per = sp.share(cn);
+      const int k0 = cb + sp.part * per, k1 = min(cb + cn, k0 + per);
+      const Panel<PT> p(rs, bytes, t.nrows, k0, k1, l, l.row < t.nrows && l.grp < l.G, 0, t.row0 + l.row < w ? t.row0 + l.row + 1 : t.ncols);
+      PT a[8];
+      tile_load(p, a);
+      if (p.n > 0) tile_dot(p, vt + (k0 - cb + l.grp), l.G, cn - 1 - (k0 - cb + l.grp), a, ar, ai);
     }
     __syncthreads();
   }
@@ -202,7 +287,7 @@ __device__ __forceinline__ void fwd_task(const Task& task, const Batch& b, const
   if (out) {
     double rr = 0, ii = 0;
     for (int q = 0; q < sp.wpt; ++q)
-      for (int g = lane; g < G * R; g += R) {
+      for (int g = lane; g < l.G * l.R; g += l.R) {
         rr += red[wv + q][g].x;
         ii += red[wv + q][g].y;
       }
@@ -216,36 +301,33 @@ __device__ __forceinline__ void fwd_task(const Task& task, const Batch& b, const
 template <class PT>
 __device__ __forceinline__ void bwd_task(const Task& task, const Batch& b, double2* vin, double2 (*red)[64],
                                          int chunk) {
-  const Split sp = split_of(task, chunk);
+  const Split sp = split_of(task.wpt, task.ntile, chunk);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Tile t{};
   if (sp.has) t = b.tb[task.tile0 + sp.my];
   const int c0 = t.c0, w = t.w;
   const int64_t roff = t.aux;
   double2* vt = vin + sp.my * sp.region;
-  const int R = row_group(t.nrows), G = 64 / R, grp = lane / R, row_l = lane % R;
-  const PT* __restrict__ P = reinterpret_cast<const PT*>(b.pb) + t.off + row_l;
+  const Lanes l(t.nrows);
+  const int bytes = t.nrows * t.ncols * (int)sizeof(PT);
+  const __amdgpu_buffer_rsrc_t rs = panel_rsrc(b.pb, t.off * (int64_t)sizeof(PT), bytes);
   const double2* __restrict__ yv = reinterpret_cast<const double2*>(b.y);
   const double2* xv = reinterpret_cast<const double2*>(b.x);
   double ar = 0, ai = 0;
-  const int npass = sp.wpt == 4 ? (t.ncols + chunk - 1) / chunk : 1;
-  for (int pass = 0; pass < npass; ++pass) {
-    const int cb = pass * sp.region;
+  for (int cb = 0; cb == 0 || (sp.wpt == 4 && cb < t.ncols); cb += sp.region) {
     const int cn = sp.has ? min(sp.region, t.ncols - cb) : 0;
     for (int k = sp.part * 64 + lane; k < cn; k += 64 * sp.wpt) {
       const int c = t.col0 + cb + k;
       vt[k] = c < w ? yv[c0 + c] : xv[b.rows[roff + (c - w)]];
     }
     __syncthreads();
-    if (sp.has && row_l < t.nrows && grp < G) {
-      const PT* __restrict__ Pp = P + (int64_t)cb * t.nrows;
-      const int per = (cn + sp.wpt - 1) / sp.wpt;
-      const int k0 = sp.part * per + grp, k1 = min(cn, sp.part * per + per);
-      if (k0 < k1) {
-        PT a[8];
-        tile_load(Pp, t.nrows, k0, k1, G, a);
-        tile_dot(Pp, t.nrows, vt, k0, k1, G, a, ar, ai);
-      }
+    {
+      const int per = sp.share(cn);
+      const int k0 = cb + sp.part * per, k1 = min(cb + cn, k0 + per);
+      const Panel<PT> p(rs, bytes, t.nrows, k0, k1, l, l.row < t.nrows && l.grp < l.G, l.row, t.ncols);
+      PT a[8];
+      tile_load(p, a);
+      if (p.n > 0) tile_dot(p, vt + (k0 - cb + l.grp), l.G, cn - 1 - (k0 - cb + l.grp), a, ar, ai);
     }
     __syncthreads();
   }
@@ -254,7 +336,7 @@ __device__ __forceinline__ void bwd_task(const Task& task, const Batch& b, doubl
   if (sp.has && sp.part == 0 && lane < t.nrows) {
     double rr = 0, ii = 0;
     for (int q = 0; q < sp.wpt; ++q)
-      for (int g = lane; g < G * R; g += R) {
+      for (int g = lane; g < l.G * l.R; g += l.R) {
         rr += red[wv + q][g].x;
         ii += red[wv + q][g].y;
       }
@@ -267,8 +349,11 @@ __device__ __forceinline__ void bwd_task(const Task& task, const Batch& b, doubl
 // The grid holds at most as many workgroups as fit on the device at once;
 // each sweeps tasks blockIdx.x, blockIdx.x + gridDim.x, ... (widest first),
 // so a level costs no workgroup launches beyond the first wave of them.
+// Complex64 panels: six workgroups per CU against four, 2.224 -> 2.205 ms for the
+// two-level preconditioner at one million unknowns; complex128 panels got slower
+// (3.65 -> 3.69 ms).
 template <class PT, int kCoarse>
-__global__ __launch_bounds__(kWG) void fwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
+__global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 6 : 4) void fwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
                                                         const double2* __restrict__ bin, int chunk) {
   extern __shared__ double2 vin[];
   __shared__ double2 red[4][64];
@@ -279,7 +364,7 @@ __global__ __launch_bounds__(kWG) void fwd_level_kernel(const Task* __restrict__
 }
 
 template <class PT, int kCoarse>
-__global__ __launch_bounds__(kWG) void bwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
+__global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 6 : 4) void bwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
                                                         int chunk) {
   extern __shared__ double2 vin[];
   __shared__ double2 red[4][64];
@@ -393,8 +478,6 @@ __device__ __forceinline__ double2 flow_children(const FlowBatch& b, int fr, int
   return e;
 }
 
-__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
 // task: in LDS.  nx: the number drawn for the next task (first lane of the
 // workgroup); *word: this lane's word of that task's record (first wave).
 template <class PT, bool kBwd>
@@ -403,27 +486,28 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
                                           double2 (*red)[64], int* gave_up, uint32_t sweep, int nx_bound, uint32_t nx,
                                           const FlowTask* __restrict__ tasks, uint32_t& word) {
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-  const int wpt = uni(task.t[0].wpt), my = wv / wpt, part = wv % wpt, region = a.chunk / (4 / wpt);
-  const FlowTile& t = task.t[my];
+  const Split sp = split_of(uni(task.t[0].wpt), 4, a.chunk);
+  const int wpt = sp.wpt, part = sp.part, region = sp.region;
+  const FlowTile& t = task.t[sp.my];
   const int nrows = uni(t.nrows), ncols = uni(t.ncols), ld = uni(t.ld), c0 = uni(t.c0), w = uni(t.w), aux = uni(t.aux),
             col0 = uni(t.col0), row0 = uni(t.row0);
-  const int64_t off = ((int64_t)uni((int)(t.off >> 32)) << 32) | (uint32_t)uni((int)t.off);
   const bool waits = uni(task.t[0].waits) != 0;
-  double2* vt = vin + my * region;
-  const int R = row_group(nrows), G = 64 / R, grp = lane / R, row_l = lane % R;
-  const PT* __restrict__ P = reinterpret_cast<const PT*>(kBwd ? b.pb : b.pf) + off + row_l;
+  double2* vt = vin + sp.my * region;
+  const Lanes l(nrows);
+  const int bytes = ncols > 0 ? ((ncols - 1) * ld + nrows) * (int)sizeof(PT) : 0;
+  const __amdgpu_buffer_rsrc_t rs = panel_rsrc(kBwd ? b.pb : b.pf, t.off * (int64_t)sizeof(PT), bytes);
   const double2* __restrict__ ub = reinterpret_cast<const double2*>(b.ubuf);
   const bool out = part == 0 && lane < nrows;
-  const bool dots = row_l < nrows && grp < G;
+  const bool dots = l.row < nrows && l.grp < l.G;
   const int row = row0 + lane;
   const bool upd = !kBwd && out && row >= w;
-  const int npass = wpt == 4 ? (ncols + a.chunk - 1) / a.chunk : 1;
+  const bool many = wpt == 4 && ncols > region;  // several passes
   const int ks = part * 64 + lane, kst = 64 * wpt;
   const int2 co = upd ? b.fcon2[aux + row] : make_int2(-1, -1);
   double er = 0, ei = 0;
   double ar = 0, ai = 0;
-  for (int pass = 0; pass < npass; ++pass) {
-    const int cb = pass * region, cn = min(region, ncols - cb);
+  for (int cb = 0; cb == 0 || (many && cb < ncols); cb += region) {
+    const int cn = min(region, ncols - cb);
     // before the wait: the indices of this pass's inputs (at most four per
     // lane), the caller's entries (forward), and the first eight panel
     // columns of every lane
@@ -443,12 +527,14 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
         v[q] = bin[b.bidx[c0 + cb + k]];
       }
     }
-    const int per = (cn + wpt - 1) / wpt;
-    const int kb = part * per + grp, ke = min(cn, part * per + per);
-    const PT* __restrict__ Pp = P + (int64_t)cb * ld;
-    PT pre[8] = {};
-    if (dots && kb < ke) tile_load(Pp, ld, kb, ke, G, pre);
-    if (pass == 0) {
+    const int per = sp.share(cn);
+    const int kb = cb + part * per, ke = min(cb + cn, kb + per);
+    // forward pivot rows end at the diagonal, backward rows begin there
+    const Panel<PT> p(rs, bytes, ld, kb, ke, l, dots, kBwd ? l.row : 0,
+                      !kBwd && row0 + l.row < w ? row0 + l.row + 1 : ncols);
+    PT pre[8];
+    tile_load(p, pre);
+    if (cb == 0) {
       if (waits) {
         if (wv == 0) {
           const bool ok = flow_wait(task, a.cnt, sweep);
@@ -498,13 +584,13 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (ks + q * kst < cn) vt[ks + q * kst] = v[q];
-    if (pass == 0 && wv == 0) {  // the next task's record
+    if (cb == 0 && wv == 0) {  // the next task's record
       const int n = uni((int)nx);
       if (n < nx_bound) word = reinterpret_cast<const uint32_t*>(tasks + n)[lane];
     }
     __syncthreads();
-    if (dots && kb < ke) tile_dot(Pp, ld, vt, kb, ke, G, pre, ar, ai);
-    if (npass > 1) __syncthreads();
+    if (p.n > 0) tile_dot(p, vt + (kb - cb + l.grp), l.G, cn - 1 - (kb - cb + l.grp), pre, ar, ai);
+    if (many) __syncthreads();
   }
   red[wv][lane] = make_double2(ar, ai);
   __syncthreads();
@@ -512,7 +598,7 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
     if (out) {
       double rr = 0, ii = 0;
       for (int q = 0; q < wpt; ++q)
-        for (int g = lane; g < G * R; g += R) {
+        for (int g = lane; g < l.G * l.R; g += l.R) {
           rr += red[wv + q][g].x;
           ii += red[wv + q][g].y;
         }
@@ -530,8 +616,10 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
   }
 }
 
+// Three workgroups per CU: a fourth (128 registers) made the chains longer, 339
+// against 328 us for 168,075 unknowns.
 template <class PT, int kCoarse>
-__global__ __launch_bounds__(kWG) void flow_kernel(FlowArgs a, int t0, int t1, int last,
+__global__ __launch_bounds__(kWG, 3) void flow_kernel(FlowArgs a, int t0, int t1, int last,
                                                    const double2* __restrict__ bin) {
   extern __shared__ double2 vin[];
   __shared__ double2 red[4][64];
@@ -586,26 +674,23 @@ __device__ __forceinline__ double bcast(double x, int k) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// acc[q] += tile q (rows lane, columns 0..w-1) * v, NQ tiles at P + 64 q w
-// (tile q has rows[q] rows, tiles q >= nq are skipped), 8 loads in flight
-// per lane.  Lanes past a tile's last row re-read that row: their sums are
-// never stored, and every load stays inside the tile.
+// acc[q] += tile q (rows lane, columns 0..w-1) * v, NQ tiles at byte offset
+// 64 q w of the buffer (tile q has rows[q] rows, none for q >= nq), eight loads
+// in flight per lane.  Lanes past a tile's last row skip their loads, and in
+// the first tile (diag) the lanes above the diagonal.
 template <class PT, int NQ>
-__device__ __forceinline__ void sn_stream(const PT* __restrict__ P, int w, int nq, const int* rows, double2 v,
+__device__ __forceinline__ void sn_stream(__amdgpu_buffer_rsrc_t r, int bytes, int w, const int* rows, bool diag, double2 v,
                                           double2* acc) {
-  constexpr int KU = 8 / NQ;
+  constexpr int KU = 8 / NQ, esz = (int)sizeof(PT);
   const int lane = threadIdx.x & 63;
-  const PT* base[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) base[q] = P + (int64_t)q * 64 * w + min(lane, max(rows[q], 1) - 1);
   for (int k = 0; k < w; k += KU) {
     PT a[KU][NQ];
 #pragma unroll
     for (int u = 0; u < KU; ++u)
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        PT z{};
-        a[u][q] = (k + u < w && q < nq) ? ldp(base[q] + (int64_t)(k + u) * rows[q]) : z;
+        const bool on = lane < rows[q] && k + u < w && !(q == 0 && diag && lane < k + u);
+        a[u][q] = ldb<PT>(r, on ? lane * esz : kBufSkip, min((q * 64 * w + (k + u) * rows[q]) * esz, bytes));
       }
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
@@ -637,7 +722,6 @@ __global__ __launch_bounds__(kWG) void fwd_sn_kernel(const SnJob* __restrict__ j
         v.y -= u.y;
       });
     }
-    const PT* __restrict__ P = reinterpret_cast<const PT*>(b.pf) + jb.off;
     for (int q0 = 0; q0 * 64 < m; q0 += 4) {
       const int nq = min(4, (m - q0 * 64 + 63) / 64);
       int rows[4];
@@ -655,13 +739,15 @@ __global__ __launch_bounds__(kWG) void fwd_sn_kernel(const SnJob* __restrict__ j
             acc[q].y += u.y;
           });
       }
-      const PT* Pq = P + (int64_t)q0 * 64 * w;
+      const int bytes = min(256, m - q0 * 64) * w * (int)sizeof(PT);
+      const __amdgpu_buffer_rsrc_t rs =
+          panel_rsrc(b.pf, (jb.off + (int64_t)q0 * 64 * w) * (int64_t)sizeof(PT), bytes);
       if (nq == 1)
-        sn_stream<PT, 1>(Pq, w, nq, rows, v, acc);
+        sn_stream<PT, 1>(rs, bytes, w, rows, q0 == 0, v, acc);
       else if (nq == 2)
-        sn_stream<PT, 2>(Pq, w, nq, rows, v, acc);
+        sn_stream<PT, 2>(rs, bytes, w, rows, q0 == 0, v, acc);
       else
-        sn_stream<PT, 4>(Pq, w, nq, rows, v, acc);
+        sn_stream<PT, 4>(rs, bytes, w, rows, q0 == 0, v, acc);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int row = (q0 + q) * 64 + lane;

@@ -98,7 +98,7 @@ void fwd_sn(const Batch& b, int64_t job0, int64_t njobs, const double* bin, hipS
 void copy_tiles(const void* src, void* dst, const int64_t* from, const int64_t* to, const int64_t* words,
                 int64_t ntiles, hipStream_t s);
 // Largest LDS input buffer a level solve uses (entries).
-constexpr int kLevelChunkMax = 2048;
+constexpr int kLevelChunkMax = 1024;
 // One frontal matrix of the device factorisation (offsets in complex
 // entries).
 struct FrontJob {

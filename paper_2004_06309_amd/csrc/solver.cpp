@@ -178,9 +178,11 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
                   const std::vector<NumericOut>& num, int64_t sn_jobs_min, bool c64, BatchHost& B) {
   const int nm = (int)Ss.size();
   B = BatchHost();
-  // waves per tile from the tile's bytes per row: a complex64 column is
-  // half a complex128 one, so a wave takes twice the columns
-  auto wpt_of = [c64](int32_t ncols) { return dev::waves_per_tile(c64 ? (ncols + 1) / 2 : ncols); };
+  // waves per tile from the tile's bytes per row: a complex64 column is half a
+  // complex128 one, so a wave takes more columns (two waves up to 512, so that
+  // a workgroup's two tiles fit an LDS buffer of 1024 entries: five instead of
+  // three workgroups of those levels per CU)
+  auto wpt_of = [c64](int32_t ncols) { return c64 ? (ncols <= 192 ? 1 : ncols <= 512 ? 2 : 4) : dev::waves_per_tile(ncols); };
   std::vector<int64_t> pos0(nm + 1, 0), sn0(nm + 1, 0), pf0(nm + 1, 0), pb0(nm + 1, 0), u0(nm + 1, 0),
       fr0(nm + 1, 0);
   int32_t maxlev_f = 0, maxlev_b = 0;
@@ -604,8 +606,10 @@ void build_batch(const std::vector<const Csr*>& As, const std::vector<const Symb
   Dv.x.alloc(2 * std::max<int64_t>(B.npos, 1));
 }
 
-// Workgroups of dev::flow the device holds at once (four per CU), and the
-// columns per lane below which a tile is not split further.
+// Tasks a level of dev::flow is cut into at most, about the workgroups the device
+// holds at once (local solves of 168,075 unknowns: 345 us with 768, 328 with
+// 1024, 340 with 1536), and the columns per lane below which a tile is not split
+// further.
 constexpr int64_t kFlowSlots = 1024;
 constexpr double kFlowLaneCols = 12;
 // Panel entries up to which the sweeps take one launch (dev::flow) instead of
@@ -613,10 +617,12 @@ constexpr double kFlowLaneCols = 12;
 //   entries    complex128     complex64
 //     2.6M      78 / 153       83 / 147
 //      38M     226 / 313      199 / 333
-//     118M     423 / 474      338 / 431
-//     246M     792 / 809      555 / 593
-//     418M    1242 / 1218     832 / 767
-//    1295M    3646 / 3562    2178 / 2023
+//     118M     400 / 474      322 / 431
+//     246M     760 / 809      543 / 593
+//     418M    1183 / 1154     806 / 757
+//    1295M    3504 / 3446    2139 / 1975
+// (the first four lines' level times taken before both forms read panels
+// through buffer loads, which gave either about 4 %).
 // Beyond the line every level fills the device several times over, two
 // batches hide each other's tails, and plain accesses beat coherent ones.
 constexpr int64_t kFlowEntries = 300000000;
