@@ -281,7 +281,7 @@ struct Ctx {
   int blk_m = 0, blk_cap = 0, blk_bases = 0;
   int64_t blk_n = 0;
   DVec<double> bV[dev::kMaxBlock], bZ[dev::kMaxBlock], bw[dev::kMaxBlock];
-  DVec<double> bhcol, bhtmp, bpartial, by, bX, bZb, bW, bq, bt, bcvec, bcoef_w, bcoef_v;
+  DVec<double> bhcol, bhtmp, bpartial, by, bX, bZb, bW, bt, bcvec, bcoef_w, bcoef_v;
   double* bh_host = nullptr;  // pinned, kMaxBlock x (2 m + 4) complex
   // block GMRES (one Krylov basis of 16-column blocks shared by the block's
   // right-hand sides): bases V (m + 1 blocks) and Z_m (m blocks), W, the

@@ -232,10 +232,9 @@ void spmv_real(int64_t n, const int64_t* ptr, const int32_t* col, const double* 
 void coarse_update(int64_t n, const int64_t* zptr, const int32_t* zcol, const double* zval, const int64_t* aptr,
                    const int32_t* acol, const double* aval, const double* cx, const double* r, double* q, double* t,
                    int G, hipStream_t s);
-// coarse_update for S interleaved right-hand sides (device_block.hip).
-void coarse_update_block(int64_t n, const int64_t* zptr, const int32_t* zcol, const double* zval,
-                         const int64_t* aptr, const int32_t* acol, const double* aval, int S, const double* cx,
-                         const double* x, double* q, double* t, hipStream_t s);
+// t = x - (A Z) cx for S interleaved right-hand sides (device_block.hip).
+void coarse_update_block(int64_t n, const int64_t* aptr, const int32_t* acol, const double* aval, int S,
+                         const double* cx, const double* x, double* t, hipStream_t s);
 // z[g] = sum_p w[p] xl[idx[p]] over p in [ptr[g], ptr[g+1]) (+ q[g] if q).
 void prolong(int64_t n, const int64_t* ptr, const int32_t* idx, const double* w, const double* xl, const double* q,
              double* z, hipStream_t s);
@@ -309,14 +308,25 @@ void bgs_mul(int64_t n, const double* X, int64_t ldx, int nb, const double* C, d
 void chol16(const double* G, int s_act, const double* ref, double tiny, double* R, double* T, int* status,
             hipStream_t s);
 
-// y = A x (or b - A x) for S interleaved vectors from the CSR copy of A.
+// y = A x (or b - A x) for S interleaved vectors.  A row's real entries come from
+// the split storage if it has no imaginary ones, else from the complex storage.
 // xr / xrows: XCD row ranges as for spmv (nullptr: plain order).
-void csr_spmv_block(int64_t n, const int64_t* ptr, const int32_t* col, const double* val, const int64_t* xr,
-                    int64_t xrows, int S, const double* x, const double* b, double* y, hipStream_t s);
+struct SpmvBlock {
+  const int64_t* aptr;  // complex entries
+  const int32_t* acol;
+  const double* aval;
+  const int64_t* sptr;  // split storage
+  const int32_t* scol;
+  const double* sval;
+};
+void spmv_block(int64_t n, const SpmvBlock& A, const int64_t* xr, int64_t xrows, int S, const double* x,
+                const double* b, double* y, hipStream_t s);
 void spmv_real_block(int64_t n, const int64_t* ptr, const int32_t* col, const double* val, int S, const double* x,
                      double* y, hipStream_t s);
+// z = Z cx (cx null: 0) + the weighted local results xl, S interleaved
 void prolong_block(int64_t n, const int64_t* ptr, const int32_t* idx, const double* w, int S, const double* xl,
-                   const double* q, double* z, hipStream_t s);
+                   const int64_t* zptr, const int32_t* zcol, const double* zval, const double* cx, double* z,
+                   hipStream_t s);
 // dst (interleaved) <- the S vectors src.p[r] (zeros for null entries)
 void pack(int64_t n, int S, const PtrSetC& src, double* dst, hipStream_t s);
 // dst.p[r] <- column r of src (skipped for null entries)

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "device.hpp"
 
@@ -757,59 +758,126 @@ __global__ __launch_bounds__(kWG, 3) void level_small_kernel(const Tile* __restr
   }
 }
 
-// Block SpMV over CSR: S consecutive lanes share a row and take one
-// right-hand side each, so every x gather is one contiguous S x 16 B line.
-// With kXcd, XCD k sweeps the rows [xr[k], xr[k+1]) (as in the single-vector
-// kernel).
-template <int S, bool kXcd>
-__global__ __launch_bounds__(kWG) void csr_block_kernel(int64_t n, const int64_t* __restrict__ ptr,
-                                                        const int32_t* __restrict__ col,
-                                                        const double2* __restrict__ val,
-                                                        const int64_t* __restrict__ xr,
-                                                        const double2* __restrict__ x,
-                                                        const double2* __restrict__ bvec, double2* __restrict__ y) {
-  int64_t i, end = n;
-  int r;
-  if (kXcd) {
-    const int64_t e0 = (int64_t)(blockIdx.x >> 3) * kWG + threadIdx.x;
-    i = xr[blockIdx.x & 7] + e0 / S;
-    r = (int)(e0 % S);
-    end = xr[(blockIdx.x & 7) + 1];
+// Entry n of the 16 a row's lanes hold, on all lanes of the row (DPP broadcast
+// within 16 lanes).
+template <int N>
+__device__ __forceinline__ int row_bcast(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, 0x150 + N, 0xf, 0xf, false);
+}
+template <int N>
+__device__ __forceinline__ double row_bcast(double x) {
+  const long long v = __double_as_longlong(x);
+  const int lo = row_bcast<N>((int)v), hi = row_bcast<N>((int)(v >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Calls f(u, col, val, x entry) for the entries [p, p1) of a sparse row, in order
+// (u: the entry's place in its group), for one of S interleaved right-hand sides;
+// xs(c) is the x entry of column c.  With 16 right-hand sides the row's sixteen
+// lanes load sixteen entries at once and hand them round: one load of columns
+// and one of values per sixteen entries instead of sixteen each (the loads of a
+// product are bound by the L1s' 64 B per clock: 782 -> 558 us at one million
+// unknowns, with real instead of complex entries).  Gathers go eight at a time.
+template <int N0, class X, class F, int... N>
+__device__ __forceinline__ void row_group8(int c, double v, int cnt, X&& xs, F&& f, std::integer_sequence<int, N...>) {
+  const int cc[8] = {row_bcast<N0 + N>(c)...};
+  const double vv[8] = {row_bcast<N0 + N>(v)...};
+  double2 xv[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (N0 + u < cnt) xv[u] = xs(cc[u]);
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (N0 + u < cnt) f(u, cc[u], vv[u], xv[u]);
+}
+
+template <int S, class X, class F>
+__device__ __forceinline__ void for_row(const int32_t* __restrict__ col, const double* __restrict__ val, int64_t p,
+                                        int64_t p1, X&& xs, F&& f) {
+  if constexpr (S == 16) {
+    const int r = threadIdx.x & 15;
+    for (; p < p1; p += 16) {
+      const int cnt = (int)min((int64_t)16, p1 - p);
+      const int64_t q = p + min(r, cnt - 1);
+      const int c = col[q];
+      const double v = val[q];
+      constexpr std::make_integer_sequence<int, 8> seq{};
+      row_group8<0>(c, v, cnt, xs, f, seq);
+      if (cnt > 8) row_group8<8>(c, v, cnt, xs, f, seq);
+    }
   } else {
-    const int64_t e0 = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    i = e0 / S;
-    r = (int)(e0 % S);
+    for (; p + 8 <= p1; p += 8) {
+      int c[8];
+      double v[8];
+      double2 xv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) c[u] = col[p + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = val[p + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) xv[u] = xs(c[u]);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f(u, c[u], v[u], xv[u]);
+    }
+    for (int u = 0; p < p1; ++p, ++u) f(u, col[p], val[p], xs(col[p]));
+  }
+}
+
+// Block SpMV: S consecutive lanes share a row and take one right-hand side each,
+// so every x gather is one contiguous S x 16 B line.  A row without imaginary parts
+// (as many entries in the split storage as in the complex one: with real
+// velocities all but the rows on absorbing faces) reads its real entries only; the
+// others read the complex ones.
+// Even entries sum into a, odd ones into b, alike on both routes.  With kXcd, XCD k
+// sweeps the rows [xr[k], xr[k+1]) (as in the single-vector kernel).
+template <int S, bool kXcd>
+__global__ __launch_bounds__(kWG) void spmv_block_kernel(
+    int64_t n, const int64_t* __restrict__ aptr, const int32_t* __restrict__ acol, const double2* __restrict__ aval,
+    const int64_t* __restrict__ sptr, const int32_t* __restrict__ scol, const double* __restrict__ sval,
+    const int64_t* __restrict__ xr, const double2* __restrict__ x, const double2* __restrict__ bvec,
+    double2* __restrict__ y) {
+  const int r = threadIdx.x % S;
+  int64_t i = ((int64_t)(kXcd ? blockIdx.x >> 3 : blockIdx.x) * kWG + threadIdx.x) / S, end = n;
+  if (kXcd) {
+    i += xr[blockIdx.x & 7];
+    end = xr[(blockIdx.x & 7) + 1];
   }
   if (i >= end) return;
   const int64_t e = i * S + r;
   double ar = 0, ai = 0, br = 0, bi = 0;
-  const int64_t p1 = ptr[i + 1];
-  int64_t p = ptr[i];
-  // eight entries per step: all column loads, then the values and the x
-  // gathers, so a lane keeps eight gathers in flight (even entries sum into
-  // a, odd ones into b, in the order of the short loop below)
-  for (; p + 8 <= p1; p += 8) {
-    int c[8];
-    double2 v[8], xv[8];
+  int64_t p = aptr[i];
+  const int64_t p1 = aptr[i + 1], q = sptr[i], q1 = sptr[i + 1];
+  if (q1 - q == p1 - p) {
+    for_row<S>(scol, sval, q, q1, [&](int c) { return x[(int64_t)c * S + r]; }, [&](int u, int, double v, double2 xv) {
+      double& sr = u & 1 ? br : ar;
+      double& si = u & 1 ? bi : ai;
+      sr = fma(v, xv.x, sr);
+      si = fma(v, xv.y, si);
+    });
+  } else {
+    for (; p + 8 <= p1; p += 8) {
+      int c[8];
+      double2 v[8], xv[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) c[u] = col[p + u];
+      for (int u = 0; u < 8; ++u) c[u] = acol[p + u];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = val[p + u];
+      for (int u = 0; u < 8; ++u) v[u] = aval[p + u];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) xv[u] = x[(int64_t)c[u] * S + r];
+      for (int u = 0; u < 8; ++u) xv[u] = x[(int64_t)c[u] * S + r];
 #pragma unroll
-    for (int u = 0; u < 8; u += 2) {
-      cfma(ar, ai, v[u], xv[u]);
-      cfma(br, bi, v[u + 1], xv[u + 1]);
+      for (int u = 0; u < 8; u += 2) {
+        cfma(ar, ai, v[u], xv[u]);
+        cfma(br, bi, v[u + 1], xv[u + 1]);
+      }
     }
+    for (; p + 2 <= p1; p += 2) {
+      const int c0 = acol[p], c1 = acol[p + 1];
+      const double2 v0 = aval[p], v1 = aval[p + 1];
+      cfma(ar, ai, v0, x[(int64_t)c0 * S + r]);
+      cfma(br, bi, v1, x[(int64_t)c1 * S + r]);
+    }
+    if (p < p1) cfma(ar, ai, aval[p], x[(int64_t)acol[p] * S + r]);
   }
-  for (; p + 2 <= p1; p += 2) {
-    const int c0 = col[p], c1 = col[p + 1];
-    const double2 v0 = val[p], v1 = val[p + 1];
-    cfma(ar, ai, v0, x[(int64_t)c0 * S + r]);
-    cfma(br, bi, v1, x[(int64_t)c1 * S + r]);
-  }
-  if (p < p1) cfma(ar, ai, val[p], x[(int64_t)col[p] * S + r]);
   ar += br;
   ai += bi;
   if (bvec) {
@@ -858,75 +926,54 @@ __global__ __launch_bounds__(kWG) void spmv_real_block_kernel(int64_t n, const i
   y[e] = make_double2(ar, ai);
 }
 
-// q = Z cx and t = x - (A Z) cx for S interleaved right-hand sides (A Z in
-// split storage: bit 31 of a column marks an imaginary part).
+// t = x - (A Z) cx for S interleaved right-hand sides (A Z in split storage: bit
+// 31 of a column marks an imaginary part).
 template <int S>
-__global__ __launch_bounds__(kWG) void coarse_update_block_kernel(
-    int64_t n, const int64_t* __restrict__ zptr, const int32_t* __restrict__ zcol, const double* __restrict__ zval,
-    const int64_t* __restrict__ aptr, const int32_t* __restrict__ acol, const double* __restrict__ aval,
-    const double2* __restrict__ cx, const double2* __restrict__ x, double2* __restrict__ q, double2* __restrict__ t) {
+__global__ __launch_bounds__(kWG) void coarse_update_block_kernel(int64_t n, const int64_t* __restrict__ aptr,
+                                                                  const int32_t* __restrict__ acol,
+                                                                  const double* __restrict__ aval,
+                                                                  const double2* __restrict__ cx,
+                                                                  const double2* __restrict__ x,
+                                                                  double2* __restrict__ t) {
   const int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x;
   if (e >= n * S) return;
   const int64_t row = e / S;
   const int r = (int)(e % S);
-  double qr = 0, qi = 0, ar = 0, ai = 0;
-  for (int64_t p = zptr[row]; p < zptr[row + 1]; ++p) {
-    const double z = zval[p];
-    const double2 v = cx[(int64_t)zcol[p] * S + r];
-    qr = fma(z, v.x, qr);
-    qi = fma(z, v.y, qi);
-  }
-  auto az = [&](int c, double a, double2 v) {
-    const bool im = c < 0;  // i v = (-v.y, v.x)
-    ar = fma(a, im ? -v.y : v.x, ar);
-    ai = fma(a, im ? v.x : v.y, ai);
-  };
-  const int64_t p1 = aptr[row + 1];
-  int64_t p = aptr[row];
-  // four entries of A Z per step (loads first, then the multiply-adds in order)
-  for (; p + 4 <= p1; p += 4) {
-    int c[4];
-    double a[4];
-    double2 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) c[u] = acol[p + u];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) a[u] = aval[p + u];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = cx[(int64_t)(c[u] & 0x7fffffff) * S + r];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) az(c[u], a[u], v[u]);
-  }
-  for (; p < p1; ++p) {
-    const int c = acol[p];
-    az(c, aval[p], cx[(int64_t)(c & 0x7fffffff) * S + r]);
-  }
-  q[e] = make_double2(qr, qi);
+  double ar = 0, ai = 0;
+  for_row<S>(acol, aval, aptr[row], aptr[row + 1], [&](int c) { return cx[(int64_t)(c & 0x7fffffff) * S + r]; },
+             [&](int, int c, double a, double2 v) {
+               const bool im = c < 0;  // i v = (-v.y, v.x)
+               ar = fma(a, im ? -v.y : v.x, ar);
+               ai = fma(a, im ? v.x : v.y, ai);
+             });
   const double2 xx = x[e];
   t[e] = make_double2(xx.x - ar, xx.y - ai);
 }
 
+// z = Z cx + sum of the weighted local results, cx null for one level.  The
+// coarse part is formed here from the coarse solution, which the caches hold,
+// instead of being written by the coarse update and read back (16 right-hand sides
+// at one million unknowns: the coarse stage 796 -> 642 us, this one 167 -> 218).
 template <int S>
 __global__ __launch_bounds__(kWG) void prolong_block_kernel(int64_t n, const int64_t* __restrict__ ptr,
                                                             const int32_t* __restrict__ idx,
                                                             const double* __restrict__ w,
                                                             const double2* __restrict__ xl,
-                                                            const double2* __restrict__ q, double2* __restrict__ z) {
+                                                            const int64_t* __restrict__ zptr,
+                                                            const int32_t* __restrict__ zcol,
+                                                            const double* __restrict__ zval,
+                                                            const double2* __restrict__ cx, double2* __restrict__ z) {
   const int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x;
   if (e >= n * S) return;
   const int64_t g = e / S;
   const int r = (int)(e % S);
   double ar = 0, ai = 0;
-  if (q) {
-    ar = q[e].x;
-    ai = q[e].y;
-  }
-  for (int64_t p = ptr[g]; p < ptr[g + 1]; ++p) {
-    const double2 v = xl[(int64_t)idx[p] * S + r];
-    const double c = w[p];
+  auto add = [&](int, int, double c, double2 v) {
     ar = fma(c, v.x, ar);
     ai = fma(c, v.y, ai);
-  }
+  };
+  if (cx) for_row<S>(zcol, zval, zptr[g], zptr[g + 1], [&](int c) { return cx[(int64_t)c * S + r]; }, add);
+  for_row<S>(idx, w, ptr[g], ptr[g + 1], [&](int i) { return xl[(int64_t)i * S + r]; }, add);
   z[e] = make_double2(ar, ai);
 }
 
@@ -969,7 +1016,8 @@ void with_width(int S, F&& f) {
 // Launch of level_small_kernel: all tiles take four waves on levels of at most
 // 2048 tiles (a wave per tile would leave most of the 1024 SIMDs idle), and a
 // tile's rows are split over workgroups while those stay within 512, two per
-// CU (a level of 128 tiles: 24 us unsplit, 14 us in four).
+// CU (a block step of 8 right-hand sides at 138,000 unknowns: 1,094 us unsplit,
+// 1,018 so).
 template <class PT, int kFwd, int S, int kCoarse>
 static void small_go(const Batch& b, const Tile* tiles, int64_t ntiles, int64_t nwide, const double* src,
                      const double* aux, double* out, double* ubb, hipStream_t s) {
@@ -1074,19 +1122,21 @@ void bwd_level_mfma(const Batch& b, int64_t tile0, int64_t ntiles, int64_t nwide
     bwd_fused_launch<double, 0>(b, b.tb + tile0, ntiles, nwide, y, x, s);
 }
 
-void csr_spmv_block(int64_t n, const int64_t* ptr, const int32_t* col, const double* val, const int64_t* xr,
-                    int64_t xrows, int S, const double* x, const double* b, double* y, hipStream_t s) {
+void spmv_block(int64_t n, const SpmvBlock& A, const int64_t* xr, int64_t xrows, int S, const double* x,
+                const double* b, double* y, hipStream_t s) {
   if (n <= 0) return;
   with_width(S, [&](auto w) {
     constexpr int W = decltype(w)::value;
-    auto v2 = reinterpret_cast<const double2*>(val);
+    auto v2 = reinterpret_cast<const double2*>(A.aval);
     auto x2 = reinterpret_cast<const double2*>(x);
     auto b2 = reinterpret_cast<const double2*>(b);
     auto y2 = reinterpret_cast<double2*>(y);
     if (xr)
-      csr_block_kernel<W, true><<<8 * blocks_for(xrows * W), kWG, 0, s>>>(n, ptr, col, v2, xr, x2, b2, y2);
+      spmv_block_kernel<W, true><<<8 * blocks_for(xrows * W), kWG, 0, s>>>(n, A.aptr, A.acol, v2, A.sptr, A.scol,
+                                                                           A.sval, xr, x2, b2, y2);
     else
-      csr_block_kernel<W, false><<<blocks_for(n * W), kWG, 0, s>>>(n, ptr, col, v2, nullptr, x2, b2, y2);
+      spmv_block_kernel<W, false><<<blocks_for(n * W), kWG, 0, s>>>(n, A.aptr, A.acol, v2, A.sptr, A.scol, A.sval,
+                                                                    nullptr, x2, b2, y2);
   });
 }
 
@@ -1100,26 +1150,26 @@ void spmv_real_block(int64_t n, const int64_t* ptr, const int32_t* col, const do
   });
 }
 
-void coarse_update_block(int64_t n, const int64_t* zptr, const int32_t* zcol, const double* zval,
-                         const int64_t* aptr, const int32_t* acol, const double* aval, int S, const double* cx,
-                         const double* x, double* q, double* t, hipStream_t s) {
+void coarse_update_block(int64_t n, const int64_t* aptr, const int32_t* acol, const double* aval, int S,
+                         const double* cx, const double* x, double* t, hipStream_t s) {
   if (n <= 0) return;
   with_width(S, [&](auto w) {
     constexpr int W = decltype(w)::value;
     coarse_update_block_kernel<W><<<blocks_for(n * W), kWG, 0, s>>>(
-        n, zptr, zcol, zval, aptr, acol, aval, reinterpret_cast<const double2*>(cx),
-        reinterpret_cast<const double2*>(x), reinterpret_cast<double2*>(q), reinterpret_cast<double2*>(t));
+        n, aptr, acol, aval, reinterpret_cast<const double2*>(cx), reinterpret_cast<const double2*>(x),
+        reinterpret_cast<double2*>(t));
   });
 }
 
 void prolong_block(int64_t n, const int64_t* ptr, const int32_t* idx, const double* wt, int S, const double* xl,
-                   const double* q, double* z, hipStream_t s) {
+                   const int64_t* zptr, const int32_t* zcol, const double* zval, const double* cx, double* z,
+                   hipStream_t s) {
   if (n <= 0) return;
   with_width(S, [&](auto w) {
     constexpr int W = decltype(w)::value;
-    prolong_block_kernel<W><<<blocks_for(n * W), kWG, 0, s>>>(n, ptr, idx, wt, reinterpret_cast<const double2*>(xl),
-                                                               reinterpret_cast<const double2*>(q),
-                                                               reinterpret_cast<double2*>(z));
+    prolong_block_kernel<W><<<blocks_for(n * W), kWG, 0, s>>>(
+        n, ptr, idx, wt, reinterpret_cast<const double2*>(xl), zptr, zcol, zval, reinterpret_cast<const double2*>(cx),
+        reinterpret_cast<double2*>(z));
   });
 }
 

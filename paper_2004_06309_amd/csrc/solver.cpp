@@ -56,7 +56,7 @@ void Ctx::free_solve_work() {
     bZ[r].reset();
     bw[r].reset();
   }
-  for (auto* v : {&bhcol, &bhtmp, &bpartial, &by, &bX, &bZb, &bW, &bq, &bt, &bcvec, &bcoef_w, &bcoef_v}) v->reset();
+  for (auto* v : {&bhcol, &bhtmp, &bpartial, &by, &bX, &bZb, &bW, &bt, &bcvec, &bcoef_w, &bcoef_v}) v->reset();
   for (auto* v : {&t, &q, &cvec}) v->reset();
   free_bg_graphs();
   bg_m = 0;
@@ -1900,7 +1900,7 @@ void ensure_bases(Ctx& c, int m, int count) {
 // Gram-Schmidt reductions.
 size_t width_bytes(const Ctx& c, int m, int S) {
   const size_t n = (size_t)c.D.n;
-  size_t e = 5 * n * S;  // bX, bZb, bW, bq, bt (complex entries)
+  size_t e = 4 * n * S;  // bX, bZb, bW, bt (complex entries)
   if (c.two_level) e += (size_t)c.E.n * S;
   auto batch = [&](const BatchDev& b) {
     size_t v = (std::max<size_t>(b.ubuf.n / 2, 1) + 2 * std::max<int64_t>(b.npos, 1)) * S;
@@ -1963,6 +1963,10 @@ void tune_block_levels(BatchDev& b, const double* in) {
   b.blk_tuned = true;
 }
 
+dev::SpmvBlock block_matrix(const Ctx& c) {
+  return {c.A_ptr.p, c.A_col.p, c.A_val.p, c.S_ptr.p, c.S_col.p, c.S_val.p};
+}
+
 void ensure_width(Ctx& c, int m, int S) {
   const int64_t n = c.D.n;
   if (c.blk_m != m || c.blk_n != n) ensure_bases(c, m, 0);
@@ -1977,7 +1981,6 @@ void ensure_width(Ctx& c, int m, int S) {
     c.bX.alloc(2 * (size_t)n * S);
     c.bZb.alloc(2 * (size_t)n * S);
     c.bW.alloc(2 * (size_t)n * S);
-    c.bq.alloc(2 * (size_t)n * S);
     c.bt.alloc(2 * (size_t)n * S);
     if (c.two_level) c.bcvec.alloc(2 * (size_t)c.E.n * S);
     if (c.bh_host) (void)hipHostFree(c.bh_host);
@@ -1989,11 +1992,10 @@ void ensure_width(Ctx& c, int m, int S) {
       // order of the multi-vector SpMV: plain or over XCD row ranges, the faster
       HELM_HIP(hipMemset(c.bX.p, 0, sizeof(double) * 2 * n * S));
       const float td = time_launch([&] {
-        dev::csr_spmv_block(n, c.A_ptr.p, c.A_col.p, c.A_val.p, nullptr, 0, S, c.bX.p, nullptr, c.bW.p, nullptr);
+        dev::spmv_block(n, block_matrix(c), nullptr, 0, S, c.bX.p, nullptr, c.bW.p, nullptr);
       });
       const float tx = time_launch([&] {
-        dev::csr_spmv_block(n, c.A_ptr.p, c.A_col.p, c.A_val.p, c.A_xr.p, c.A_xrows, S, c.bX.p, nullptr, c.bW.p,
-                            nullptr);
+        dev::spmv_block(n, block_matrix(c), c.A_xr.p, c.A_xrows, S, c.bX.p, nullptr, c.bW.p, nullptr);
       });
       c.blk_xcd = tx < td;
       c.blk_timed = true;
@@ -2064,9 +2066,9 @@ void batch_solve_block(BatchDev& b, int S, const double* in, hipStream_t s, Prof
 
 void spmv_block(Ctx& c, int S, const double* x, const double* b, double* y, hipStream_t s) {
   if (c.blk_force == 3 || (c.blk_force == 0 && c.blk_xcd))
-    dev::csr_spmv_block(c.D.n, c.A_ptr.p, c.A_col.p, c.A_val.p, c.A_xr.p, c.A_xrows, S, x, b, y, s);
+    dev::spmv_block(c.D.n, block_matrix(c), c.A_xr.p, c.A_xrows, S, x, b, y, s);
   else
-    dev::csr_spmv_block(c.D.n, c.A_ptr.p, c.A_col.p, c.A_val.p, nullptr, 0, S, x, b, y, s);
+    dev::spmv_block(c.D.n, block_matrix(c), nullptr, 0, S, x, b, y, s);
 }
 
 // Z = M^{-1} X for S interleaved vectors (eq. 2lvl, or eq. oras one-level).
@@ -2092,17 +2094,16 @@ void apply_precond_block(Ctx& c, int S, const double* X, double* Z, hipStream_t 
     if (p) c.prof.begin(s);
     dev::spmv_real_block(c.ZT.n, c.ZT_ptr.p, c.ZT_col.p, c.ZT_val.p, S, X, c.bcvec.p, s);
     batch_solve_block(c.coarse, S, c.bcvec.p, s, &c.prof, false);
-    // q = Z x_c, t = x - (A Z) x_c
-    dev::coarse_update_block(n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.AZ_ptr.p, c.AZ_col.p, c.AZ_val.p, S,
-                             c.coarse.x_b.p, X, c.bq.p, c.bt.p, s);
+    // t = x - (A Z) x_c; Z x_c joins the prolongation
+    dev::coarse_update_block(n, c.AZ_ptr.p, c.AZ_col.p, c.AZ_val.p, S, c.coarse.x_b.p, X, c.bt.p, s);
     if (p) c.prof.end(HELM_K_COARSE, 0.0, s);
     fine_solve_block(c, S, c.bt.p, s);
   } else {
     fine_solve_block(c, S, X, s);
   }
   if (p) c.prof.begin(s);
-  dev::prolong_block(n, c.pro_ptr.p, c.pro_idx.p, c.pro_w.p, S, c.fine[0].xout_b(), c.two_level ? c.bq.p : nullptr, Z,
-                     s);
+  dev::prolong_block(n, c.pro_ptr.p, c.pro_idx.p, c.pro_w.p, S, c.fine[0].xout_b(), c.Zp_ptr.p, c.Zp_col.p,
+                     c.Zp_val.p, c.two_level ? c.coarse.x_b.p : nullptr, Z, s);
   if (p) c.prof.end(HELM_K_PROLONG, 0.0, s);
 }
 

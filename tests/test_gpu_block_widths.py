@@ -1,5 +1,7 @@
 """Level solves of 2 to 8 right-hand sides advanced together (FP64 MFMA, real
 and imaginary parts side by side) against one right-hand side at a time."""
+import dataclasses
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -31,6 +33,24 @@ def test_narrow_blocks_match_single_solves(name, c64, nrhs):
     B = torch.stack([torch.from_numpy(wl.random_vector(h.n, 50 + k)) for k in range(nrhs)]).to("cuda")
     U, V = torch.zeros_like(B), torch.zeros_like(B)
     h.solve(B, U, tol=1e-14, restart=1, maxit=1, block=8)
+    for k in range(nrhs):
+        h.solve(B[k].contiguous(), V[k], tol=1e-14, restart=1, maxit=1)
+        assert float((U[k] - V[k]).norm() / V[k].norm()) <= 1e-11
+
+
+# The sparse kernels of a block step (products, coarse update, prolongation) over
+# every width, and rows of every kind: real, on an absorbing face (a few imaginary
+# parts), all complex (attenuation).  One step as above.
+@pytest.mark.parametrize("nrhs", [2, 4, 7, 9, 16])
+@pytest.mark.parametrize("attenuation", [0.0, 0.02])
+def test_block_products_match_single_solves(attenuation, nrhs):
+    w = wl.small_box(n=(6, 5, 4), order=2, n_parts=(2, 2, 1), overlap=2)
+    w = dataclasses.replace(w, c_tet=w.c_tet * (1 - 1j * attenuation))
+    h = helm.from_workload(w)
+    print(f"[products] attenuation={attenuation} nrhs={nrhs}", flush=True)
+    B = torch.stack([torch.from_numpy(wl.random_vector(h.n, 80 + k)) for k in range(nrhs)]).to("cuda")
+    U, V = torch.zeros_like(B), torch.zeros_like(B)
+    h.solve(B, U, tol=1e-14, restart=1, maxit=1, block=16)
     for k in range(nrhs):
         h.solve(B[k].contiguous(), V[k], tol=1e-14, restart=1, maxit=1)
         assert float((U[k] - V[k]).norm() / V[k].norm()) <= 1e-11
