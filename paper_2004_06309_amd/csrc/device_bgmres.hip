@@ -32,6 +32,16 @@ __device__ __forceinline__ dv4 mma(double a, double b, dv4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// bgs_dots streams the basis once per pass: non-temporal loads (a plain read of
+// 8 GB reaches 6.3 TB/s on this card, a non-temporal one 7.2; all Gram-Schmidt of
+// 49 block steps at one million unknowns 301 -> 293 ms).  Not in bgs_mul, whose
+// loads take half a cache line at a time and find the other half again (321 ms).
+typedef double dvec2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double2 ldnt(const double2* p) {
+  const dvec2 v = __builtin_nontemporal_load(reinterpret_cast<const dvec2*>(p));
+  return make_double2(v.x, v.y);
+}
+
 constexpr int kWaves = 4;   // waves per workgroup
 constexpr int kBPW = 4;     // basis blocks per wave in bgs_dots
 constexpr int kJG = kWaves * kBPW;  // basis blocks per dots workgroup (grid y splits the rest)
@@ -91,28 +101,39 @@ __global__ __launch_bounds__(64 * kWaves, 3) void bgs_dots_kernel(int64_t n, con
   // lane l takes row 4 t + l / 16 of the tile at k-step t, column l % 16
   const int rk = lane >> 4, col = lane & 15;
   const int64_t prow = (int64_t)blockIdx.x * wpg + sub;
-  for (int64_t tile = prow; tile < ntiles; tile += (int64_t)gridDim.x * wpg) {
-    const int64_t i0 = tile << 4;
-    double2 w[4], v[4][kBPW];
+  const int64_t stride = (int64_t)gridDim.x * wpg;
+  double2 w[4], v[4][kBPW];
+  // k-step t of a tile; rows past n read row n - 1 and count as zero in W
+  auto load = [&](int64_t tile, int t) {
+    const int64_t at = min((tile << 4) + 4 * t + rk, n - 1) * 16 + col;
+    w[t] = W[at];
+#pragma unroll
+    for (int q = 0; q < kBPW; ++q)
+      if (q < njb) v[t][q] = ldnt(Xq[q] + at);
+  };
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int q = 0; q < kBPW; ++q) v[t][q] = make_double2(0, 0);
+    if (prow < ntiles) load(prow, t);
+  }
+  for (int64_t tile = prow; tile < ntiles; tile += stride) {
+    // conj(v) w: re = vr wr + vi wi, im = vr wi - vi wr; a k-step's registers
+    // are refilled for the next tile right after their MFMAs
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int64_t row = i0 + 4 * t + rk;
-      const bool in = row < n;
-      w[t] = in ? W[row * 16 + col] : make_double2(0, 0);
+      const bool in = (tile << 4) + 4 * t + rk < n;
+      const double wr = in ? w[t].x : 0.0, wi = in ? w[t].y : 0.0;
 #pragma unroll
-      for (int q = 0; q < kBPW; ++q) v[t][q] = (q < njb && in) ? Xq[q][row * 16 + col] : make_double2(0, 0);
-    }
-    // conj(v) w: re = vr wr + vi wi, im = vr wi - vi wr
+      for (int q = 0; q < kBPW; ++q) dre[q] = mma(v[t][q].x, wr, dre[q]);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+      for (int q = 0; q < kBPW; ++q) dim[q] = mma(v[t][q].x, wi, dim[q]);
 #pragma unroll
-      for (int q = 0; q < kBPW; ++q) dre[q] = mma(v[t][q].x, w[t].x, dre[q]);
+      for (int q = 0; q < kBPW; ++q) dre[q] = mma(v[t][q].y, wi, dre[q]);
 #pragma unroll
-      for (int q = 0; q < kBPW; ++q) dim[q] = mma(v[t][q].x, w[t].y, dim[q]);
-#pragma unroll
-      for (int q = 0; q < kBPW; ++q) dre[q] = mma(v[t][q].y, w[t].y, dre[q]);
-#pragma unroll
-      for (int q = 0; q < kBPW; ++q) dim[q] = mma(-v[t][q].y, w[t].x, dim[q]);
+      for (int q = 0; q < kBPW; ++q) dim[q] = mma(-v[t][q].y, wr, dim[q]);
+      load(tile + stride, t);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   // register r of lane l holds entry (4 r + l / 16, l % 16) of each block
