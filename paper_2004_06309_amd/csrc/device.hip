@@ -38,19 +38,6 @@ __device__ __forceinline__ void cfma(double& ar, double& ai, double2 a, double2 
 __device__ __forceinline__ double2 widen(double2 a) { return a; }
 __device__ __forceinline__ double2 widen(float2 a) { return make_double2((double)a.x, (double)a.y); }
 
-// Panels are streamed once per sweep: non-temporal loads keep them from
-// evicting the reused vectors from the caches.
-typedef double dvec2 __attribute__((ext_vector_type(2)));
-typedef float fvec2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ double2 ldp(const double2* p) {
-  const dvec2 v = __builtin_nontemporal_load(reinterpret_cast<const dvec2*>(p));
-  return make_double2(v.x, v.y);
-}
-__device__ __forceinline__ float2 ldp(const float2* p) {
-  const fvec2 v = __builtin_nontemporal_load(reinterpret_cast<const fvec2*>(p));
-  return make_float2(v.x, v.y);
-}
-
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ int64_t uni64(int64_t x) {
   return ((int64_t)uni((int)(x >> 32)) << 32) | (uint32_t)uni((int)x);
@@ -786,15 +773,6 @@ __global__ __launch_bounds__(kWG) void batch_solve_coop_kernel(Batch b, const do
   }
 }
 
-// XCD-aware workgroup order for grids that are a multiple of 8: workgroups
-// are dealt round-robin to the 8 XCDs, so workgroup b takes block
-// (b % 8) * per + b / 8 and every XCD sweeps a contiguous eighth of the
-// blocks, keeping the x entries that block gathers in its own L2.
-__device__ __forceinline__ int64_t xcd_block() {
-  const unsigned per = gridDim.x / 8;
-  return (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-}
-
 // One row of a CSR matrix per G lanes; each lane takes U entries per pass
 // (entries base + u G + lane), loading all U columns, then all U values and
 // x entries before the multiply-adds, so a wave keeps U gathers in flight
@@ -1409,8 +1387,6 @@ __global__ __launch_bounds__(kWG) void copy_kernel(int64_t n, const double* __re
 }
 
 inline unsigned blocks_for(int64_t n, int per = kWG) { return (unsigned)((n + per - 1) / per); }
-// Same, rounded up to a multiple of 8 (grids of kernels that use xcd_block).
-inline unsigned blocks8_for(int64_t n) { return (blocks_for(n) + 7) / 8 * 8; }
 
 __global__ __launch_bounds__(kWG) void copy_tiles_kernel(const uint64_t* __restrict__ src, uint64_t* __restrict__ dst,
                                                          const int64_t* __restrict__ from,
