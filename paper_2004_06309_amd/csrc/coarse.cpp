@@ -36,9 +36,10 @@ struct Locator {
       }
     nb = std::max(1, (int)std::cbrt((double)nt / 4.0));
     for (int d = 0; d < 3; ++d) w[d] = (hi[d] - lo[d]) / nb + 1e-300;
-    std::vector<std::pair<int64_t, int64_t>> pairs;
+    // bins counted, then filled tet by tet
+    RawVec<int> box(6 * nt);
     for (int64_t q = 0; q < nt; ++q) {
-      int b0[3], b1[3];
+      int *b0 = &box[6 * q], *b1 = b0 + 3;
       for (int d = 0; d < 3; ++d) {
         double mn = 1e300, mx = -1e300;
         for (int a = 0; a < 4; ++a) {
@@ -49,19 +50,20 @@ struct Locator {
         b0[d] = clampb((int)std::floor((mn - lo[d]) / w[d] - 1e-9));
         b1[d] = clampb((int)std::floor((mx - lo[d]) / w[d] + 1e-9));
       }
+    }
+    auto bins = [&](int64_t q, auto&& f) {
+      const int *b0 = &box[6 * q], *b1 = b0 + 3;
       for (int i = b0[0]; i <= b1[0]; ++i)
         for (int j = b0[1]; j <= b1[1]; ++j)
-          for (int k = b0[2]; k <= b1[2]; ++k) pairs.push_back({i + (int64_t)nb * (j + (int64_t)nb * k), q});
-    }
-    std::sort(pairs.begin(), pairs.end());
-    int64_t nbk = (int64_t)nb * nb * nb;
+          for (int k = b0[2]; k <= b1[2]; ++k) f(i + (int64_t)nb * (j + (int64_t)nb * k));
+    };
+    const int64_t nbk = (int64_t)nb * nb * nb;
     ptr.assign(nbk + 1, 0);
-    idx.resize(pairs.size());
-    for (size_t p = 0; p < pairs.size(); ++p) {
-      ptr[pairs[p].first + 1]++;
-      idx[p] = pairs[p].second;
-    }
+    for (int64_t q = 0; q < nt; ++q) bins(q, [&](int64_t b) { ptr[b + 1]++; });
     for (int64_t b = 0; b < nbk; ++b) ptr[b + 1] += ptr[b];
+    idx.resize(ptr[nbk]);
+    std::vector<int64_t> fill(ptr.begin(), ptr.end() - 1);
+    for (int64_t q = 0; q < nt; ++q) bins(q, [&](int64_t b) { idx[fill[b]++] = q; });
   }
   int clampb(int v) const { return std::min(std::max(v, 0), nb - 1); }
 
@@ -123,16 +125,22 @@ void coarse_interpolation(const Discretization& D, const helm_mesh& cm, CsrReal&
   Z.m = nc;
   Z.ptr.assign(n + 1, 0);
   for (int64_t j = 0; j < n; ++j) {
+    Z.ptr[j + 1] = Z.ptr[j];
+    for (int a = 0; a < 4; ++a) Z.ptr[j + 1] += rc[4 * j + a] >= 0;
+  }
+  Z.col.resize(Z.ptr[n]);
+  Z.val.resize(Z.ptr[n]);
+#pragma omp parallel for schedule(static)
+  for (int64_t j = 0; j < n; ++j) {
     std::pair<int32_t, double> e[4];
     int ne = 0;
     for (int a = 0; a < 4; ++a)
       if (rc[4 * j + a] >= 0) e[ne++] = {rc[4 * j + a], rv[4 * j + a]};
     std::sort(e, e + ne);
     for (int a = 0; a < ne; ++a) {
-      Z.col.push_back(e[a].first);
-      Z.val.push_back(e[a].second);
+      Z.col[Z.ptr[j] + a] = e[a].first;
+      Z.val[Z.ptr[j] + a] = e[a].second;
     }
-    Z.ptr[j + 1] = (int64_t)Z.col.size();
   }
 }
 

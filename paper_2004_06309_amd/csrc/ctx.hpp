@@ -50,7 +50,10 @@ struct DVec {
     alloc(count);
     if (count) HELM_HIP(hipMemcpy(p, src, count * sizeof(T), hipMemcpyHostToDevice));
   }
-  void upload(const std::vector<T>& v) { upload(v.data(), v.size()); }
+  template <class A>
+  void upload(const std::vector<T, A>& v) {
+    upload(v.data(), v.size());
+  }
 };
 
 // Host description of a batch of factored matrices (solve layout).

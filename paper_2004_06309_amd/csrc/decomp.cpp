@@ -68,6 +68,7 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
     std::vector<int32_t> layer(nt, -1);
     std::vector<int32_t> lev(n, -1);
     std::vector<uint8_t> vmark(nv, 0);
+    std::vector<int32_t> g2l(n, -1);
 #pragma omp for schedule(dynamic, 1)
     for (int32_t i = 0; i < n_sub; ++i) {
       SubdomainHost& S = subs[i];
@@ -118,17 +119,32 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
         S.chi[k] = overlap == 0 ? 1.0 : std::max(0.0, 1.0 - (double)S.level[k] / overlap);
         D.dof_coord(dl[k], &S.coords[3 * k]);
         lev[dl[k]] = -1;
+        g2l[dl[k]] = (int32_t)k;
       }
       // faces of Gamma_i met once: physical boundary or artificial interface
-      std::vector<FK> fk(4 * cur.size());
-      for (size_t q = 0; q < cur.size(); ++q)
-        for (int f = 0; f < 4; ++f) {
-          FK& k = fk[4 * q + f];
-          for (int c = 0; c < 3; ++c) k.v[c] = D.tets[4 * cur[q] + kTetFace[f][c]];
-          std::sort(k.v, k.v + 3);
-          k.tet = cur[q];
-        }
-      std::sort(fk.begin(), fk.end());
+      // (grouped by their smallest vertex, local vertices being the first local
+      // dofs, each group sorted by itself)
+      auto face = [&](int64_t t, int f) {
+        FK k;
+        for (int c = 0; c < 3; ++c) k.v[c] = D.tets[4 * t + kTetFace[f][c]];
+        std::sort(k.v, k.v + 3);
+        k.tet = t;
+        return k;
+      };
+      std::vector<int64_t> gp(dl.size() + 1, 0);
+      for (int64_t t : cur)
+        for (int f = 0; f < 4; ++f) gp[g2l[face(t, f).v[0]] + 1]++;
+      for (size_t k = 0; k < dl.size(); ++k) gp[k + 1] += gp[k];
+      RawVec<FK> fk(4 * cur.size());
+      {
+        std::vector<int64_t> fill(gp.begin(), gp.end() - 1);
+        for (int64_t t : cur)
+          for (int f = 0; f < 4; ++f) {
+            const FK k = face(t, f);
+            fk[fill[g2l[k.v[0]]]++] = k;
+          }
+      }
+      for (size_t k = 0; k < dl.size(); ++k) std::sort(fk.begin() + gp[k], fk.begin() + gp[k + 1]);
       std::vector<ImpFace> imp;
       for (size_t a = 0; a < fk.size();) {
         size_t b = a + 1;
@@ -142,7 +158,8 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
         a = b;
       }
       for (int64_t t : cur) layer[t] = -1;
-      assemble_local(D, S.tets, imp, S.dofs, S.A);
+      assemble_local(D, S.tets, imp, S.dofs, g2l.data(), S.A);
+      for (int64_t d : dl) g2l[d] = -1;
     }
   }
   // partition of unity

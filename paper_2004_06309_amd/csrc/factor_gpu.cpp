@@ -17,28 +17,26 @@ namespace {
 
 // Front scatter list of one matrix: for every supernode, the front positions
 // (row + col * m) and value indices of its original entries (those with
-// min(row, col) among its columns, in the symbolic ordering).
-void scatter_lists(const Csr& A, const Symbolic& S, int64_t val0, std::vector<int64_t>& sn_ptr,
-                   std::vector<int32_t>& pos, std::vector<int32_t>& val) {
-  const int64_t n = A.n;
+// min(row, col) among its columns, in the symbolic ordering).  Every entry of A
+// belongs to one supernode, so pos and val hold as many places as A has entries.
+void scatter_lists(const Csr& A, const Symbolic& S, int64_t val0, std::vector<int64_t>& sn_ptr, int32_t* pos,
+                   int32_t* val) {
+  const int64_t n = A.n, nnz = A.nnz();
   std::vector<int64_t> tptr(n + 1, 0);
-  for (int64_t p = 0; p < A.nnz(); ++p) tptr[A.col[p] + 1]++;
+  for (int64_t p = 0; p < nnz; ++p) tptr[A.col[p] + 1]++;
   for (int64_t i = 0; i < n; ++i) tptr[i + 1] += tptr[i];
-  std::vector<int32_t> trow(A.nnz());
-  std::vector<int64_t> tidx(A.nnz());
+  struct Entry {
+    int32_t row, p;  // row and value index
+  };
+  RawVec<Entry> tr(nnz);  // column by column
   {
     std::vector<int64_t> fill(tptr.begin(), tptr.end() - 1);
     for (int64_t i = 0; i < n; ++i)
-      for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) {
-        const int64_t q = fill[A.col[p]]++;
-        trow[q] = (int32_t)i;
-        tidx[q] = p;
-      }
+      for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) tr[fill[A.col[p]]++] = {(int32_t)i, (int32_t)p};
   }
   std::vector<int32_t> fpos(n, -1);
   sn_ptr.assign(S.nsn + 1, 0);
-  pos.clear();
-  val.clear();
+  int64_t o = 0;
   for (int32_t s = 0; s < S.nsn; ++s) {
     const int32_t c0 = S.sn_c0[s], w = S.sn_w[s], c1 = c0 + w;
     const int32_t* R = S.rows.data() + S.sn_rptr[s];
@@ -46,27 +44,28 @@ void scatter_lists(const Csr& A, const Symbolic& S, int64_t val0, std::vector<in
     const int64_t m = w + r;
     for (int32_t k = 0; k < w; ++k) fpos[c0 + k] = k;
     for (int32_t a = 0; a < r; ++a) fpos[R[a]] = w + a;
+    auto add = [&](int64_t f, int32_t outer, int64_t p) {
+      if (outer < 0) fail(HELM_EINVAL, "internal: entry outside its front");
+      if (o >= nnz) fail(HELM_EINVAL, "internal: entry in two fronts");
+      pos[o] = (int32_t)f;
+      val[o++] = (int32_t)(val0 + p);
+    };
     for (int32_t j = c0; j < c1; ++j) {
       const int32_t old = S.perm[j];
       for (int64_t p = A.ptr[old]; p < A.ptr[old + 1]; ++p) {
         const int32_t nc = S.iperm[A.col[p]];
-        if (nc < c0) continue;
-        if (fpos[nc] < 0) fail(HELM_EINVAL, "internal: entry outside its front");
-        pos.push_back((int32_t)(fpos[j] + (int64_t)fpos[nc] * m));
-        val.push_back((int32_t)(val0 + p));
+        if (nc >= c0) add(fpos[j] + (int64_t)fpos[nc] * m, fpos[nc], p);
       }
       for (int64_t p = tptr[old]; p < tptr[old + 1]; ++p) {
-        const int32_t nr = S.iperm[trow[p]];
-        if (nr < c1) continue;
-        if (fpos[nr] < 0) fail(HELM_EINVAL, "internal: entry outside its front");
-        pos.push_back((int32_t)(fpos[nr] + (int64_t)fpos[j] * m));
-        val.push_back((int32_t)(val0 + tidx[p]));
+        const int32_t nr = S.iperm[tr[p].row];
+        if (nr >= c1) add(fpos[nr] + (int64_t)fpos[j] * m, fpos[nr], tr[p].p);
       }
     }
     for (int32_t k = 0; k < w; ++k) fpos[c0 + k] = -1;
     for (int32_t a = 0; a < r; ++a) fpos[R[a]] = -1;
-    sn_ptr[s + 1] = (int64_t)pos.size();
+    sn_ptr[s + 1] = o;
   }
+  if (o != nnz) fail(HELM_EINVAL, "internal: entry in no front");
 }
 
 // ep[a] for a child's rows a: the position of that row in its parent's front.
@@ -111,15 +110,21 @@ void factor_batch_device(const std::vector<const Csr*>& As, const std::vector<co
   if (nnz0[nm] >= (int64_t)INT32_MAX) fail(HELM_EINVAL, "batch too large for 32-bit value indices");
   std::vector<double> anorm(nm, 0.0);
   std::vector<std::vector<int64_t>> sptr(nm);
-  std::vector<std::vector<int32_t>> spos(nm), sval(nm);
+  RawVec<int32_t> spos(nnz0[nm]), sval(nnz0[nm]);  // all matrices' scatter lists
   std::vector<int32_t> ep(std::max<int64_t>(rows0[nm], 1));
   std::string errmsg;
   int errcode = 0;
 #pragma omp parallel for schedule(dynamic, 1)
   for (int i = 0; i < nm; ++i) {
     try {
-      for (const cplx& v : As[i]->val) anorm[i] = std::max(anorm[i], std::abs(v));
-      scatter_lists(*As[i], *Ss[i], nnz0[i], sptr[i], spos[i], sval[i]);
+      // moduli only of entries that may be the largest
+      double lim = 0;
+      for (const cplx& v : As[i]->val)
+        if (!(std::norm(v) < lim)) {
+          anorm[i] = std::max(anorm[i], std::abs(v));
+          lim = anorm[i] * anorm[i] * (1 - 1e-12);
+        }
+      scatter_lists(*As[i], *Ss[i], nnz0[i], sptr[i], spos.data() + nnz0[i], sval.data() + nnz0[i]);
       extend_add_map(*Ss[i], ep.data() + rows0[i]);
     } catch (const Error& e) {
 #pragma omp critical
@@ -136,24 +141,15 @@ void factor_batch_device(const std::vector<const Csr*>& As, const std::vector<co
     if (!(anorm[i] > 0)) fail(HELM_ESINGULAR, "zero local matrix");
 
   // device inputs: values, scatter lists, extend-add map
-  std::vector<int64_t> asm0(nm + 1, 0);
-  for (int i = 0; i < nm; ++i) asm0[i + 1] = asm0[i] + (int64_t)spos[i].size();
   DVec<double> aval;
   DVec<int32_t> asm_pos, asm_val, ep_d;
-  {
-    std::vector<cplx> v(nnz0[nm]);
-    std::vector<int32_t> pa(asm0[nm]), va(asm0[nm]);
-#pragma omp parallel for schedule(static)
-    for (int i = 0; i < nm; ++i) {
-      std::copy(As[i]->val.begin(), As[i]->val.end(), v.begin() + nnz0[i]);
-      std::copy(spos[i].begin(), spos[i].end(), pa.begin() + asm0[i]);
-      std::copy(sval[i].begin(), sval[i].end(), va.begin() + asm0[i]);
-    }
-    aval.upload(reinterpret_cast<const double*>(v.data()), 2 * v.size());
-    asm_pos.upload(pa);
-    asm_val.upload(va);
-    ep_d.upload(ep);
-  }
+  aval.alloc(2 * (size_t)nnz0[nm]);
+  for (int i = 0; i < nm; ++i)
+    if (As[i]->nnz())
+      HELM_HIP(hipMemcpy(aval.p + 2 * nnz0[i], As[i]->val.data(), sizeof(cplx) * As[i]->nnz(), hipMemcpyHostToDevice));
+  asm_pos.upload(spos);
+  asm_val.upload(sval);
+  ep_d.upload(ep);
 
   // Schur complement offsets, children lists, levels.  A supernode's Schur
   // complement (r x r) is live from its own level (its height in the
@@ -295,8 +291,8 @@ void factor_batch_device(const std::vector<const Csr*>& As, const std::vector<co
       J.pb = pb[i];
       J.pfo = S.sn_fwd_off[s];
       J.pbo = S.sn_bwd_off[s];
-      J.asm0 = asm0[i] + sptr[i][s];
-      J.asm1 = asm0[i] + sptr[i][s + 1];
+      J.asm0 = nnz0[i] + sptr[i][s];
+      J.asm1 = nnz0[i] + sptr[i][s + 1];
       J.m = m;
       J.w = w;
       J.c0 = S.sn_c0[s];

@@ -256,28 +256,53 @@ void build_discretization(Discretization& D, const helm_mesh& mesh, const double
 
   // edges (P2): sorted unique (min, max) pairs
   if (D.order == 2) {
-    std::vector<std::pair<int64_t, int64_t>> all((size_t)nt * 6);
+    // larger ends grouped by smaller end, each group sorted by itself
+    auto ends = [&](int64_t t, int e, int64_t& lo, int64_t& hi) {
+      const int64_t a = D.tets[4 * t + kEdge[e][0]], b = D.tets[4 * t + kEdge[e][1]];
+      lo = std::min(a, b);
+      hi = std::max(a, b);
+    };
+    std::vector<int64_t> ptr(nv + 1, 0), eptr(nv + 1, 0);
+    int64_t lo, hi;
     for (int64_t t = 0; t < nt; ++t)
       for (int e = 0; e < 6; ++e) {
-        int64_t a = D.tets[4 * t + kEdge[e][0]], b = D.tets[4 * t + kEdge[e][1]];
-        all[6 * t + e] = {std::min(a, b), std::max(a, b)};
+        ends(t, e, lo, hi);
+        ptr[lo + 1]++;
       }
-    std::vector<std::pair<int64_t, int64_t>> u = all;
-    std::sort(u.begin(), u.end());
-    u.erase(std::unique(u.begin(), u.end()), u.end());
-    D.ne = (int64_t)u.size();
-    D.edges.resize(2 * D.ne);
-    for (int64_t i = 0; i < D.ne; ++i) {
-      D.edges[2 * i] = u[i].first;
-      D.edges[2 * i + 1] = u[i].second;
+    for (int64_t v = 0; v < nv; ++v) ptr[v + 1] += ptr[v];
+    RawVec<int64_t> up((size_t)nt * 6);
+    {
+      std::vector<int64_t> fill(ptr.begin(), ptr.end() - 1);
+      for (int64_t t = 0; t < nt; ++t)
+        for (int e = 0; e < 6; ++e) {
+          ends(t, e, lo, hi);
+          up[fill[lo]++] = hi;
+        }
     }
+#pragma omp parallel for schedule(dynamic, 256)
+    for (int64_t v = 0; v < nv; ++v) {
+      auto b = up.begin() + ptr[v], e = up.begin() + ptr[v + 1];
+      std::sort(b, e);
+      eptr[v + 1] = std::unique(b, e) - b;
+    }
+    for (int64_t v = 0; v < nv; ++v) eptr[v + 1] += eptr[v];
+    D.ne = eptr[nv];
+    D.edges.resize(2 * D.ne);
     D.tet_dofs.resize((size_t)nt * 10);
+#pragma omp parallel for schedule(static)
+    for (int64_t v = 0; v < nv; ++v)
+      for (int64_t i = eptr[v]; i < eptr[v + 1]; ++i) {
+        D.edges[2 * i] = v;
+        D.edges[2 * i + 1] = up[ptr[v] + (i - eptr[v])];
+      }
 #pragma omp parallel for schedule(static)
     for (int64_t t = 0; t < nt; ++t) {
       for (int a = 0; a < 4; ++a) D.tet_dofs[10 * t + a] = D.tets[4 * t + a];
       for (int e = 0; e < 6; ++e) {
-        auto it = std::lower_bound(u.begin(), u.end(), all[6 * t + e]);
-        D.tet_dofs[10 * t + 4 + e] = nv + (it - u.begin());
+        int64_t a, b;
+        ends(t, e, a, b);
+        const auto u = up.begin() + ptr[a];
+        D.tet_dofs[10 * t + 4 + e] = nv + eptr[a] + (std::lower_bound(u, u + (eptr[a + 1] - eptr[a]), b) - u);
       }
     }
   } else {
@@ -287,27 +312,62 @@ void build_discretization(Discretization& D, const helm_mesh& mesh, const double
   D.n = D.nv + D.ne;
 
   // boundary faces
-  std::vector<FaceKey> fk((size_t)nt * 4);
-  for (int64_t t = 0; t < nt; ++t)
-    for (int f = 0; f < 4; ++f) {
-      FaceKey& k = fk[4 * t + f];
-      for (int q = 0; q < 3; ++q) k.v[q] = D.tets[4 * t + kTetFace[f][q]];
-      std::sort(k.v, k.v + 3);
-      k.tet = t;
+  {
+    // faces grouped by their smallest vertex, each group sorted by itself
+    auto face = [&](int64_t t, int f, int64_t* v) {
+      for (int q = 0; q < 3; ++q) v[q] = D.tets[4 * t + kTetFace[f][q]];
+      std::sort(v, v + 3);
+    };
+    std::vector<int64_t> ptr(nv + 1, 0), bptr(nv + 1, 0);
+    int64_t v[3];
+    for (int64_t t = 0; t < nt; ++t)
+      for (int f = 0; f < 4; ++f) {
+        face(t, f, v);
+        ptr[v[0] + 1]++;
+      }
+    for (int64_t a = 0; a < nv; ++a) ptr[a + 1] += ptr[a];
+    RawVec<FaceKey> fk((size_t)nt * 4);
+    {
+      std::vector<int64_t> fill(ptr.begin(), ptr.end() - 1);
+      for (int64_t t = 0; t < nt; ++t)
+        for (int f = 0; f < 4; ++f) {
+          face(t, f, v);
+          fk[fill[v[0]]++] = {{v[0], v[1], v[2]}, t};
+        }
     }
-  std::sort(fk.begin(), fk.end());
-  for (size_t i = 0; i < fk.size();) {
-    size_t j = i + 1;
-    while (j < fk.size() && fk[j].same(fk[i])) ++j;
-    if (j - i > 2) fail(HELM_EINVAL, "face shared by more than two tets");
-    if (j - i == 1) {
-      for (int q = 0; q < 3; ++q) D.bface.push_back(fk[i].v[q]);
-      D.bowner.push_back(fk[i].tet);
-      bool top = true;
-      for (int q = 0; q < 3; ++q) top = top && D.xyz[3 * fk[i].v[q] + 2] == D.ztop;
-      D.bdir.push_back(top ? 1 : 0);
+    int over = 0;
+    // the faces of one tet move to the front of their group
+#pragma omp parallel for schedule(dynamic, 256) reduction(+ : over)
+    for (int64_t a = 0; a < nv; ++a) {
+      const int64_t e = ptr[a + 1];
+      std::sort(fk.begin() + ptr[a], fk.begin() + e);
+      int64_t out = ptr[a];
+      for (int64_t i = ptr[a]; i < e;) {
+        int64_t j = i + 1;
+        while (j < e && fk[j].same(fk[i])) ++j;
+        if (j - i > 2) ++over;
+        if (j - i == 1) fk[out++] = fk[i];
+        i = j;
+      }
+      bptr[a + 1] = out - ptr[a];
     }
-    i = j;
+    if (over) fail(HELM_EINVAL, "face shared by more than two tets");
+    for (int64_t a = 0; a < nv; ++a) bptr[a + 1] += bptr[a];
+    D.bface.resize(3 * bptr[nv]);
+    D.bowner.resize(bptr[nv]);
+    D.bdir.resize(bptr[nv]);
+#pragma omp parallel for schedule(static)
+    for (int64_t a = 0; a < nv; ++a)
+      for (int64_t b = bptr[a]; b < bptr[a + 1]; ++b) {
+        const FaceKey& k = fk[ptr[a] + (b - bptr[a])];
+        bool top = true;
+        for (int q = 0; q < 3; ++q) {
+          D.bface[3 * b + q] = k.v[q];
+          top = top && D.xyz[3 * k.v[q] + 2] == D.ztop;
+        }
+        D.bowner[b] = k.tet;
+        D.bdir[b] = top ? 1 : 0;
+      }
   }
   D.dir_mask.assign(D.n, 0);
   const int64_t nb = (int64_t)D.bowner.size();
@@ -326,20 +386,15 @@ void build_discretization(Discretization& D, const helm_mesh& mesh, const double
     if (!D.bdir[f]) faces.push_back({{D.bface[3 * f], D.bface[3 * f + 1], D.bface[3 * f + 2]}, D.bowner[f]});
   std::vector<int64_t> all_dofs(D.n);
   std::iota(all_dofs.begin(), all_dofs.end(), 0);
-  assemble_local(D, all_tets, faces, all_dofs, D.A);
+  assemble_local(D, all_tets, faces, all_dofs, nullptr, D.A);
 }
 
 void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_list,
-                    const std::vector<ImpFace>& faces, const std::vector<int64_t>& dofs, Csr& out) {
+                    const std::vector<ImpFace>& faces, const std::vector<int64_t>& dofs, const int32_t* g2l,
+                    Csr& out) {
   const int nl = D.nloc, nfl = D.nfloc;
   const int64_t nloc_dofs = (int64_t)dofs.size();
-  const bool identity_map = nloc_dofs == D.n;
-  auto lid = [&](int64_t g) -> int64_t {
-    if (identity_map) return g;
-    auto it = std::lower_bound(dofs.begin(), dofs.end(), g);
-    if (it == dofs.end() || *it != g) return -1;
-    return it - dofs.begin();
-  };
+  auto lid = [&](int64_t g) -> int64_t { return g2l ? g2l[g] : g; };
   const int64_t ntl = (int64_t)tet_list.size(), nfc = (int64_t)faces.size();
   // local dofs of every listed tet and face
   std::vector<int32_t> tl((size_t)ntl * nl);
@@ -379,64 +434,88 @@ void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_lis
   out = Csr();
   out.n = out.m = nloc_dofs;
   out.ptr.assign(nloc_dofs + 1, 0);
-  std::vector<std::vector<int32_t>> rowcols(nloc_dofs);
-#pragma omp parallel for schedule(dynamic, 256)
-  for (int64_t r = 0; r < nloc_dofs; ++r) {
-    std::vector<int32_t>& c = rowcols[r];
-    if (D.dir_mask[dofs[r]]) {
-      c.push_back((int32_t)r);
-      continue;
-    }
-    for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
-      int64_t item = rt_idx[p] / nl;
-      for (int b = 0; b < nl; ++b) {
-        int32_t cc = tl[item * nl + b];
-        if (!D.dir_mask[dofs[cc]]) c.push_back(cc);
+  // rows in blocks; `seen` marks the columns met in the present row and, in the
+  // second pass, `at` their places in it
+  constexpr int64_t kBlk = 256;
+  const int64_t nblk = (nloc_dofs + kBlk - 1) / kBlk;
+  std::vector<uint8_t> dir(nloc_dofs);
+  for (int64_t r = 0; r < nloc_dofs; ++r) dir[r] = D.dir_mask[dofs[r]];
+  std::vector<std::vector<int32_t>> bcol(nblk);
+#pragma omp parallel
+  {
+    std::vector<int32_t> seen(nloc_dofs, -1);
+#pragma omp for schedule(dynamic, 1)
+    for (int64_t k = 0; k < nblk; ++k) {
+      std::vector<int32_t>& c = bcol[k];
+      for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
+        const size_t c0 = c.size();
+        if (dir[r]) {
+          c.push_back((int32_t)r);
+        } else {
+          for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
+            const int32_t* cc = &tl[rt_idx[p] / nl * nl];
+            for (int b = 0; b < nl; ++b)
+              if (seen[cc[b]] != (int32_t)r && !dir[cc[b]]) {
+                seen[cc[b]] = (int32_t)r;
+                c.push_back(cc[b]);
+              }
+          }
+          std::sort(c.begin() + c0, c.end());
+        }
+        out.ptr[r + 1] = (int64_t)(c.size() - c0);
       }
     }
-    std::sort(c.begin(), c.end());
-    c.erase(std::unique(c.begin(), c.end()), c.end());
   }
-  for (int64_t r = 0; r < nloc_dofs; ++r) out.ptr[r + 1] = out.ptr[r] + (int64_t)rowcols[r].size();
+  for (int64_t r = 0; r < nloc_dofs; ++r) out.ptr[r + 1] += out.ptr[r];
   out.col.resize(out.ptr[nloc_dofs]);
-  out.val.assign(out.ptr[nloc_dofs], cplx(0, 0));
-#pragma omp parallel for schedule(dynamic, 256)
-  for (int64_t r = 0; r < nloc_dofs; ++r) {
-    std::vector<int32_t>& c = rowcols[r];
-    std::copy(c.begin(), c.end(), out.col.begin() + out.ptr[r]);
-    cplx* v = &out.val[out.ptr[r]];
-    auto pos = [&](int32_t cc) { return std::lower_bound(c.begin(), c.end(), cc) - c.begin(); };
-    if (D.dir_mask[dofs[r]]) {
-      v[0] = 1.0;
-    } else {
-      for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
-        int64_t item = rt_idx[p] / nl;
-        int a = (int)(rt_idx[p] % nl);
-        int64_t t = tet_list[item];
-        cplx k2 = D.k[t] * D.k[t];
-        const double* K = &D.Ke[(size_t)t * nl * nl + a * nl];
-        const double* M = &D.Me[(size_t)t * nl * nl + a * nl];
-        for (int b = 0; b < nl; ++b) {
-          int32_t cc = tl[item * nl + b];
-          if (D.dir_mask[dofs[cc]]) continue;
-          v[pos(cc)] += -K[b] + k2 * M[b];
+  out.val.resize(out.ptr[nloc_dofs]);
+#pragma omp parallel
+  {
+    std::vector<int32_t> seen(nloc_dofs, -1), at(nloc_dofs);
+#pragma omp for schedule(dynamic, 1)
+    for (int64_t k = 0; k < nblk; ++k) {
+      const int32_t* c = bcol[k].data();
+      for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
+        const int32_t len = (int32_t)(out.ptr[r + 1] - out.ptr[r]);
+        cplx* v = &out.val[out.ptr[r]];
+        for (int32_t q = 0; q < len; ++q) {
+          out.col[out.ptr[r] + q] = c[q];
+          v[q] = cplx(0, 0);
+          seen[c[q]] = (int32_t)r;
+          at[c[q]] = q;
+        }
+        c += len;
+        if (dir[r]) {
+          v[0] = 1.0;
+          continue;
+        }
+        for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
+          int64_t item = rt_idx[p] / nl;
+          int a = (int)(rt_idx[p] % nl);
+          int64_t t = tet_list[item];
+          cplx k2 = D.k[t] * D.k[t];
+          const double* K = &D.Ke[(size_t)t * nl * nl + a * nl];
+          const double* M = &D.Me[(size_t)t * nl * nl + a * nl];
+          for (int b = 0; b < nl; ++b) {
+            int32_t cc = tl[item * nl + b];
+            if (dir[cc]) continue;
+            v[at[cc]] += -K[b] + k2 * M[b];
+          }
+        }
+        for (int64_t p = rf_ptr[r]; p < rf_ptr[r + 1]; ++p) {
+          int64_t item = rf_idx[p] / nfl;
+          int a = (int)(rf_idx[p] % nfl);
+          cplx ik = cplx(0, 1) * D.k[faces[item].owner];
+          const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
+          for (int b = 0; b < nfl; ++b) {
+            int32_t cc = fl[item * nfl + b];
+            // not a face dof outside the tet pattern
+            if (cc >= 0 && !dir[cc] && seen[cc] == (int32_t)r) v[at[cc]] += ik * B[b];
+          }
         }
       }
-      for (int64_t p = rf_ptr[r]; p < rf_ptr[r + 1]; ++p) {
-        int64_t item = rf_idx[p] / nfl;
-        int a = (int)(rf_idx[p] % nfl);
-        cplx ik = cplx(0, 1) * D.k[faces[item].owner];
-        const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
-        for (int b = 0; b < nfl; ++b) {
-          int32_t cc = fl[item * nfl + b];
-          if (cc < 0 || D.dir_mask[dofs[cc]]) continue;
-          auto q = pos(cc);
-          if (q >= (int64_t)c.size() || c[q] != cc) continue;  // face dof outside the tet pattern
-          v[q] += ik * B[b];
-        }
-      }
+      std::vector<int32_t>().swap(bcol[k]);
     }
-    std::vector<int32_t>().swap(c);
   }
 }
 

@@ -6,6 +6,8 @@
 #include <memory>
 #include <stdexcept>
 #include <string>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/helm.h"
@@ -20,13 +22,34 @@ struct Error : std::runtime_error {
 };
 [[noreturn]] inline void fail(int code, const std::string& msg) { throw Error(code, msg); }
 
+// Vector whose elements start unwritten: large arrays are first touched by the
+// threads that fill them (clearing them first is a serial pass of page faults,
+// 29 of 385 ms of a whole setup at 138,000 unknowns for the element matrices alone).
+template <class T>
+struct RawAlloc : std::allocator<T> {
+  template <class U>
+  struct rebind {
+    using other = RawAlloc<U>;
+  };
+  template <class U>
+  void construct(U*) noexcept {
+    static_assert(std::is_trivially_copyable<U>::value, "raw elements are plain data");
+  }
+  template <class U, class... A>
+  void construct(U* p, A&&... a) {
+    ::new (static_cast<void*>(p)) U(std::forward<A>(a)...);
+  }
+};
+template <class T>
+using RawVec = std::vector<T, RawAlloc<T>>;
+
 // Complex CSR with 64-bit row pointers (rows may exceed 2^31 entries in total).
 struct Csr {
   int64_t n = 0;  // rows
   int64_t m = 0;  // columns
   std::vector<int64_t> ptr;
-  std::vector<int32_t> col;
-  std::vector<cplx> val;
+  RawVec<int32_t> col;
+  RawVec<cplx> val;
   int64_t nnz() const { return ptr.empty() ? 0 : ptr.back(); }
 };
 
@@ -49,8 +72,8 @@ struct Discretization {
   std::vector<int64_t> edges;    // [ne][2], sorted (min, max), lexicographic
   std::vector<int64_t> tet_dofs; // [nt][nloc]
   std::vector<double> vol;       // [nt]
-  std::vector<double> Ke;        // [nt][nloc][nloc]  int grad phi_a . grad phi_b
-  std::vector<double> Me;        // [nt][nloc][nloc]  int phi_a phi_b
+  RawVec<double> Ke;             // [nt][nloc][nloc]  int grad phi_a . grad phi_b
+  RawVec<double> Me;             // [nt][nloc][nloc]  int phi_a phi_b
   std::vector<cplx> k;           // wavenumber per tet
   double omega = 0;
   double ztop = 0;
@@ -79,9 +102,11 @@ void build_discretization(Discretization& D, const helm_mesh& mesh, const double
 void face_matrix(int order, double area, double* B);  // nfloc x nfloc, int psi_a psi_b
 // Assemble -K + M_{k^2} + i B_k over tet_list (+ impedance faces), restricted
 // to the sorted dof list `dofs` (global ids), Dirichlet rows/cols replaced by
-// identity.  Rows/cols of the result index into `dofs`.
+// identity.  Rows/cols of the result index into `dofs`.  g2l maps global dofs to
+// places in `dofs`, -1 outside (null: `dofs` holds all dofs).
 void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_list,
-                    const std::vector<ImpFace>& faces, const std::vector<int64_t>& dofs, Csr& out);
+                    const std::vector<ImpFace>& faces, const std::vector<int64_t>& dofs, const int32_t* g2l,
+                    Csr& out);
 // Locate a point: tet index (or -1) and barycentric coordinates.
 int64_t locate_point(const std::vector<double>& xyz, const std::vector<int64_t>& tets, const double* p,
                      double* lam, const std::vector<int64_t>* candidates = nullptr);

@@ -221,13 +221,16 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
   std::vector<std::vector<dev::Tile>> lf(maxlev_f + 1), lb(maxlev_b + 1);
   std::vector<char> sn_narrow(nsn, 0), sn_top(nsn, 0);
   std::vector<int32_t> fcon_cnt(fr0[nm] + 1, 0);
-  std::vector<std::vector<std::pair<int64_t, int32_t>>> fcon_m(nm);
+  std::vector<std::vector<int64_t>> frls(nm);
+  std::vector<std::vector<int32_t>> kinvs(nm);
   std::vector<TileShape> ts;
   for (int i = 0; i < nm; ++i) {
     const Symbolic& S = *Ss[i];
     const std::vector<int32_t>& piv = num[i].piv;
-    std::vector<int32_t> kinv(S.n);
-    std::vector<int64_t> frl(S.nsn);
+    std::vector<int32_t>& kinv = kinvs[i];
+    std::vector<int64_t>& frl = frls[i];
+    kinv.resize(S.n);
+    frl.resize(S.nsn);
     int64_t fr = 0;
     for (int32_t s = 0; s < S.nsn; ++s) {
       const int64_t g = sn0[i] + s;
@@ -262,8 +265,17 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
         off += (int64_t)t.nrows * t.ncols;
       }
     }
-    // children's updates routed to the parent's front rows
-    auto& fl = fcon_m[i];
+  }
+  // children's updates routed to the parent's front rows: (front row, update)
+  // in the order of the children, counted and then filled by row, every matrix
+  // by itself
+  std::vector<RawVec<int64_t>> fcon_m(nm);
+  int missing = 0;
+#pragma omp parallel for schedule(dynamic, 1) reduction(+ : missing)
+  for (int i = 0; i < nm; ++i) {
+    const Symbolic& S = *Ss[i];
+    RawVec<int64_t>& fl = fcon_m[i];
+    fl.resize(S.rows.size());
     for (int32_t c = 0; c < S.nsn; ++c) {
       const int32_t p = S.sn_parent[c];
       if (p < 0) continue;
@@ -274,29 +286,32 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
         const int32_t row = S.rows[a];
         int64_t f;
         if (row >= pc0 && row < pc0 + pw) {
-          f = kinv[row];
+          f = kinvs[i][row];
         } else {
           const int32_t* it = std::lower_bound(Rp, Rp + rp, row);
-          if (it == Rp + rp || *it != row) fail(HELM_EINVAL, "internal: child row missing from parent front");
+          if (it == Rp + rp || *it != row) ++missing, it = Rp;
           f = pw + (it - Rp);
         }
-        fl.push_back({fr0[i] + frl[p] + f, (int32_t)(u0[i] + a)});
+        fl[a] = fr0[i] + frls[i][p] + f;
+        if (!missing) fcon_cnt[fl[a] + 1]++;
       }
     }
-    std::stable_sort(fl.begin(), fl.end(),
-                     [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
-                       return x.first < y.first;
-                     });
-    for (auto& e : fl) fcon_cnt[e.first + 1]++;
   }
+  if (missing) fail(HELM_EINVAL, "internal: child row missing from parent front");
   B.fcon_ptr.resize(fr0[nm] + 1);
   B.fcon_ptr[0] = 0;
   for (int64_t f = 0; f < fr0[nm]; ++f) B.fcon_ptr[f + 1] = B.fcon_ptr[f] + fcon_cnt[f + 1];
   B.fcon_idx.resize(B.fcon_ptr[fr0[nm]]);
   {
     std::vector<int32_t> fill(B.fcon_ptr.begin(), B.fcon_ptr.end() - 1);
-    for (int i = 0; i < nm; ++i)
-      for (auto& e : fcon_m[i]) B.fcon_idx[fill[e.first]++] = e.second;
+#pragma omp parallel for schedule(dynamic, 1)
+    for (int i = 0; i < nm; ++i) {
+      const Symbolic& S = *Ss[i];
+      for (int32_t c = 0; c < S.nsn; ++c)
+        if (S.sn_parent[c] >= 0)
+          for (int64_t a = S.sn_rptr[c]; a < S.sn_rptr[c + 1]; ++a)
+            B.fcon_idx[fill[fcon_m[i][a]]++] = (int32_t)(u0[i] + a);
+    }
   }
   // the same lists as index pairs (one load for the common rows)
   B.fcon2.assign(2 * (size_t)std::max<int64_t>(fr0[nm], 1), -1);
@@ -928,35 +943,46 @@ uint64_t spread3(uint64_t v) {
 // together in time then share the cache lines of x they gather.
 std::vector<int32_t> morton_rows(const Discretization& D) {
   const int64_t n = D.n;
-  std::vector<double> xyz(3 * n);
-  for (int64_t v = 0; v < D.nv; ++v)
-    for (int d = 0; d < 3; ++d) xyz[3 * v + d] = D.xyz[3 * v + d];
-  for (int64_t e = 0; e < n - D.nv; ++e)
-    for (int d = 0; d < 3; ++d)
-      xyz[3 * (D.nv + e) + d] = 0.5 * (D.xyz[3 * D.edges[2 * e] + d] + D.xyz[3 * D.edges[2 * e + 1] + d]);
   double lo[3], hi[3];
   for (int d = 0; d < 3; ++d) {
     lo[d] = 1e300;
     hi[d] = -1e300;
   }
-  for (int64_t i = 0; i < n; ++i)
+  // edge midpoints lie between the vertices
+  for (int64_t v = 0; v < D.nv; ++v)
     for (int d = 0; d < 3; ++d) {
-      lo[d] = std::min(lo[d], xyz[3 * i + d]);
-      hi[d] = std::max(hi[d], xyz[3 * i + d]);
+      lo[d] = std::min(lo[d], D.xyz[3 * v + d]);
+      hi[d] = std::max(hi[d], D.xyz[3 * v + d]);
     }
   // one scale for all axes keeps the curve's cells cubic
   double ext = 0;
   for (int d = 0; d < 3; ++d) ext = std::max(ext, hi[d] - lo[d]);
   const double sc = ext > 0 ? 2097151.0 / ext : 0.0;
-  std::vector<std::pair<uint64_t, int32_t>> key(n);
-  for (int64_t i = 0; i < n; ++i) {
-    uint64_t k = 0;
-    for (int d = 0; d < 3; ++d) k |= spread3((uint64_t)((xyz[3 * i + d] - lo[d]) * sc)) << d;
-    key[i] = {k, (int32_t)i};
+  struct Key {
+    uint64_t k;
+    int32_t i;
+    bool operator<(const Key& o) const { return k != o.k ? k < o.k : i < o.i; }
+  };
+  RawVec<Key> key(n);
+  // pieces sorted by themselves, then merged pairwise
+  constexpr int kPieces = 16;
+  auto at = [&](int64_t q) { return key.begin() + std::min<int64_t>(q, kPieces) * n / kPieces; };
+#pragma omp parallel for schedule(dynamic, 1)
+  for (int q = 0; q < kPieces; ++q) {
+    for (int64_t i = at(q) - key.begin(); i < at(q + 1) - key.begin(); ++i) {
+      double x[3];
+      D.dof_coord(i, x);
+      uint64_t k = 0;
+      for (int d = 0; d < 3; ++d) k |= spread3((uint64_t)((x[d] - lo[d]) * sc)) << d;
+      key[i] = {k, (int32_t)i};
+    }
+    std::sort(at(q), at(q + 1));
   }
-  std::sort(key.begin(), key.end());
+  for (int w = 1; w < kPieces; w *= 2)
+#pragma omp parallel for schedule(dynamic, 1)
+    for (int q = 0; q < kPieces; q += 2 * w) std::inplace_merge(at(q), at(q + w), at(q + 2 * w));
   std::vector<int32_t> order(n);
-  for (int64_t i = 0; i < n; ++i) order[i] = key[i].second;
+  for (int64_t i = 0; i < n; ++i) order[i] = key[i].i;
   return order;
 }
 
@@ -968,6 +994,7 @@ void build_sell(Ctx& c, const std::vector<int32_t>& order) {
   const int64_t n = A.n;
   const int64_t ns = (n + 63) / 64;
   std::vector<int32_t> perm(ns * 64, 0);
+#pragma omp parallel for schedule(static)
   for (int64_t w0 = 0; w0 < n; w0 += 1024) {
     const int64_t w1 = std::min<int64_t>(n, w0 + 1024);
     std::vector<int32_t> r(order.begin() + w0, order.begin() + w1);
@@ -985,15 +1012,16 @@ void build_sell(Ctx& c, const std::vector<int32_t>& order) {
     swidth[s] = wd;
     soff[s + 1] = soff[s] + 64 * (int64_t)wd;
   }
-  std::vector<int32_t> scol(soff[ns], 0);
-  std::vector<cplx> sval(soff[ns], cplx(0, 0));
+  RawVec<int32_t> scol(soff[ns]);
+  RawVec<cplx> sval(soff[ns]);
 #pragma omp parallel for schedule(static)
   for (int64_t s = 0; s < ns; ++s)
-    for (int64_t q = s * 64; q < std::min<int64_t>(n, s * 64 + 64); ++q) {
-      const int64_t row = perm[q], lane = q - s * 64;
+    for (int64_t q = s * 64; q < s * 64 + 64; ++q) {
+      // lanes past the last row hold zero entries of row 0
+      const int64_t row = q < n ? perm[q] : 0, lane = q - s * 64, len = q < n ? A.ptr[row + 1] - A.ptr[row] : 0;
       for (int64_t j = 0; j < swidth[s]; ++j) {
         const int64_t p = A.ptr[row] + j;
-        const bool real = p < A.ptr[row + 1];
+        const bool real = j < len;
         scol[soff[s] + j * 64 + lane] = real ? A.col[p] : (int32_t)row;
         sval[soff[s] + j * 64 + lane] = real ? A.val[p] : cplx(0, 0);
       }
@@ -1016,21 +1044,27 @@ void upload_matrix(Ctx& c) {
   c.A_val.upload(reinterpret_cast<const double*>(A.val.data()), 2 * A.val.size());
   {
     std::vector<int64_t> sp(n + 1, 0);
-    std::vector<int32_t> sc;
-    std::vector<double> sv;
-    sc.reserve(A.nnz());
-    sv.reserve(A.nnz());
+#pragma omp parallel for schedule(static)
     for (int64_t i = 0; i < n; ++i) {
+      int64_t len = A.ptr[i + 1] - A.ptr[i];
+      for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) len += A.val[p].imag() != 0.0;
+      sp[i + 1] = len;
+    }
+    for (int64_t i = 0; i < n; ++i) sp[i + 1] += sp[i];
+    RawVec<int32_t> sc(sp[n]);
+    RawVec<double> sv(sp[n]);
+#pragma omp parallel for schedule(static)
+    for (int64_t i = 0; i < n; ++i) {
+      int64_t q = sp[i];
       for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) {
-        sc.push_back(A.col[p]);
-        sv.push_back(A.val[p].real());
+        sc[q] = A.col[p];
+        sv[q++] = A.val[p].real();
       }
       for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p)
         if (A.val[p].imag() != 0.0) {
-          sc.push_back((int32_t)((uint32_t)A.col[p] | 0x80000000u));
-          sv.push_back(A.val[p].imag());
+          sc[q] = (int32_t)((uint32_t)A.col[p] | 0x80000000u);
+          sv[q++] = A.val[p].imag();
         }
-      sp[i + 1] = (int64_t)sc.size();
     }
     c.S_ptr.upload(sp);
     c.S_col.upload(sc);
@@ -1342,6 +1376,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
       // Z with columns renumbered to the coarse solve's output positions
       CsrReal Zp = c.Z;
       for (auto& col : Zp.col) col = c.Esym.iperm[col];
+#pragma omp parallel for schedule(static)
       for (int64_t i = 0; i < Zp.n; ++i) {
         std::vector<std::pair<int32_t, double>> e;
         for (int64_t p = Zp.ptr[i]; p < Zp.ptr[i + 1]; ++p) e.push_back({Zp.col[p], Zp.val[p]});
