@@ -1258,13 +1258,9 @@ __global__ __launch_bounds__(kWG) void gs_update_rows_kernel(int64_t n, PtrSetC 
 // h_j = (t_j - s^H t_{<j}) / a; cw_k = t_k - s_k h_j / a (k < j),
 // cw_j = h_j / a; cv_k = s_k, cv_j = 1 / a.  out (host-bound) gets
 // [t_0 .. t_{j-1}, h_j, (slot for |w|), s_0 .. s_{j-1}, a].  ncol <= 64.
-__global__ __launch_bounds__(64) void dcgs2_coef_kernel(PtrSetC dots_, int ncol, PtrSet cws, PtrSet cvs,
-                                                         PtrSet outs) {
-  const double2* __restrict__ t = reinterpret_cast<const double2*>(dots_.p[blockIdx.y]);
-  const double2* __restrict__ g = t + ncol;
-  double2* __restrict__ cw = reinterpret_cast<double2*>(cws.p[blockIdx.y]);
-  double2* __restrict__ cv = reinterpret_cast<double2*>(cvs.p[blockIdx.y]);
-  double2* __restrict__ out = reinterpret_cast<double2*>(outs.p[blockIdx.y]);
+__device__ __forceinline__ void dcgs2_coefs(const double2* t, int ncol, double2* __restrict__ cw,
+                                            double2* __restrict__ cv, double2* __restrict__ out) {
+  const double2* g = t + ncol;
   const int j = ncol - 1, k = threadIdx.x;  // one wave, lane k < j owns column k
   const double2 gk = k < j ? g[k] : make_double2(0.0, 0.0);
   const double2 tk = k < j ? t[k] : make_double2(0.0, 0.0);
@@ -1294,6 +1290,60 @@ __global__ __launch_bounds__(64) void dcgs2_coef_kernel(PtrSetC dots_, int ncol,
     out[j] = make_double2(hr, hi);
     out[2 * j + 2] = make_double2(a, 0.0);
   }
+}
+
+__global__ __launch_bounds__(64) void dcgs2_coef_kernel(PtrSetC dots, int ncol, PtrSet cws, PtrSet cvs, PtrSet outs) {
+  const int r = blockIdx.y;
+  dcgs2_coefs(reinterpret_cast<const double2*>(dots.p[r]), ncol, reinterpret_cast<double2*>(cws.p[r]),
+              reinterpret_cast<double2*>(cvs.p[r]), reinterpret_cast<double2*>(outs.p[r]));
+}
+
+// The sum a workgroup of kWG threads takes over nblk <= kWG partials (thread t
+// holds partial t, the threads add pairwise), on one wave: lane l stands for
+// threads l, l + 64, l + 128, l + 192 and holds their partials a; lane 0's
+// result.
+__device__ __forceinline__ double wave_sum(const double* a) {
+  static_assert(kWG == 256, "four threads per lane");
+  double v = (a[0] + a[2]) + (a[1] + a[3]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  return v;
+}
+
+// Reduction of the pass-A dots (nblk <= kWG partials) and the coefficients in
+// one launch: a workgroup per right-hand side, its 16 waves taking four columns
+// at a time.  Same sums, in the same order, as gs_dots_final_kernel.  Dependent
+// launches of this size take 4.5 us each; with norm_scale_kernel two fewer per
+// step: 110 -> 108 us per step at 4,913 unknowns, 238 -> 232 for eight
+// right-hand sides.  Above kWG partials (16,384 unknowns) one workgroup reads
+// them slower than the columns' workgroups do (37,485 unknowns, eight right-hand
+// sides: 499 us fused, 494 not).
+__global__ __launch_bounds__(1024) void dcgs2_final_kernel(PtrSetC parts, int nblk, int ncol, PtrSet cws, PtrSet cvs,
+                                                           PtrSet outs) {
+  __shared__ double2 t[2 * kGsMaxCols];
+  const int r = blockIdx.y, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const double2* __restrict__ partial = reinterpret_cast<const double2*>(parts.p[r]);
+  for (int k0 = wv; k0 < 2 * ncol; k0 += 64) {
+    double2 v[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = k0 + 16 * u, b = lane + 64 * q;
+        v[u][q] = k < 2 * ncol && b < nblk ? partial[(int64_t)b * 2 * ncol + k] : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const double re[4] = {v[u][0].x, v[u][1].x, v[u][2].x, v[u][3].x};
+      const double im[4] = {v[u][0].y, v[u][1].y, v[u][2].y, v[u][3].y};
+      const double2 sum = make_double2(wave_sum(re), wave_sum(im));
+      if (lane == 0 && k0 + 16 * u < 2 * ncol) t[k0 + 16 * u] = sum;
+    }
+  }
+  __syncthreads();
+  if (wv == 0)
+    dcgs2_coefs(t, ncol, reinterpret_cast<double2*>(cws.p[r]), reinterpret_cast<double2*>(cvs.p[r]),
+                reinterpret_cast<double2*>(outs.p[r]));
 }
 
 __global__ __launch_bounds__(kWG) void norm_final2_kernel(PtrSetC parts, int nblk, PtrSet outs) {
@@ -1353,6 +1403,35 @@ __global__ __launch_bounds__(kWG) void scale_by_inv_kernel(int64_t n, PtrSetC ws
   const double inv = d != 0.0 ? 1.0 / d : 0.0;
   const double2 a = w[i];
   v[i] = make_double2(a.x * inv, a.y * inv);
+}
+
+// norm_final2_kernel and scale_by_inv_kernel in one launch: every wave reduces
+// the nblk <= kWG partials itself (the same sum), wave 0 of right-hand side r also
+// stores the norm and, with a host buffer, copies the step's nout
+// Hessenberg entries (the norm at entry inorm) there.
+__global__ __launch_bounds__(kWG) void norm_scale_kernel(int64_t n, PtrSetC ws, PtrSetC parts, int nblk, PtrSet nrms,
+                                                         PtrSet vs, const double2* __restrict__ hcol, int nout,
+                                                         int inorm, double2* __restrict__ host) {
+  const int r = blockIdx.y;
+  const double2* __restrict__ w = reinterpret_cast<const double2*>(ws.p[r]);
+  const double2* __restrict__ partial = reinterpret_cast<const double2*>(parts.p[r]);
+  const int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x;
+  const double2 a = w[min(i, n - 1)];
+  double p[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int b = (threadIdx.x & 63) + 64 * q;
+    p[q] = b < nblk ? partial[b].x : 0.0;
+  }
+  const double d = sqrt(__shfl(wave_sum(p), 0, 64));
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    const double2 nv = make_double2(d, 0.0);
+    if (threadIdx.x == 0) reinterpret_cast<double2*>(nrms.p[r])[0] = nv;
+    if (host)
+      for (int e = threadIdx.x; e < nout; e += 64) host[e] = e == inorm ? nv : hcol[e];
+  }
+  const double inv = d != 0.0 ? 1.0 / d : 0.0;
+  if (i < n) reinterpret_cast<double2*>(vs.p[r])[i] = make_double2(a.x * inv, a.y * inv);
 }
 
 __global__ __launch_bounds__(kWG) void scale_kernel(int64_t n, const double2* __restrict__ w, double alpha,
@@ -1656,22 +1735,37 @@ void gs_dual(bool update, int nr, int64_t n, const PtrSetC& V, const PtrSet& Vw,
   else
     gs_dots_kernel<kGsMaxCols / 4><<<grid, kWG, lds, s>>>(n, V, ld, ncol, w, partial);
 }
-void dcgs2_coef(int nr, const PtrSetC& dots, int ncol, const PtrSet& cw, const PtrSet& cv, const PtrSet& out,
-                hipStream_t s) {
-  dcgs2_coef_kernel<<<dim3(1, (unsigned)nr), 64, 0, s>>>(dots, ncol, cw, cv, out);
+void dcgs2_coef(int nr, const PtrSetC& partial, int nblk, int ncol, const PtrSet& dots, const PtrSet& cw,
+                const PtrSet& cv, const PtrSet& out, hipStream_t s) {
+  if (nblk <= kWG) {
+    dcgs2_final_kernel<<<dim3(1, (unsigned)nr), 1024, 0, s>>>(partial, nblk, ncol, cw, cv, out);
+    return;
+  }
+  gs_final(nr, partial, nblk, 2 * ncol, dots, PtrSet{}, 0, s);
+  PtrSetC d{};
+  for (int r = 0; r < nr; ++r) d.p[r] = dots.p[r];
+  dcgs2_coef_kernel<<<dim3(1, (unsigned)nr), 64, 0, s>>>(d, ncol, cw, cv, out);
 }
-void norm_final(int nr, const PtrSetC& partial, int nblk, const PtrSet& out, hipStream_t s) {
-  norm_final2_kernel<<<dim3(1, (unsigned)nr), kWG, 0, s>>>(partial, nblk, out);
+
+bool norm_scale(int nr, int64_t n, const PtrSetC& w, const PtrSetC& partial, int nblk, const PtrSet& nrm,
+                const PtrSet& v, const double* hcol, int nout, int inorm, double* host, hipStream_t s) {
+  if (n <= 0) return false;
+  if (nblk <= kWG) {
+    norm_scale_kernel<<<dim3(blocks_for(n), (unsigned)nr), kWG, 0, s>>>(
+        n, w, partial, nblk, nrm, v, reinterpret_cast<const double2*>(hcol), nout, inorm,
+        reinterpret_cast<double2*>(host));
+    return host != nullptr;
+  }
+  norm_final2_kernel<<<dim3(1, (unsigned)nr), kWG, 0, s>>>(partial, nblk, nrm);
+  PtrSetC d{};
+  for (int r = 0; r < nr; ++r) d.p[r] = nrm.p[r];
+  scale_by_inv_kernel<<<dim3(blocks_for(n), (unsigned)nr), kWG, 0, s>>>(n, w, d, v);
+  return false;
 }
 
 void norm2(int64_t n, const double* w, double* partial, int nblk, double* out, hipStream_t s) {
   norm_partial_kernel<<<(unsigned)nblk, kWG, 0, s>>>(n, reinterpret_cast<const double2*>(w), partial);
   norm_final_kernel<<<1, kWG, 0, s>>>(partial, nblk, reinterpret_cast<double2*>(out));
-}
-
-void scale_by_inv_set(int nr, int64_t n, const PtrSetC& w, const PtrSetC& nrm, const PtrSet& v, hipStream_t s) {
-  if (n <= 0) return;
-  scale_by_inv_kernel<<<dim3(blocks_for(n), (unsigned)nr), kWG, 0, s>>>(n, w, nrm, v);
 }
 
 void scale(int64_t n, const double* w, double alpha, double* v, hipStream_t s) {

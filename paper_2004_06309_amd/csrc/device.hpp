@@ -245,26 +245,28 @@ int gs_blocks(int64_t n);
 // right-hand side, ncol <= 64), for nr right-hand sides at once (entry r of
 // each pointer set belongs to right-hand side r):
 // mode 0: partial dots V^H w; mode 1: w -= V h then partial dots of the new
-// w; mode 2: w -= V h then partial squared norms (reduce with norm_final).
+// w; mode 2: w -= V h then partial squared norms (for norm_scale).
 int gs_tiles(int64_t n);
 void gs_pass(int mode, int nr, int64_t n, const PtrSetC& V, int64_t ld, int ncol, const PtrSetC& h, const PtrSet& w,
              const PtrSet& partial, hipStream_t s);
 // h[k] = sum_b partial[b*ncol + k]; hacc[k] = (or +=) h[k], per right-hand side
 void gs_final(int nr, const PtrSetC& partial, int nblk, int ncol, const PtrSet& h, const PtrSet& hacc,
               int accumulate, hipStream_t s);
-void norm_final(int nr, const PtrSetC& partial, int nblk, const PtrSet& out, hipStream_t s);
 // Delayed CGS2 passes over ncol = j + 1 columns of V (see device.hip):
 // update = false: partial dots V^H w and V^H v_j (2 ncol per tile, reduce
-// with gs_final over 2 ncol); update = true: v_j and w updated with the
+// with dcgs2_coef); update = true: v_j and w updated with the
 // coefficients cw, cv (written to column j through Vw), partial |w|^2.
 void gs_dual(bool update, int nr, int64_t n, const PtrSetC& V, const PtrSet& Vw, int64_t ld, int ncol,
              const PtrSetC& cw, const PtrSetC& cv, const PtrSet& w, const PtrSet& partial, hipStream_t s);
-// Pass-B coefficients and the host-bound Hessenberg data from the reduced
-// pass-A dots (2 ncol entries per right-hand side); one wave per RHS.
-void dcgs2_coef(int nr, const PtrSetC& dots, int ncol, const PtrSet& cw, const PtrSet& cv, const PtrSet& out,
-                hipStream_t s);
-// v = w / nrm[0] per right-hand side
-void scale_by_inv_set(int nr, int64_t n, const PtrSetC& w, const PtrSetC& nrm, const PtrSet& v, hipStream_t s);
+// Pass-B coefficients and the host-bound Hessenberg data from the pass-A
+// partials of nblk tiles (dots: scratch of 2 ncol entries per right-hand side).
+void dcgs2_coef(int nr, const PtrSetC& partial, int nblk, int ncol, const PtrSet& dots, const PtrSet& cw,
+                const PtrSet& cv, const PtrSet& out, hipStream_t s);
+// nrm[0] = |w| from the partials of nblk tiles, v = w / |w|, per right-hand
+// side.  host (pinned, nr = 1, or null) gets the nout complex entries of hcol,
+// of which entry inorm is nrm, if the call returns true.
+bool norm_scale(int nr, int64_t n, const PtrSetC& w, const PtrSetC& partial, int nblk, const PtrSet& nrm,
+                const PtrSet& v, const double* hcol, int nout, int inorm, double* host, hipStream_t s);
 
 // ---- block (multi-right-hand-side) operations, S in {2, 4, 8, 16},
 //      interleaved n x S vectors (device_block.hip) ----

@@ -1716,8 +1716,8 @@ void dual_pass_a(Ctx& c, int ncol, hipStream_t s) {
   const int64_t n = c.D.n;
   dev::gs_dual(false, 1, n, csetc(c.V.p), pset(c.V.p), n, ncol, csetc(c.coef_w.p), csetc(c.coef_v.p), pset(c.w.p),
                pset(c.partial.p), s);
-  dev::gs_final(1, csetc(c.partial.p), dev::gs_tiles(n), 2 * ncol, pset(c.htmp.p), dev::PtrSet{}, 0, s);
-  dev::dcgs2_coef(1, csetc(c.htmp.p), ncol, pset(c.coef_w.p), pset(c.coef_v.p), pset(c.hcol.p), s);
+  dev::dcgs2_coef(1, csetc(c.partial.p), dev::gs_tiles(n), ncol, pset(c.htmp.p), pset(c.coef_w.p), pset(c.coef_v.p),
+                  pset(c.hcol.p), s);
 }
 
 // Column j of H (unrotated) finished with the second-pass data of v_{j+1}:
@@ -1728,6 +1728,14 @@ void finish_column(cplx* h, int j, const double* sv, double alpha) {
   for (int k = 0; k <= j; ++k) h[k] += h[j + 1] * cplx(sv[2 * k], sv[2 * k + 1]);
   h[j + 1] *= alpha;
 }
+
+// One-level operators up to this many factor entries apply the next step's
+// preconditioner while the host decides about the present one (4,913 unknowns,
+// 1.4e6 entries: 108 -> 101 us per step; 9,889, 3.9e6: 133 -> 128).  The
+// application a cycle's end wastes takes as long as the gaps of about 15 steps
+// at the line.  With a coarse stage the gap is covered already (37,485
+// unknowns: 263 and 261-269 us).
+constexpr int64_t kAheadEntries = 10000000;
 
 int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int maxit, bool x0, bool dcgs2,
                  double* U, hipStream_t s, helm_solve_info* info) {
@@ -1772,10 +1780,11 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
       g[0] = beta;
       int k = 0;
       precond_stage1(c, V, s);
+      bool ahead = false;  // Zk_jj is enqueued already
       for (int jj = 0; jj < m; ++jj) {
         double* vj = V + 2 * (size_t)n * jj;
         double* zj = Zk + 2 * (size_t)n * jj;
-        precond_stage2(c, vj, zj, s);
+        if (!ahead) precond_stage2(c, vj, zj, s);
         apply_A(c, zj, c.w.p, s);
         const bool prof = c.prof.on;
         if (prof) c.prof.begin(s);
@@ -1794,7 +1803,6 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
           // w orthogonalised, |w|^2
           dual_pass_a(c, jj + 1, s);
           dev::gs_dual(true, 1, n, Vs, pset(V), n, jj + 1, csetc(c.coef_w.p), csetc(c.coef_v.p), ws, pw, s);
-          dev::norm_final(1, ps, nt, nrm, s);
           nout = 2 * jj + 3;
         } else {
           // CGS2: dots | update + dots | update + norm, each one pass over V
@@ -1808,17 +1816,25 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
           dev::gs_pass(1, 1, n, Vs, n, jj + 1, hs, ws, pw, s);
           dev::gs_final(1, ps, nt, jj + 1, hts, hcs, 1, s);
           dev::gs_pass(2, 1, n, Vs, n, jj + 1, hs, ws, pw, s);
-          dev::norm_final(1, ps, nt, nrm, s);
           nout = jj + 2;
         }
-        dev::scale_by_inv_set(1, n, csetc(c.w.p), csetc(nrm.p[0]), vn, s);
+        const bool sent =
+            dev::norm_scale(1, n, csetc(c.w.p), ps, nt, nrm, vn, c.hcol.p, nout, jj + 1, c.h_host, s);
         if (prof)
           c.prof.end(HELM_K_GS, 16.0 * n * (dcgs2 ? 2.0 * (jj + 1) + 6.0 : 3.0 * (jj + 1) + 7.0), s);
-        HELM_HIP(hipMemcpyAsync(c.h_host, c.hcol.p, 2 * sizeof(double) * nout, hipMemcpyDeviceToHost, s));
+        if (!sent)
+          HELM_HIP(hipMemcpyAsync(c.h_host, c.hcol.p, 2 * sizeof(double) * nout, hipMemcpyDeviceToHost, s));
         HELM_HIP(hipEventRecord(c.hev, s));
         // the next step's coarse stage runs while the host updates the
-        // least-squares problem (wasted only when this step ends the cycle)
-        if (jj + 1 < m && its + 1 < maxit) precond_stage1(c, V + 2 * (size_t)n * (jj + 1), s);
+        // least-squares problem (wasted only when this step ends the cycle), or
+        // the whole of a small one-level preconditioner
+        ahead = false;
+        if (jj + 1 < m && its + 1 < maxit) {
+          const double* vnext = V + 2 * (size_t)n * (jj + 1);
+          precond_stage1(c, vnext, s);
+          ahead = !prof && !c.two_level && c.stats.factor_entries <= kAheadEntries;
+          if (ahead) precond_stage2(c, vnext, Zk + 2 * (size_t)n * (jj + 1), s);
+        }
         HELM_HIP(hipEventSynchronize(c.hev));
         ++its;
         for (int i = 0; i < 2 * nout; ++i)
@@ -2228,7 +2244,7 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
       // Gram-Schmidt over the active right-hand sides (slot q holds act[q])
       if (prof) c.prof.begin(s);
       const size_t ld = blk_ld(m);
-      dev::PtrSetC Vs{}, hs{}, ps{}, wc{}, nc{}, cwc{}, cvc{};
+      dev::PtrSetC Vs{}, hs{}, ps{}, wc{}, cwc{}, cvc{};
       dev::PtrSet Vw{}, ws{}, hts{}, hcs{}, pw{}, nrm{}, vn{}, cwp{}, cvp{};
       for (int q = 0; q < na; ++q) {
         const int r = act[q];
@@ -2242,7 +2258,6 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
         ws.p[q] = c.bw[r].p;
         wc.p[q] = c.bw[r].p;
         nrm.p[q] = hcs.p[q] + 2 * (jj + 1);
-        nc.p[q] = nrm.p[q];
         vn.p[q] = c.bV[r].p + n2 * (jj + 1);
         cwp.p[q] = c.bcoef_w.p + 2 * (size_t)q * (m + 2);
         cvp.p[q] = c.bcoef_v.p + 2 * (size_t)q * (m + 2);
@@ -2253,10 +2268,8 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
       if (dcgs2) {
         // delayed CGS2: dual dots | coefficients | v_j finished, w orthogonalised
         dev::gs_dual(false, na, n, Vs, Vw, n, jj + 1, cwc, cvc, ws, pw, s);
-        dev::gs_final(na, ps, nt, 2 * (jj + 1), hts, dev::PtrSet{}, 0, s);
-        dev::dcgs2_coef(na, hs, jj + 1, cwp, cvp, hcs, s);
+        dev::dcgs2_coef(na, ps, nt, jj + 1, hts, cwp, cvp, hcs, s);
         dev::gs_dual(true, na, n, Vs, Vw, n, jj + 1, cwc, cvc, ws, pw, s);
-        dev::norm_final(na, ps, nt, nrm, s);
         nout = 2 * jj + 3;
       } else {
         dev::gs_pass(0, na, n, Vs, n, jj + 1, hs, ws, pw, s);
@@ -2264,10 +2277,9 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
         dev::gs_pass(1, na, n, Vs, n, jj + 1, hs, ws, pw, s);
         dev::gs_final(na, ps, nt, jj + 1, hts, hcs, 1, s);
         dev::gs_pass(2, na, n, Vs, n, jj + 1, hs, ws, pw, s);
-        dev::norm_final(na, ps, nt, nrm, s);
         nout = jj + 2;
       }
-      dev::scale_by_inv_set(na, n, wc, nc, vn, s);
+      dev::norm_scale(na, n, wc, ps, nt, nrm, vn, nullptr, 0, 0, nullptr, s);
       if (prof)
         c.prof.end(HELM_K_GS, na * 16.0 * n * (dcgs2 ? 2.0 * (jj + 1) + 6.0 : 3.0 * (jj + 1) + 7.0), s);
       HELM_HIP(hipMemcpyAsync(c.bh_host, c.bhcol.p, 2 * sizeof(double) * na * ld, hipMemcpyDeviceToHost, s));
@@ -2331,8 +2343,7 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
           cve.p[e] = cvc.p[q];
         }
         dev::gs_dual(false, ne, n, Ve, Vwe, n, jj + 2, cwe, cve, we, pwe, s);
-        dev::gs_final(ne, pe, nt, 2 * (jj + 2), hte, dev::PtrSet{}, 0, s);
-        dev::dcgs2_coef(ne, he, jj + 2, cwpe, cvpe, hce, s);
+        dev::dcgs2_coef(ne, pe, nt, jj + 2, hte, cwpe, cvpe, hce, s);
         HELM_HIP(hipMemcpyAsync(c.bh_host, c.bhcol.p, 2 * sizeof(double) * na * ld, hipMemcpyDeviceToHost, s));
         HELM_HIP(hipStreamSynchronize(s));
         for (int e = 0; e < ne; ++e) {
@@ -2994,7 +3005,7 @@ int Server::launch() {
   for (size_t a = 0; a < act.size(); ++a) {
     if (done[a]) continue;
     const int jj = slot[act[a]].jj;
-    dev::PtrSetC Vs{}, hs{}, ps{}, wc{}, nc{}, cwc{}, cvc{};
+    dev::PtrSetC Vs{}, hs{}, ps{}, wc{}, cwc{}, cvc{};
     dev::PtrSet Vw{}, ws{}, hts{}, hcs{}, pw{}, nrm{}, vn{}, cwp{}, cvp{};
     int na = 0;
     for (size_t b2 = a; b2 < act.size(); ++b2) {
@@ -3015,14 +3026,12 @@ int Server::launch() {
       ws.p[na] = c.bw[q].p;
       wc.p[na] = c.bw[q].p;
       nrm.p[na] = hcs.p[na] + 2 * (jj + 1);
-      nc.p[na] = nrm.p[na];
       vn.p[na] = c.bV[q].p + n2 * (jj + 1);
       ++na;
     }
     if (dcgs2) {
       dev::gs_dual(false, na, n, Vs, Vw, n, jj + 1, cwc, cvc, ws, pw, s);
-      dev::gs_final(na, ps, nt, 2 * (jj + 1), hts, dev::PtrSet{}, 0, s);
-      dev::dcgs2_coef(na, hs, jj + 1, cwp, cvp, hcs, s);
+      dev::dcgs2_coef(na, ps, nt, jj + 1, hts, cwp, cvp, hcs, s);
       dev::gs_dual(true, na, n, Vs, Vw, n, jj + 1, cwc, cvc, ws, pw, s);
     } else {
       dev::gs_pass(0, na, n, Vs, n, jj + 1, hs, ws, pw, s);
@@ -3031,8 +3040,7 @@ int Server::launch() {
       dev::gs_final(na, ps, nt, jj + 1, hts, hcs, 1, s);
       dev::gs_pass(2, na, n, Vs, n, jj + 1, hs, ws, pw, s);
     }
-    dev::norm_final(na, ps, nt, nrm, s);
-    dev::scale_by_inv_set(na, n, wc, nc, vn, s);
+    dev::norm_scale(na, n, wc, ps, nt, nrm, vn, nullptr, 0, 0, nullptr, s);
   }
   HELM_HIP(hipMemcpyAsync(c.bh_host, c.bhcol.p, 2 * sizeof(double) * slots_n * blk_ld(m), hipMemcpyDeviceToHost, s));
   HELM_HIP(hipEventRecord(done_ev, s));
@@ -3130,8 +3138,7 @@ void Server::finish(std::vector<helm_server_event>& out) {
         ++na;
       }
       dev::gs_dual(false, na, n, Vs, Vw, n, jj + 2, cwc, cvc, ws, pw, s);
-      dev::gs_final(na, ps, nt, 2 * (jj + 2), hts, dev::PtrSet{}, 0, s);
-      dev::dcgs2_coef(na, hs, jj + 2, cwp, cvp, hcs, s);
+      dev::dcgs2_coef(na, ps, nt, jj + 2, hts, cwp, cvp, hcs, s);
     }
     if (!ending.empty()) {
       HELM_HIP(hipMemcpyAsync(c.bh_host, c.bhcol.p, 2 * sizeof(double) * slots_n * blk_ld(m), hipMemcpyDeviceToHost,
