@@ -32,10 +32,10 @@ __device__ __forceinline__ dv4 mma(double a, double b, dv4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// bgs_dots streams the basis once per pass: non-temporal loads (a plain read of
-// 8 GB reaches 6.3 TB/s on this card, a non-temporal one 7.2; all Gram-Schmidt of
-// 49 block steps at one million unknowns 301 -> 293 ms).  Not in bgs_mul, whose
-// loads take half a cache line at a time and find the other half again (321 ms).
+// The basis is streamed once per pass: non-temporal loads of whole lines (a plain
+// read of 8 GB reaches 6.3 TB/s on this card, a non-temporal one 7.2).  All
+// Gram-Schmidt of 49 block steps at one million unknowns: 301 ms at first, 293 so
+// in bgs_dots, 284 in bgs_mul too, 278 with more loads in flight in bgs_reduce.
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ double2 ldnt(const double2* p) {
   const dvec2 v = __builtin_nontemporal_load(reinterpret_cast<const dvec2*>(p));
@@ -162,19 +162,17 @@ __global__ __launch_bounds__(256) void bgs_reduce_kernel(const double2* __restri
   double sr = 0, si = 0;
   if (e < ne) {
     int wg = u;
-    for (; wg + 3 * kRedT < nwg; wg += 4 * kRedT) {
-      const double2 p0 = partial[(int64_t)wg * ne + e];
-      const double2 p1 = partial[(int64_t)(wg + kRedT) * ne + e];
-      const double2 p2 = partial[(int64_t)(wg + 2 * kRedT) * ne + e];
-      const double2 p3 = partial[(int64_t)(wg + 3 * kRedT) * ne + e];
-      sr += p0.x;
-      si += p0.y;
-      sr += p1.x;
-      si += p1.y;
-      sr += p2.x;
-      si += p2.y;
-      sr += p3.x;
-      si += p3.y;
+    // 16 loads in flight, added in order (four: 5.4 ms more in 49 block steps at
+    // one million unknowns)
+    for (; wg + 15 * kRedT < nwg; wg += 16 * kRedT) {
+      double2 p[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) p[k] = partial[(int64_t)(wg + k * kRedT) * ne + e];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        sr += p[k].x;
+        si += p[k].y;
+      }
     }
     for (; wg < nwg; wg += kRedT) {
       const double2 p = partial[(int64_t)wg * ne + e];
@@ -208,14 +206,18 @@ constexpr int kMulTiles = 2;  // 16-row tiles per wave in bgs_mul
 // C + 256 jb (16 x 16, entry (a, c) at a * 16 + c); with gram, the
 // workgroup's partial sum of Y^H Y goes to gram[blockIdx.x * 256 + ...].
 // Y may alias Y0 and X (each wave reads its own rows before it writes them;
-// rows past n, never stored, read row n - 1).  The operands of block jb + 1
-// are loaded, into the other of two register sets, before the MFMAs of
-// block jb; a step past nb meets zero coefficients.
+// rows past n, never stored, read row n - 1).  The rows of block jb + 1 are
+// loaded right after those of block jb have gone to LDS, before its MFMAs.
+// Bound by reading X: the MFMA operands straight from memory took half a
+// cache line per row and load (no room for non-temporal loads, 321 ms in the
+// measure above), whole rows turned in LDS 284.
 __global__ __launch_bounds__(64 * kWaves, 3) void bgs_mul_kernel(int64_t n, const double2* X, int64_t ldx,
                                                                   int nb, const double2* __restrict__ C, double sign,
                                                                   const double2* Y0, double2* Y,
                                                                   double2* __restrict__ gram) {
-  __shared__ double2 red[kWaves][256];
+  // a wave's rows of X, 17 entries apart (free of bank conflicts); reused for
+  // the Gram sums
+  __shared__ double2 xs[kWaves][kMulTiles][16][17];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rk = lane >> 4, col = lane & 15;
   const int64_t base = ((int64_t)blockIdx.x * kWaves + wv) * kMulTiles * 16;
@@ -238,48 +240,50 @@ __global__ __launch_bounds__(64 * kWaves, 3) void bgs_mul_kernel(int64_t n, cons
       dim[tt][q] = keep != 0.0 ? y[tt][q].y : 0.0;
     }
   if (nb > 0) {
-    // A operand at k-step t: X_jb[row l % 16][column 4 t + l / 16] (the four
-    // lanes of a row read 64 contiguous bytes); B operand: C_jb[4 t + l / 16]
-    // [l % 16]
-    int64_t arow[kMulTiles];
+    // A operand at k-step t: X_jb[row l % 16][column 4 t + l / 16], read from
+    // memory four whole rows at a time and turned in LDS; B operand:
+    // C_jb[4 t + l / 16][l % 16]
+    int64_t arow[kMulTiles][4];
 #pragma unroll
-    for (int tt = 0; tt < kMulTiles; ++tt) arow[tt] = min(base + 16 * tt + col, n - 1) * 16 + rk;
-    auto load = [&](int jb, double2 (&cb)[4], double2 (&a)[kMulTiles][4]) {
-      const int j = min(jb, nb - 1);
+    for (int tt = 0; tt < kMulTiles; ++tt)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) cb[t] = C[j * 256 + (4 * t + rk) * 16 + col];
-      const double2* Xj = X + j * ldx;
+      for (int q = 0; q < 4; ++q) arow[tt][q] = min(base + 16 * tt + 4 * q + rk, n - 1) * 16 + col;
+    double2 a[kMulTiles][4], c[4];
+    auto load = [&](int jb) {
+      const double2* Xj = X + jb * ldx;
 #pragma unroll
       for (int tt = 0; tt < kMulTiles; ++tt)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[tt][t] = Xj[arow[tt] + 4 * t];
+        for (int q = 0; q < 4; ++q) a[tt][q] = ldnt(Xj + arow[tt][q]);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) c[t] = C[jb * 256 + (4 * t + rk) * 16 + col];
     };
-    auto step = [&](int jb, const double2 (&c)[4], const double2 (&a)[kMulTiles][4]) {
-      const bool on = jb < nb;
+    load(0);
+    for (int jb = 0; jb < nb; ++jb) {
+      double2 cb[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) cb[t] = c[t];
+#pragma unroll
+      for (int tt = 0; tt < kMulTiles; ++tt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xs[wv][tt][4 * q + rk][col] = a[tt][q];
+      load(min(jb + 1, nb - 1));
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const double2 cb = on ? c[t] : make_double2(0, 0);
+        double2 v[kMulTiles];
+#pragma unroll
+        for (int tt = 0; tt < kMulTiles; ++tt) v[tt] = xs[wv][tt][col][4 * t + rk];
         // (ar + i ai)(cr + i ci), a scaled by sign
 #pragma unroll
-        for (int tt = 0; tt < kMulTiles; ++tt) dre[tt] = mma(sign * a[tt][t].x, cb.x, dre[tt]);
+        for (int tt = 0; tt < kMulTiles; ++tt) dre[tt] = mma(sign * v[tt].x, cb[t].x, dre[tt]);
 #pragma unroll
-        for (int tt = 0; tt < kMulTiles; ++tt) dim[tt] = mma(sign * a[tt][t].x, cb.y, dim[tt]);
+        for (int tt = 0; tt < kMulTiles; ++tt) dim[tt] = mma(sign * v[tt].x, cb[t].y, dim[tt]);
 #pragma unroll
-        for (int tt = 0; tt < kMulTiles; ++tt) dre[tt] = mma(-sign * a[tt][t].y, cb.y, dre[tt]);
+        for (int tt = 0; tt < kMulTiles; ++tt) dre[tt] = mma(-sign * v[tt].y, cb[t].y, dre[tt]);
 #pragma unroll
-        for (int tt = 0; tt < kMulTiles; ++tt) dim[tt] = mma(sign * a[tt][t].y, cb.x, dim[tt]);
+        for (int tt = 0; tt < kMulTiles; ++tt) dim[tt] = mma(sign * v[tt].y, cb[t].x, dim[tt]);
       }
-    };
-    double2 c0[4], a0[kMulTiles][4], c1[4], a1[kMulTiles][4];
-    load(0, c0, a0);
-    for (int jb = 0; jb < nb; jb += 2) {
-      load(jb + 1, c1, a1);
-      __builtin_amdgcn_sched_barrier(0);
-      step(jb, c0, a0);
-      __builtin_amdgcn_sched_barrier(0);
-      load(jb + 2, c0, a0);
-      __builtin_amdgcn_sched_barrier(0);
-      step(jb + 1, c1, a1);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -306,6 +310,9 @@ __global__ __launch_bounds__(64 * kWaves, 3) void bgs_mul_kernel(int64_t n, cons
     }
   }
   if (gram) {
+    static_assert(sizeof(xs) >= sizeof(double2) * kWaves * 256, "the Gram sums fit");
+    double2 (*red)[256] = reinterpret_cast<double2 (*)[256]>(&xs[0][0][0][0]);
+    __syncthreads();  // every wave is done with its rows
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wv][(4 * r + rk) * 16 + col] = make_double2(gre[r], gim[r]);
     __syncthreads();
