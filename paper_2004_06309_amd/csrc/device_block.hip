@@ -689,7 +689,7 @@ __global__ __launch_bounds__(kWG, 3) void level_small_kernel(const Tile* __restr
   constexpr int split = 4 / NRB, D = 8 / NRB;
   __shared__ double2 G[8 * kWG];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15,
-            lk = lane >> 4, r = lr & 7;
+            r = lr & 7;
   const int c = 2 * r + (lr >> 3);  // component of this lane's MFMA column
   const PT* __restrict__ panels = reinterpret_cast<const PT*>(kFwd ? b.pf : b.pb);
   dv4 d[NRB];
