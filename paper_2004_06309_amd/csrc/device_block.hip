@@ -569,11 +569,36 @@ __global__ __launch_bounds__(kWG, 3) void level_fused_kernel(const Tile* __restr
 // solved together: 37.4 -> 12.2 ms).  Bound by latencies on operators of that
 // size (staging, panel, epilogue), by HBM on large ones.
 //
+// Panel entries through raw buffer loads (range checked in bytes against the
+// buffer's size, out of range reads give zero; non-temporal): the k-step's offset
+// is scalar, a lane's offset constant.  The check is lane offset >= size - scalar
+// offset, so the scalar offset must not pass the size.
+typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, int bytes) {
+  const int64_t a = reinterpret_cast<int64_t>(p);
+  const int lo = __builtin_amdgcn_readfirstlane((int)a), hi = __builtin_amdgcn_readfirstlane((int)(a >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((int64_t)hi << 32) | (uint32_t)lo), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+template <class PT>
+__device__ __forceinline__ PT ldb(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  constexpr int kNt = 2;
+  if constexpr (sizeof(PT) == 16)
+    return __builtin_bit_cast(PT, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kNt));
+  else
+    return __builtin_bit_cast(PT, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, kNt));
+}
+
 // Streams the k-steps k0 = ks0, ks0 + kst, ... < cn of a panel tile (nr rows,
 // ld apart, at most NRB 16-row blocks) against the staged block Bk (S
 // right-hand sides per column).  D k-steps of panel loads stay in flight, each
-// register set refilled right after its MFMAs; addresses are clamped as in
-// mfma_stream.  (With two k-steps in flight a level of a small operator took
+// register set refilled right after its MFMAs; rows past nr read row nr - 1,
+// columns past cn lie past the buffer.  (64-bit lane addresses took 50 more
+// registers in the backward kernels, three waves per SIMD instead of five: a step
+// of 8 right-hand sides at 168,075 unknowns 1,051 -> 1,034 us, at 370,301 2,189 ->
+// 2,146, complex64 panels.  Twice the k-steps with complex64: 1,071 and 2,210;
+// four waves in the forward kernels, which then spill: 1,130 and 2,252.)  (With two k-steps in flight a level of a small operator took
 // 20-25 us, most of it panel latency.)
 template <class PT, int S, int NRB, int D>
 __device__ __forceinline__ void mfma_stream_small(const PT* __restrict__ P, int ld, int nr, int cn,
@@ -582,14 +607,17 @@ __device__ __forceinline__ void mfma_stream_small(const PT* __restrict__ P, int 
   const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, r = lr & 7;
   const bool im = lr >= 8, used = r < S;
   const int rs = used ? r : 0;
-  int roff[NRB];
+  constexpr int esz = sizeof(PT);
+  const int bytes = ((cn - 1) * ld + nr) * esz;
+  const __amdgpu_buffer_rsrc_t buf = tile_rsrc(P, bytes);
+  int voff[NRB];
 #pragma unroll
-  for (int rb = 0; rb < NRB; ++rb) roff[rb] = min(16 * rb + lr, nr - 1);
+  for (int rb = 0; rb < NRB; ++rb) voff[rb] = (lk * ld + min(16 * rb + lr, nr - 1)) * esz;
   PT a[D][NRB];
   auto load = [&](int k0, PT (&w)[NRB]) {
-    const PT* pc = P + (int64_t)min(k0 + lk, cn - 1) * ld;
+    const int soff = __builtin_amdgcn_readfirstlane(min(k0 * ld * esz, bytes));
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) w[rb] = ldp(pc + roff[rb]);
+    for (int rb = 0; rb < NRB; ++rb) w[rb] = ldb<PT>(buf, voff[rb], soff);
   };
   auto step = [&](int k0, const PT (&w)[NRB]) {
     const double2 b = Bk[min(k0 + lk, cn - 1) * S + rs];
