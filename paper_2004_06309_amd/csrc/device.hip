@@ -336,11 +336,13 @@ __device__ __forceinline__ void bwd_task(const Task& task, const Batch& b, doubl
 // The grid holds at most as many workgroups as fit on the device at once;
 // each sweeps tasks blockIdx.x, blockIdx.x + gridDim.x, ... (widest first),
 // so a level costs no workgroup launches beyond the first wave of them.
-// Complex64 panels: six workgroups per CU against four, 2.224 -> 2.205 ms for the
-// two-level preconditioner at one million unknowns; complex128 panels got slower
-// (3.65 -> 3.69 ms).
+// Complex64 panels: five workgroups per CU.  Local solves with six / five / four
+// registers' worth: one million unknowns in 64 subdomains 2.004 / 1.992 / 1.984 ms,
+// in 16 2.144 / 2.104 / 2.113, 608,375 unknowns in 20 1.098 / 1.036 / 1.041 (six
+// hold too few loads in flight per wave where the upper levels have few tiles).
+// Complex128 panels: four (six: 3.65 -> 3.69 ms for the two-level preconditioner).
 template <class PT, int kCoarse>
-__global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 6 : 4) void fwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
+__global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 5 : 4) void fwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
                                                         const double2* __restrict__ bin, int chunk) {
   extern __shared__ double2 vin[];
   __shared__ double2 red[4][64];
@@ -351,7 +353,7 @@ __global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 6 : 4) void fwd_level_kernel
 }
 
 template <class PT, int kCoarse>
-__global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 6 : 4) void bwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
+__global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 5 : 4) void bwd_level_kernel(const Task* __restrict__ tasks, int ntasks, Batch b,
                                                         int chunk) {
   extern __shared__ double2 vin[];
   __shared__ double2 red[4][64];
