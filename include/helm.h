@@ -316,7 +316,11 @@ int helm_coarse_nnz(const helm_ctx* ctx, int64_t* n_c, int64_t* nnz);
 int helm_coarse_get(const helm_ctx* ctx, int64_t* rowptr, int32_t* col, double* val);
 
 /* --- Device operations (device pointers to c128[n]; stream = hipStream_t or
- *     NULL for the null stream).  Asynchronous with respect to the host. --- */
+ *     NULL for the null stream).  Asynchronous with respect to the host.
+ *     Operations of one context share its work vectors: those on different
+ *     streams must be ordered by the caller (events).  Operations that overlap
+ *     spoil each other's results (a coarse or subdomain solve among them may
+ *     give NaN after about a second); the context stays usable. --- */
 
 /* SpMV storage used by every single-vector product with A: 0 = the fastest
  * as timed at helm_assemble (default), 1 = CSR in dof order, 2 = sliced ELL
@@ -353,7 +357,8 @@ int helm_apply_coarse(helm_ctx* ctx, const void* r, void* q, void* stream);
  * call on a GPU shares that GPU's scratch: calls that overlap on one GPU
  * (other streams, other threads or contexts) race and must be serialised by
  * the caller.  Nothing in the scratch needs clearing between calls (every
- * work vector is written before it is read). */
+ * work vector is written before it is read); the counters of the coarse solve
+ * belong to the context, and every call leaves them clear. */
 int helm_apply_coarse_noalloc(helm_ctx* ctx, const void* r, void* q, void* stream);
 
 /* Solve A U = B for nrhs right-hand sides with right-preconditioned GMRES.

@@ -174,11 +174,15 @@ struct Flow {
   DVec<uint32_t> cnt;
   int nf = 0, n = 0;
   int chunk = 0;
+  int64_t counters = 0;
   bool ready() const { return n > 0; }
+  // what the kernel after a sweep with the counters cnt has to clear
+  dev::FlowState state(uint32_t* cnt) const { return ready() ? dev::FlowState{cnt, counters} : dev::FlowState{}; }
   void reset() {
     tasks.reset();
     cnt.reset();
     nf = n = chunk = 0;
+    counters = 0;
   }
 };
 

@@ -377,11 +377,16 @@ __global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 5 : 4) void bwd_level_kernel
 // forward tile of its supernode's children has finished (they hold the
 // updates it gathers), a backward tile until every backward tile of the parent
 // has (the ancestors' results are then complete, since the parent waited for
-// its own parent), a root's backward tiles for its forward tiles.  Counters
-// only grow: a sweep raises each one by a known amount, so the target of sweep
-// number e is (e + 1) times that amount (modulo 2^32) and nothing is cleared
-// between sweeps; e sits in device memory, so a captured launch replays
-// correctly.
+// its own parent), a root's backward tiles for its forward tiles.  A sweep
+// raises each counter from zero to a known amount.  The kernel that follows it
+// on its stream (prolongation, coarse update) clears counters and state for the
+// next one and counts a generation (flow_clear), so eager and captured launches
+// may alternate, and no sweep depends on how an earlier one went: applications of
+// one context that overlap, which the callers have to order, draw from one ticket
+// and spoil each other's results, but the last clear comes after all of them.  A
+// sweep cleared under a wait sees the generation change and gives up.  (With
+// counters that ran on from sweep to sweep, an overlap left them off their targets
+// for the life of the context.)
 //
 // Progress: a task's dependencies have smaller numbers, and numbers are drawn
 // in order by workgroups already running, so the smallest unfinished task
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(kWG, sizeof(PT) == 8 ? 5 : 4) void bwd_level_kernel
 // registers and four loads at once).  What bounds it now is the chain
 // of latencies in a task (indices, inputs, hop, children's updates, panel,
 // reduction, stores), about 5 us per level on the small operator.
-constexpr int kFlowPolls = 1 << 22;
+constexpr int kFlowPolls = 1 << 20;  // about a second, a thousand times the longest sweep
 
 __device__ __forceinline__ double2 ld_agent(const double2* p) {
   const double* d = reinterpret_cast<const double*>(p);
@@ -425,23 +430,39 @@ __device__ __forceinline__ void cnt_store(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Waits until the counters of the task's tiles have reached their targets
-// (modulo 2^32): lane u of the first wave polls tile u's counter, since a
-// thousand workgroups polling from every wave slow down the additions they
-// wait for (same-address traffic: 11 ns per access).  False if it gave up.
-__device__ __forceinline__ bool flow_wait(const FlowTask& task, uint32_t* cnt, uint32_t sweep) {
+// Clears the counters and the state of a sweep that has ended (thread id of
+// nthreads of the kernel after it; one store per thread and counter).
+__device__ __forceinline__ void flow_clear(const FlowState& f, int64_t id, int64_t nthreads) {
+  if (id >= f.counters) return;
+  for (int64_t k = id; k < f.counters; k += nthreads) cnt_store(f.cnt + kFlowHead + kFlowPad * k, 0u);
+  if (id == 0) {
+    cnt_store(f.cnt + kFlowTicket, 0u);
+    cnt_store(f.cnt + kFlowTicket + 1, 0u);
+    cnt_store(f.cnt + kFlowGaveUp, 0u);
+  }
+  if (threadIdx.x == 0) cnt_add(f.cnt + kFlowGeneration);  // every workgroup that cleared something
+}
+
+// Waits until the counters of the task's tiles have reached their targets:
+// lane u of the first wave polls tile u's counter, since a thousand workgroups
+// polling from every wave slow down the additions they wait for (same-address
+// traffic: 11 ns per access).  False if it gave up.
+__device__ __forceinline__ bool flow_wait(const FlowTask& task, uint32_t* cnt, uint32_t generation) {
   const int u = threadIdx.x;
   const int32_t c = u < 4 ? task.t[u].wait : -1;
-  const uint32_t target = u < 4 ? task.t[u].need * (sweep + 1) : 0;
+  const uint32_t target = u < 4 ? task.t[u].need : 0;
   const uint32_t* p = cnt + kFlowHead + (int64_t)kFlowPad * c;
   for (int i = 0; i < kFlowPolls; ++i) {
     bool done = true;
-    if (c >= 0) done = (int32_t)(cnt_load(p) - target) >= 0;
+    if (c >= 0) done = cnt_load(p) >= target;
     if (__all(done)) return true;
-    if ((i & 1023) == 1023 && cnt_load(cnt + 3)) return false;
+    if ((i & 255) == 255) {
+      if (cnt_load(cnt + kFlowGaveUp)) return false;
+      if (cnt_load(cnt + kFlowGeneration) != generation) break;
+    }
     __builtin_amdgcn_s_sleep(1);
   }
-  cnt_store(cnt + 3, 1u);
+  cnt_store(cnt + kFlowGaveUp, 1u);
   return false;
 }
 
@@ -472,7 +493,7 @@ __device__ __forceinline__ double2 flow_children(const FlowBatch& b, int fr, int
 template <class PT, bool kBwd>
 __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& a, const FlowBatch& b,
                                           const double2* __restrict__ bin, double2* vin,
-                                          double2 (*red)[64], int* gave_up, uint32_t sweep, int nx_bound, uint32_t nx,
+                                          double2 (*red)[64], int* gave_up, uint32_t generation, int nx_bound, uint32_t nx,
                                           const FlowTask* __restrict__ tasks, uint32_t& word) {
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
   const Split sp = split_of(uni(task.t[0].wpt), 4, a.chunk);
@@ -526,7 +547,7 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
     if (cb == 0) {
       if (waits) {
         if (wv == 0) {
-          const bool ok = flow_wait(task, a.cnt, sweep);
+          const bool ok = flow_wait(task, a.cnt, generation);
           if (lane == 0) *gave_up = ok ? 0 : 1;
         }
         __syncthreads();
@@ -608,7 +629,7 @@ __device__ __forceinline__ void flow_task(const FlowTask& task, const FlowArgs& 
 // Three workgroups per CU: a fourth (128 registers) made the chains longer, 339
 // against 328 us for 168,075 unknowns.
 template <class PT, int kCoarse>
-__global__ __launch_bounds__(kWG, 3) void flow_kernel(FlowArgs a, int t0, int t1, int last,
+__global__ __launch_bounds__(kWG, 3) void flow_kernel(FlowArgs a, int t0, int t1, int ticket_word,
                                                    const double2* __restrict__ bin) {
   extern __shared__ double2 vin[];
   __shared__ double2 red[4][64];
@@ -616,10 +637,11 @@ __global__ __launch_bounds__(kWG, 3) void flow_kernel(FlowArgs a, int t0, int t1
   __shared__ int next, gave_up;
   const FlowTask* __restrict__ tasks = a.tasks + t0;
   const int n = t1 - t0;
-  const uint32_t sweep = uni((int)cnt_load(a.cnt + 2));
+  const uint32_t generation = uni((int)cnt_load(a.cnt + kFlowGeneration));
+  uint32_t* const ticket = a.cnt + ticket_word;
   if (threadIdx.x < 64) {
     uint32_t d = 0;
-    if (threadIdx.x == 0) next = (int)(d = cnt_add(a.cnt));
+    if (threadIdx.x == 0) next = (int)(d = cnt_add(ticket));
     const int t = uni((int)d);
     if (t < n)
       reinterpret_cast<uint32_t*>(&rec[0])[threadIdx.x] = reinterpret_cast<const uint32_t*>(tasks + t)[threadIdx.x];
@@ -629,26 +651,17 @@ __global__ __launch_bounds__(kWG, 3) void flow_kernel(FlowArgs a, int t0, int t1
   for (int cur = 0; t < n; cur ^= 1) {
     // the next task is drawn, and its record loaded, while this one runs
     uint32_t nx = 0, word = 0;
-    if (threadIdx.x == 0) nx = cnt_add(a.cnt);
+    if (threadIdx.x == 0) nx = cnt_add(ticket);
     const FlowTask& task = rec[cur];
     const FlowBatch& b = a.b[uni(task.t[0].batch)];
     if (uni(task.t[0].bwd))
-      flow_task<PT, true>(task, a, b, bin, vin, red, &gave_up, sweep, n, nx, tasks, word);
+      flow_task<PT, true>(task, a, b, bin, vin, red, &gave_up, generation, n, nx, tasks, word);
     else
-      flow_task<PT, false>(task, a, b, bin, vin, red, &gave_up, sweep, n, nx, tasks, word);
+      flow_task<PT, false>(task, a, b, bin, vin, red, &gave_up, generation, n, nx, tasks, word);
     if (threadIdx.x < 64) reinterpret_cast<uint32_t*>(&rec[cur ^ 1])[threadIdx.x] = word;
     if (threadIdx.x == 0) next = (int)nx;
     __syncthreads();  // vin and red are rewritten by the next task
     t = uni(next);
-  }
-  // the last workgroup to finish readies the state for the next launch
-  if (threadIdx.x == 0 && cnt_add(a.cnt + 1) == gridDim.x - 1) {
-    cnt_store(a.cnt, 0);
-    cnt_store(a.cnt + 1, 0);
-    if (last) {
-      cnt_store(a.cnt + 2, sweep + 1);
-      cnt_store(a.cnt + 3, 0);
-    }
   }
 }
 
@@ -898,8 +911,11 @@ template <int G>
 __global__ __launch_bounds__(kWG) void spmv_real_kernel(int64_t n, const int64_t* __restrict__ ptr,
                                                         const int32_t* __restrict__ col,
                                                         const double* __restrict__ val,
-                                                        const double2* __restrict__ x, double2* __restrict__ y) {
-  const int64_t row = ((int64_t)blockIdx.x * kWG + threadIdx.x) / G;
+                                                        const double2* __restrict__ x, double2* __restrict__ y,
+                                                        FlowState done) {
+  const int64_t id = (int64_t)blockIdx.x * kWG + threadIdx.x;
+  flow_clear(done, id, (int64_t)gridDim.x * kWG);
+  const int64_t row = id / G;
   const int l = threadIdx.x % G;
   double ar = 0, ai = 0;
   if (row < n) {
@@ -931,8 +947,10 @@ __global__ __launch_bounds__(kWG) void coarse_update_kernel(int64_t n, const int
                                                             const double* __restrict__ aval,
                                                             const double2* __restrict__ cx,
                                                             const double2* __restrict__ r, double2* __restrict__ q,
-                                                            double2* __restrict__ t) {
-  const int64_t row = ((int64_t)blockIdx.x * kWG + threadIdx.x) / G;
+                                                            double2* __restrict__ t, FlowState done) {
+  const int64_t id = (int64_t)blockIdx.x * kWG + threadIdx.x;
+  flow_clear(done, id, (int64_t)gridDim.x * kWG);
+  const int64_t row = id / G;
   const int l = threadIdx.x % G;
   double qr = 0, qi = 0, ar = 0, ai = 0;
   if (row < n) {
@@ -962,8 +980,9 @@ __global__ __launch_bounds__(kWG) void coarse_update_kernel(int64_t n, const int
 __global__ __launch_bounds__(kWG) void prolong_kernel(int64_t n, const int64_t* __restrict__ ptr,
                                                       const int32_t* __restrict__ idx, const double* __restrict__ w,
                                                       const double2* __restrict__ xl, const double2* __restrict__ q,
-                                                      double2* __restrict__ z) {
+                                                      double2* __restrict__ z, FlowState done) {
   const int64_t g = (int64_t)blockIdx.x * kWG + threadIdx.x;
+  flow_clear(done, g, (int64_t)gridDim.x * kWG);
   if (g >= n) return;
   double ar = 0, ai = 0;
   if (q) {
@@ -1559,16 +1578,17 @@ void bwd_level(const Batch& b, int64_t task0, int64_t ntasks, int chunk, bool co
     level_go(bwd_level_kernel<double2, 0>, ntasks, lds, s, k, nt, b, chunk);
 }
 
-void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, bool last, const double* bin, hipStream_t s) {
+void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, const double* bin, hipStream_t s) {
   if (t1 <= t0) return;
   const double2* in = reinterpret_cast<const double2*>(bin);
   const size_t lds = sizeof(double2) * (size_t)a.chunk;
+  const int word = kFlowTicket + (t0 > 0);  // a second launch of one sweep draws from the other ticket
   if (coarse)
-    level_go(flow_kernel<double2, 1>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
+    level_go(flow_kernel<double2, 1>, t1 - t0, lds, s, a, t0, t1, word, in);
   else if (c64)
-    level_go(flow_kernel<float2, 0>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
+    level_go(flow_kernel<float2, 0>, t1 - t0, lds, s, a, t0, t1, word, in);
   else
-    level_go(flow_kernel<double2, 0>, t1 - t0, lds, s, a, t0, t1, (int)last, in);
+    level_go(flow_kernel<double2, 0>, t1 - t0, lds, s, a, t0, t1, word, in);
 }
 
 int coop_grid() {
@@ -1655,42 +1675,47 @@ void sell_spmv(int64_t n, int64_t nslices, const int64_t* soff, const int32_t* s
 }
 
 void spmv_real(int64_t n, const int64_t* ptr, const int32_t* col, const double* val, const double* x, double* y,
-               int G, hipStream_t s) {
+               int G, hipStream_t s, const FlowState& done) {
   if (n <= 0) return;
   auto x2 = reinterpret_cast<const double2*>(x);
   auto y2 = reinterpret_cast<double2*>(y);
   switch (G) {
-    case 8: spmv_real_kernel<8><<<blocks_for(n * 8), kWG, 0, s>>>(n, ptr, col, val, x2, y2); break;
-    case 16: spmv_real_kernel<16><<<blocks_for(n * 16), kWG, 0, s>>>(n, ptr, col, val, x2, y2); break;
-    case 32: spmv_real_kernel<32><<<blocks_for(n * 32), kWG, 0, s>>>(n, ptr, col, val, x2, y2); break;
-    case 64: spmv_real_kernel<64><<<blocks_for(n * 64), kWG, 0, s>>>(n, ptr, col, val, x2, y2); break;
-    default: spmv_real_kernel<4><<<blocks_for(n * 4), kWG, 0, s>>>(n, ptr, col, val, x2, y2); break;
+    case 8: spmv_real_kernel<8><<<blocks_for(n * 8), kWG, 0, s>>>(n, ptr, col, val, x2, y2, done); break;
+    case 16: spmv_real_kernel<16><<<blocks_for(n * 16), kWG, 0, s>>>(n, ptr, col, val, x2, y2, done); break;
+    case 32: spmv_real_kernel<32><<<blocks_for(n * 32), kWG, 0, s>>>(n, ptr, col, val, x2, y2, done); break;
+    case 64: spmv_real_kernel<64><<<blocks_for(n * 64), kWG, 0, s>>>(n, ptr, col, val, x2, y2, done); break;
+    default: spmv_real_kernel<4><<<blocks_for(n * 4), kWG, 0, s>>>(n, ptr, col, val, x2, y2, done); break;
   }
 }
 
 void coarse_update(int64_t n, const int64_t* zptr, const int32_t* zcol, const double* zval, const int64_t* aptr,
                    const int32_t* acol, const double* aval, const double* cx, const double* r, double* q, double* t,
-                   int G, hipStream_t s) {
+                   int G, hipStream_t s, const FlowState& done) {
   if (n <= 0) return;
   auto c2 = reinterpret_cast<const double2*>(cx);
   auto r2 = reinterpret_cast<const double2*>(r);
   auto q2 = reinterpret_cast<double2*>(q);
   auto t2 = reinterpret_cast<double2*>(t);
   if (G == 8)
-    coarse_update_kernel<8><<<blocks_for(n * 8), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2);
+    coarse_update_kernel<8><<<blocks_for(n * 8), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2,
+                                                            done);
   else if (G == 2)
-    coarse_update_kernel<2><<<blocks_for(n * 2), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2);
+    coarse_update_kernel<2><<<blocks_for(n * 2), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2,
+                                                            done);
   else if (G == 1)
-    coarse_update_kernel<1><<<blocks_for(n), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2);
+    coarse_update_kernel<1><<<blocks_for(n), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2,
+                                                            done);
   else
-    coarse_update_kernel<4><<<blocks_for(n * 4), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2);
+    coarse_update_kernel<4><<<blocks_for(n * 4), kWG, 0, s>>>(n, zptr, zcol, zval, aptr, acol, aval, c2, r2, q2, t2,
+                                                            done);
 }
 
 void prolong(int64_t n, const int64_t* ptr, const int32_t* idx, const double* w, const double* xl, const double* q,
-             double* z, hipStream_t s) {
+             double* z, hipStream_t s, const FlowState& done) {
   if (n <= 0) return;
   prolong_kernel<<<blocks_for(n), kWG, 0, s>>>(n, ptr, idx, w, reinterpret_cast<const double2*>(xl),
-                                               reinterpret_cast<const double2*>(q), reinterpret_cast<double2*>(z));
+                                               reinterpret_cast<const double2*>(q), reinterpret_cast<double2*>(z),
+                                               done);
 }
 
 int gs_blocks(int64_t n) {

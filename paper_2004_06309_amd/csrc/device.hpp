@@ -184,10 +184,20 @@ struct FlowArgs {
   FlowBatch b[kFlowBatches];
 };
 constexpr int kFlowChunk = 1024;   // four per thread
-constexpr int kFlowHead = 32;      // next task, finished workgroups, sweeps done, gave up (one cache line)
+constexpr int kFlowHead = 32;      // words of state (one cache line):
+constexpr int kFlowTicket = 0;     //   next task, of a sweep's first and second launch
+constexpr int kFlowGeneration = 2; //   grows with every clear
+constexpr int kFlowGaveUp = 3;     //   a wait gave up
 constexpr int kFlowPad = 16;       // words per counter: few share a cache line, so polling one does not slow another
-// Tasks [t0, t1); last: the launch that ends the backward sweep.
-void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, bool last, const double* bin, hipStream_t s);
+// Tasks [t0, t1) of a sweep, in one launch or in two (the second from t0 > 0 on).
+// The next kernel on the stream has to clear the state: see FlowState.
+void flow(const FlowArgs& a, bool c64, bool coarse, int t0, int t1, const double* bin, hipStream_t s);
+// State of a finished sweep, for the kernel after it to clear (none: nothing to
+// clear).
+struct FlowState {
+  uint32_t* cnt = nullptr;
+  int64_t counters = 0;
+};
 
 // Task ranges of every level of a batch (a kernel argument).
 constexpr int kMaxLevels = 40;
@@ -223,21 +233,22 @@ int64_t xcd_ranges(int64_t n, const int64_t* ptr, int64_t xr[9]);
 // Same product from the sliced-ELL copy of A (64-row slices).
 void sell_spmv(int64_t n, int64_t nslices, const int64_t* soff, const int32_t* swidth, const int32_t* perm,
                const int32_t* col, const double* val, const double* x, const double* b, double* y, hipStream_t s);
-// y = A x with a real CSR matrix and complex vectors; G lanes per row.
+// y = A x with a real CSR matrix and complex vectors; G lanes per row.  This and
+// the next two clear the state of the sweeps whose result they read.
 void spmv_real(int64_t n, const int64_t* ptr, const int32_t* col, const double* val, const double* x, double* y,
-               int G, hipStream_t s);
+               int G, hipStream_t s, const FlowState& done = {});
 // q = Z cx and t = r - (A Z) cx for a coarse solution cx (complex vectors):
 // Z real CSR, A Z in the split storage of spmv_split; G = 1, 2, 4 or 8
 // lanes per row.
 void coarse_update(int64_t n, const int64_t* zptr, const int32_t* zcol, const double* zval, const int64_t* aptr,
                    const int32_t* acol, const double* aval, const double* cx, const double* r, double* q, double* t,
-                   int G, hipStream_t s);
+                   int G, hipStream_t s, const FlowState& done = {});
 // t = x - (A Z) cx for S interleaved right-hand sides (device_block.hip).
 void coarse_update_block(int64_t n, const int64_t* aptr, const int32_t* acol, const double* aval, int S,
                          const double* cx, const double* x, double* t, hipStream_t s);
 // z[g] = sum_p w[p] xl[idx[p]] over p in [ptr[g], ptr[g+1]) (+ q[g] if q).
 void prolong(int64_t n, const int64_t* ptr, const int32_t* idx, const double* w, const double* xl, const double* q,
-             double* z, hipStream_t s);
+             double* z, hipStream_t s, const FlowState& done = {});
 
 // Blocks for norm2's partial sums.
 int gs_blocks(int64_t n);

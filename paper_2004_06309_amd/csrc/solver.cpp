@@ -807,6 +807,7 @@ struct FlowHost {
     }
     for (int64_t q = 0; q < 3 * nsn; ++q)
       if (end[q] && seen[q] != end[q]) fail(HELM_EINVAL, "internal: a solve counter misses its target");
+    F.counters = 3 * nsn;
     F.tasks.upload(tasks);
     F.cnt.upload(std::vector<uint32_t>(dev::kFlowHead + (size_t)dev::kFlowPad * 3 * nsn, 0));
   }
@@ -838,12 +839,13 @@ bool coop_solve(const BatchDev& b, const dev::Batch& v, const double* in, hipStr
   return false;
 }
 
+// The kernel after it clears F's state in cnt (dev::FlowState).
 void batch_solve_view(const BatchDev& b, const dev::Batch& v, const Flow& F, uint32_t* cnt, const double* in,
                       hipStream_t s) {
   if (F.ready()) {
     dev::FlowArgs a = flow_args(F, cnt);
     a.b[0] = flow_view(v);
-    dev::flow(a, false, true, 0, F.n, true, in, s);
+    dev::flow(a, false, true, 0, F.n, in, s);
     return;
   }
   if (b.coop > 0 && coop_solve(b, v, in, s)) return;
@@ -1534,7 +1536,8 @@ void apply_coarse_scratch(Ctx& c, const double* r, double* q, hipStream_t s, voi
   v.x = x;
   v.ubuf = ub;
   batch_solve_view(c.coarse, v, c.flow_coarse, c.flow_cnt_noalloc.p, cv, s);
-  dev::spmv_real(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, x, q, c.g_Zp, s);
+  dev::spmv_real(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, x, q, c.g_Zp, s,
+                 c.flow_coarse.state(c.flow_cnt_noalloc.p));
 }
 
 void apply_coarse(Ctx& c, const double* r, double* q, hipStream_t s) {
@@ -1542,7 +1545,8 @@ void apply_coarse(Ctx& c, const double* r, double* q, hipStream_t s) {
   if (p) c.prof.begin(s);
   dev::spmv_real(c.ZT.n, c.ZT_ptr.p, c.ZT_col.p, c.ZT_val.p, r, c.cvec.p, c.g_ZT, s);
   batch_solve_view(c.coarse, c.coarse.view(), c.flow_coarse, c.flow_coarse.cnt.p, c.cvec.p, s);
-  dev::spmv_real(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.coarse.x.p, q, c.g_Zp, s);
+  dev::spmv_real(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.coarse.x.p, q, c.g_Zp, s,
+                 c.flow_coarse.state(c.flow_coarse.cnt.p));
   if (p) {
     const double zb = 2.0 * (12.0 * (double)c.Z.col.size() + 8.0 * c.D.n) + 16.0 * (c.D.n + c.E.n);
     c.prof.end(HELM_K_COARSE, zb + sum(c.coarse.bytes_f) + sum(c.coarse.bytes_b), s);
@@ -1582,19 +1586,19 @@ void apply_oras(Ctx& c, const double* r, double* z, const double* q, hipStream_t
       double bf = 0, bb = 0;
       for (int k = 0; k < c.nbatch; ++k) bf += sum(c.fine[k].bytes_f), bb += sum(c.fine[k].bytes_b);
       c.prof.begin(s);
-      dev::flow(a, c64, false, 0, F.nf, false, r, s);
+      dev::flow(a, c64, false, 0, F.nf, r, s);
       c.prof.end(HELM_K_TRSV_FWD, bf, s);
       c.prof.begin(s);
-      dev::flow(a, c64, false, F.nf, F.n, true, r, s);
+      dev::flow(a, c64, false, F.nf, F.n, r, s);
       c.prof.end(HELM_K_TRSV_BWD, bb, s);
     } else {
-      dev::flow(a, c64, false, 0, F.n, true, r, s);
+      dev::flow(a, c64, false, 0, F.n, r, s);
     }
   } else {
     for_batches(c, s, [&](BatchDev& b, hipStream_t sk) { batch_solve(b, r, sk, &c.prof, true); });
   }
   if (p) c.prof.begin(s);
-  dev::prolong(c.D.n, c.pro_ptr.p, c.pro_idx.p, c.pro_w.p, c.fine[0].xout(), q, z, s);
+  dev::prolong(c.D.n, c.pro_ptr.p, c.pro_idx.p, c.pro_w.p, c.fine[0].xout(), q, z, s, F.state(F.cnt.p));
   if (p) c.prof.end(HELM_K_PROLONG, 12.0 * c.pro_w.n + 28.0 * c.pro_w.n + 16.0 * c.D.n * (q ? 2 : 1) + 8.0 * c.D.n, s);
 }
 
@@ -1610,7 +1614,7 @@ void precond_stage1(Ctx& c, const double* r, hipStream_t s) {
   dev::spmv_real(c.ZT.n, c.ZT_ptr.p, c.ZT_col.p, c.ZT_val.p, r, c.cvec.p, c.g_ZT, s);
   batch_solve_view(c.coarse, c.coarse.view(), c.flow_coarse, c.flow_coarse.cnt.p, c.cvec.p, s);
   dev::coarse_update(c.D.n, c.Zp_ptr.p, c.Zp_col.p, c.Zp_val.p, c.AZ_ptr.p, c.AZ_col.p, c.AZ_val.p, c.coarse.x.p, r,
-                     c.q.p, c.t.p, c.g_AZ, s);
+                     c.q.p, c.t.p, c.g_AZ, s, c.flow_coarse.state(c.flow_coarse.cnt.p));
   if (p) {
     const double zb = 12.0 * (double)c.Z.col.size() + 8.0 * c.E.n + 16.0 * (c.D.n + c.E.n);
     const double ub = 12.0 * (double)(c.Z.col.size() + c.AZ_col.n) + 16.0 * (double)c.D.n + 48.0 * c.D.n;
