@@ -83,11 +83,12 @@ typedef struct helm_precond_opts {
                               this many supernodes of <= 64 pivots (and
                               64-row tiles) solves those with one wave per
                               supernode instead of one per tile; 0 = 6144,
-                              -1 = never.  A positive value also keeps one
-                              launch per level on operators of at most 3e8
-                              panel entries, whose single-vector sweeps
-                              otherwise share one launch (workgroups wait for
-                              the tiles they depend on)                   */
+                              -1 = never.  Single-vector sweeps of
+                              operators of at most 3e8 panel entries share
+                              one launch (workgroups wait for the tiles they
+                              depend on), which has no such jobs: a positive
+                              value other than 6144 keeps one launch per
+                              level there too                             */
   int32_t batches;         /* the subdomains as 1 .. 4 consecutive batches
                               of about equal factor size whose level
                               sweeps run concurrently, each on a stream of

@@ -641,6 +641,11 @@ constexpr double kFlowLaneCols = 12;
 // Beyond the line every level fills the device several times over, two
 // batches hide each other's tails, and plain accesses beat coherent ones.
 constexpr int64_t kFlowEntries = 300000000;
+// Narrow supernodes from which a forward level takes one wave each (complex128,
+// all batches together).  Only level launches have those jobs, so a caller who
+// sets another line gets level launches whatever the size; 0, the line itself and
+// -1 (no such jobs) leave the choice to kFlowEntries.
+constexpr int64_t kSnJobsMin = 6144;
 // The same line for the coarse matrix, whose short tiles (16 rows) make many
 // small tasks: coarse correction, flow against levels, us: 1,024 unknowns (0.3M
 // entries) 34 / 42, 7,688 (3.7M) 98 / 105, 16,810 (10M) 168 / 174, 27,048 (17M)
@@ -1215,7 +1220,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
   const int ctrows = opts && opts->coarse_tile_rows > 0 ? opts->coarse_tile_rows : 16;
   if (trows != 16 && trows != 32 && trows != 64) fail(HELM_EINVAL, "tile_rows must be 16, 32 or 64");
   if (ctrows != 16 && ctrows != 32 && ctrows != 64) fail(HELM_EINVAL, "coarse_tile_rows must be 16, 32 or 64");
-  const int64_t snmin = !opts || opts->sn_jobs_min == 0 ? 6144 : (opts->sn_jobs_min < 0 ? -1 : opts->sn_jobs_min);
+  const int64_t snmin = !opts || opts->sn_jobs_min == 0 ? kSnJobsMin : (opts->sn_jobs_min < 0 ? -1 : opts->sn_jobs_min);
   const int cmode = opts ? opts->coarse_launch : 0;
   if (cmode < 0 || cmode > 2) fail(HELM_EINVAL, "coarse_launch must be 0, 1 or 2");
 #pragma omp parallel for schedule(dynamic, 1)
@@ -1307,7 +1312,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
     st.factor_flops += fb.flops;
     npos_all += fb.npos;
   }
-  if (on_device && st.factor_entries <= kFlowEntries && !(opts && opts->sn_jobs_min > 0)) fh.build(c.flow_fine);
+  if (on_device && st.factor_entries <= kFlowEntries && (snmin < 0 || snmin == kSnJobsMin)) fh.build(c.flow_fine);
   if (nb > 1) {
     // one output vector in subdomain order, as the prolongation map expects
     c.xall.alloc(2 * (size_t)npos_all);
