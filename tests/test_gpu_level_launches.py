@@ -31,3 +31,27 @@ def test_the_line_of_one_wave_jobs_chooses_the_form(value, one):
     r = torch.from_numpy(wl.random_vector(h.n, 5)).to("cuda")
     n = _forward_launches(h, r, torch.empty_like(r))
     assert (n == 1) if one else (n > h.stats()["batches"])
+
+
+@pytest.mark.parametrize("nb", [2, 3, 4])
+@pytest.mark.parametrize("c64", [0, 1, 2])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_batches_on_level_launches(name, c64, nb):
+    """Two, three and four batches, each on a stream of its own, against one: the
+    same tiles and sums, so bit for bit, also with kernel timing on (the batches
+    one after the other), repeated, and on another input."""
+    w = SHAPES[name]()
+    h1 = helm.from_workload(w, c64=c64, batches=1, sn_jobs_min=1 << 30)
+    hk = helm.from_workload(w, c64=c64, batches=nb, sn_jobs_min=1 << 30)
+    assert hk.stats()["batches"] == nb and h1.stats()["batches"] == 1
+    print(f"[batches] {name} c64={c64} x{nb}", flush=True)
+    for seed in (6, 7):
+        r = torch.from_numpy(wl.random_vector(h1.n, seed)).to("cuda")
+        z1, zk = torch.empty_like(r), torch.empty_like(r)
+        h1.apply_oras(r, z1)
+        for _ in range(2):
+            hk.apply_oras(r, zk)
+            assert torch.equal(zk, z1)
+        zk.zero_()
+        assert _forward_launches(hk, r, zk) > nb
+        assert torch.equal(zk, z1)
