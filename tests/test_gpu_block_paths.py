@@ -38,3 +38,21 @@ def test_narrow_blocks_on_levels_of_many_tiles(nrhs, c64):
     assert h.stats()["n_supernodes"] > 2 * 2048
     print(f"[many tiles] c64={c64} nrhs={nrhs}", flush=True)
     _one_step(h, nrhs, 8, 60)
+
+
+# Rows of every kind: with real velocities real rows of many entries (and those of
+# the absorbing faces, with a few imaginary parts), with attenuation only complex
+# ones; even counts of cells, so a coarse stage takes part.
+@pytest.mark.parametrize("nrhs", [2, 4, 7, 9, 16])
+@pytest.mark.parametrize("attenuation", [0.0, 0.02])
+def test_products_and_coarse_stage_of_a_block(attenuation, nrhs):
+    w = wl.small_box(n=(6, 6, 4), order=2, n_parts=(2, 2, 1), overlap=2, attenuation=attenuation)
+    h = helm.from_workload(w)
+    assert h.stats()["n_coarse"] > 0
+    ptr, _, val = h.matrix_csr()
+    length = np.diff(ptr)
+    imag = np.add.reduceat((val.imag != 0).astype(np.int64), ptr[:-1])
+    assert bool(((imag == 0) & (length > 16)).any()) == (attenuation == 0.0)
+    assert bool(((imag > 0) & (imag < length)).any()) == (attenuation == 0.0)
+    print(f"[products] attenuation={attenuation} nrhs={nrhs}", flush=True)
+    _one_step(h, nrhs, 16, 90)
