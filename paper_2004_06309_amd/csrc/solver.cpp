@@ -1739,12 +1739,33 @@ void finish_column(cplx* h, int j, const double* sv, double alpha) {
 }
 
 // One-level operators up to this many factor entries apply the next step's
-// preconditioner while the host decides about the present one (4,913 unknowns,
-// 1.4e6 entries: 108 -> 101 us per step; 9,889, 3.9e6: 133 -> 128).  The
-// application a cycle's end wastes takes as long as the gaps of about 15 steps
-// at the line.  With a coarse stage the gap is covered already (37,485
-// unknowns: 263 and 261-269 us).
+// preconditioner while the host decides about the present one.  Whole solves
+// without and with it, us: 4,913 unknowns (1.4e6 entries) 7 steps 865 / 832, 13 steps
+// 1,487 / 1,388; 15,625 (5.2e6) 7 steps 1,137 / 1,098, 15 steps 2,287 / 2,180;
+// 24,389 (9.5e6) 7 steps 1,308 / 1,269, 16 steps 2,778 / 2,681.  The gap it hides is
+// 7 us of a step whatever the size, 4 % at the line.  With a coarse stage the gap
+// is covered already (37,485 unknowns: 263 and 261-269 us).
 constexpr int64_t kAheadEntries = 10000000;
+// An application whose step ends the cycle is wasted and takes as long as the gaps
+// of 10 to 18 steps, so one is enqueued only where two more steps at the last
+// step's rate leave the residual above its target; the first step of a solve, with
+// no rate yet, goes without.  (Enqueued after every step, solves of 1, 4 and 7 steps
+// took 287, 574 and 865 us at 4,913 unknowns and 414, 898 and 1,383 at 24,389; 229,
+// 535 and 832, and 300, 796 and 1,269 so.)
+class AheadRule {
+ public:
+  explicit AheadRule(double target) : target_(target) {}
+  void residual(double r) {
+    if (r_ > 0) rate_ = std::min(1.0, r / r_);
+    r_ = r;
+  }
+  void restart(double r) { r_ = r; }  // a new cycle's true residual; the rate stays
+  // Whether the next step is taken to leave another one to do.
+  bool go() const { return r_ * rate_ * rate_ > target_; }
+
+ private:
+  double target_, r_ = 0, rate_ = 0;
+};
 
 int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int maxit, bool x0, bool dcgs2,
                  double* U, hipStream_t s, helm_solve_info* info) {
@@ -1774,6 +1795,7 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
     int its = 0;
     bool conv = false;
     double rel = 0;
+    AheadRule rule(tol * bnorm);
     while (true) {
       spmv_A(c, x, b, V, s);  // r = b - A x
       const double beta = device_norm(c, V, s);
@@ -1784,6 +1806,7 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
         break;
       }
       if (its >= maxit) break;
+      rule.restart(beta);
       dev::scale(n, V, 1.0 / beta, V, s);
       std::fill(g.begin(), g.end(), cplx(0, 0));
       g[0] = beta;
@@ -1841,7 +1864,7 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
         if (jj + 1 < m && its + 1 < maxit) {
           const double* vnext = V + 2 * (size_t)n * (jj + 1);
           precond_stage1(c, vnext, s);
-          ahead = !prof && !c.two_level && c.stats.factor_entries <= kAheadEntries;
+          ahead = !prof && !c.two_level && c.stats.factor_entries <= kAheadEntries && rule.go();
           if (ahead) precond_stage2(c, vnext, Zk + 2 * (size_t)n * (jj + 1), s);
         }
         HELM_HIP(hipEventSynchronize(c.hev));
@@ -1855,6 +1878,7 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
         if (!dcgs2) {
           givens_step(h, jj, cs, sn, g);
           k = jj + 1;
+          rule.residual(std::abs(g[jj + 1]));
           if (std::abs(g[jj + 1]) <= tol * bnorm || its >= maxit || hn == 0) break;
           continue;
         }
@@ -1874,6 +1898,7 @@ int solve_single(Ctx& c, int32_t nrhs, const double* B, double tol, int m, int m
           const double r = std::sqrt(std::norm(hc[jj]) + std::norm(hc[jj + 1]));
           est = hc[jj] == cplx(0, 0) ? std::abs(g[jj]) : std::abs(hc[jj + 1]) / r * std::abs(g[jj]);
         }
+        rule.residual(est);
         if (est <= tol * bnorm || jj + 1 == m || its >= maxit || hn == 0) {
           if (hn > 0) {
             // finish column j with the dots of v_{j+1}
