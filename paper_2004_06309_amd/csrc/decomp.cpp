@@ -66,9 +66,8 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
 #pragma omp parallel
   {
     std::vector<int32_t> layer(nt, -1);
-    std::vector<int32_t> lev(n, -1);
+    std::vector<int32_t> lev(n, -1);  // a dof's first layer, then its place in the subdomain
     std::vector<uint8_t> vmark(nv, 0);
-    std::vector<int32_t> g2l(n, -1);
 #pragma omp for schedule(dynamic, 1)
     for (int32_t i = 0; i < n_sub; ++i) {
       SubdomainHost& S = subs[i];
@@ -118,9 +117,9 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
         S.level[k] = lev[dl[k]];
         S.chi[k] = overlap == 0 ? 1.0 : std::max(0.0, 1.0 - (double)S.level[k] / overlap);
         D.dof_coord(dl[k], &S.coords[3 * k]);
-        lev[dl[k]] = -1;
-        g2l[dl[k]] = (int32_t)k;
+        lev[dl[k]] = (int32_t)k;
       }
+      const std::vector<int32_t>& g2l = lev;
       // faces of Gamma_i met once: physical boundary or artificial interface
       // (grouped by their smallest vertex, local vertices being the first local
       // dofs, each group sorted by itself)
@@ -159,7 +158,7 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
       }
       for (int64_t t : cur) layer[t] = -1;
       assemble_local(D, S.tets, imp, S.dofs, g2l.data(), S.A);
-      for (int64_t d : dl) g2l[d] = -1;
+      for (int64_t d : dl) lev[d] = -1;
     }
   }
   // partition of unity

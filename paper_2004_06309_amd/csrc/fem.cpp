@@ -389,6 +389,77 @@ void build_discretization(Discretization& D, const helm_mesh& mesh, const double
   assemble_local(D, all_tets, faces, all_dofs, nullptr, D.A);
 }
 
+namespace {
+
+// Places of the columns of one row at a time, as marks over all columns ...
+class ColumnMarks {
+ public:
+  explicit ColumnMarks(int64_t n) : slot_(n, Slot{-1, -1}) {}
+  // Notes the place of a column unless it has one; whether it had none.
+  bool add(int32_t row, int32_t col, int32_t at) {
+    if (slot_[col].row == row) return false;
+    slot_[col] = Slot{row, at};
+    return true;
+  }
+  // The place of a column, -1 for none.
+  int32_t at(int32_t row, int32_t col) const { return slot_[col].row == row ? slot_[col].at : -1; }
+
+ private:
+  struct Slot {
+    int32_t row, at;
+  };
+  std::vector<Slot> slot_;
+};
+
+// ... or in a table of at least twice the columns any row can have, probed
+// linearly.  Entries carry their row, so rows follow each other without clearing.
+// Marks are faster (137,781 unknowns on one thread: assembly 257 ms, 281 with
+// tables), but their size is the threads times the unknowns: beyond kMarkBytes in all
+// (0.6 GB at 4.9 million unknowns on 16 threads) the threads keep tables.
+constexpr int64_t kMarkBytes = 256 << 20;
+class ColumnTable {
+ public:
+  explicit ColumnTable(int64_t most) {
+    size_t n = 16;
+    while ((int64_t)n < 2 * most) n *= 2;
+    mask_ = n - 1;
+    slot_.assign(n, Slot{~uint64_t{0}, -1});
+  }
+  bool add(int32_t row, int32_t col, int32_t at) {
+    const uint64_t k = key(row, col);
+    size_t i = home(col);
+    while (slot_[i].key != k) {
+      if (slot_[i].key >> 32 != (uint32_t)row) {
+        slot_[i] = Slot{k, at};
+        return true;
+      }
+      i = (i + 1) & mask_;
+    }
+    return false;
+  }
+  int32_t at(int32_t row, int32_t col) const {
+    const uint64_t k = key(row, col);
+    size_t i = home(col);
+    while (slot_[i].key != k) {
+      if (slot_[i].key >> 32 != (uint32_t)row) return -1;
+      i = (i + 1) & mask_;
+    }
+    return slot_[i].at;
+  }
+
+ private:
+  struct Slot {
+    uint64_t key;  // row and column
+    int32_t at;
+  };
+  static uint64_t key(int32_t row, int32_t col) { return (uint64_t)(uint32_t)row << 32 | (uint32_t)col; }
+  size_t home(int32_t col) const { return (uint32_t)col & mask_; }
+  size_t mask_;
+  std::vector<Slot> slot_;
+};
+
+}  // namespace
+
 void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_list,
                     const std::vector<ImpFace>& faces, const std::vector<int64_t>& dofs, const int32_t* g2l,
                     Csr& out) {
@@ -434,88 +505,94 @@ void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_lis
   out = Csr();
   out.n = out.m = nloc_dofs;
   out.ptr.assign(nloc_dofs + 1, 0);
-  // rows in blocks; `seen` marks the columns met in the present row and, in the
-  // second pass, `at` their places in it
+  // rows in blocks
   constexpr int64_t kBlk = 256;
   const int64_t nblk = (nloc_dofs + kBlk - 1) / kBlk;
   std::vector<uint8_t> dir(nloc_dofs);
   for (int64_t r = 0; r < nloc_dofs; ++r) dir[r] = D.dir_mask[dofs[r]];
   std::vector<std::vector<int32_t>> bcol(nblk);
+  // columns of every row, then the entries; make() gives a thread its columns of a row
+  auto fill = [&](auto make) {
 #pragma omp parallel
-  {
-    std::vector<int32_t> seen(nloc_dofs, -1);
+    {
+      auto cols = make();
 #pragma omp for schedule(dynamic, 1)
-    for (int64_t k = 0; k < nblk; ++k) {
-      std::vector<int32_t>& c = bcol[k];
-      for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
-        const size_t c0 = c.size();
-        if (dir[r]) {
-          c.push_back((int32_t)r);
-        } else {
+      for (int64_t k = 0; k < nblk; ++k) {
+        std::vector<int32_t>& c = bcol[k];
+        for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
+          const size_t c0 = c.size();
+          if (dir[r]) {
+            c.push_back((int32_t)r);
+          } else {
+            for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
+              const int32_t* cc = &tl[rt_idx[p] / nl * nl];
+              for (int b = 0; b < nl; ++b)
+                if (!dir[cc[b]] && cols.add((int32_t)r, cc[b], 0)) c.push_back(cc[b]);
+            }
+            std::sort(c.begin() + c0, c.end());
+          }
+          out.ptr[r + 1] = (int64_t)(c.size() - c0);
+        }
+      }
+    }
+    for (int64_t r = 0; r < nloc_dofs; ++r) out.ptr[r + 1] += out.ptr[r];
+    out.col.resize(out.ptr[nloc_dofs]);
+    out.val.resize(out.ptr[nloc_dofs]);
+#pragma omp parallel
+    {
+      auto cols = make();
+#pragma omp for schedule(dynamic, 1)
+      for (int64_t k = 0; k < nblk; ++k) {
+        const int32_t* c = bcol[k].data();
+        for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
+          const int32_t len = (int32_t)(out.ptr[r + 1] - out.ptr[r]);
+          cplx* v = &out.val[out.ptr[r]];
+          for (int32_t q = 0; q < len; ++q) {
+            out.col[out.ptr[r] + q] = c[q];
+            v[q] = cplx(0, 0);
+            cols.add((int32_t)r, c[q], q);
+          }
+          c += len;
+          if (dir[r]) {
+            v[0] = 1.0;
+            continue;
+          }
           for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
-            const int32_t* cc = &tl[rt_idx[p] / nl * nl];
-            for (int b = 0; b < nl; ++b)
-              if (seen[cc[b]] != (int32_t)r && !dir[cc[b]]) {
-                seen[cc[b]] = (int32_t)r;
-                c.push_back(cc[b]);
-              }
+            int64_t item = rt_idx[p] / nl;
+            int a = (int)(rt_idx[p] % nl);
+            int64_t t = tet_list[item];
+            cplx k2 = D.k[t] * D.k[t];
+            const double* K = &D.Ke[(size_t)t * nl * nl + a * nl];
+            const double* M = &D.Me[(size_t)t * nl * nl + a * nl];
+            for (int b = 0; b < nl; ++b) {
+              int32_t cc = tl[item * nl + b];
+              if (dir[cc]) continue;
+              v[cols.at((int32_t)r, cc)] += -K[b] + k2 * M[b];
+            }
           }
-          std::sort(c.begin() + c0, c.end());
+          for (int64_t p = rf_ptr[r]; p < rf_ptr[r + 1]; ++p) {
+            int64_t item = rf_idx[p] / nfl;
+            int a = (int)(rf_idx[p] % nfl);
+            cplx ik = cplx(0, 1) * D.k[faces[item].owner];
+            const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
+            for (int b = 0; b < nfl; ++b) {
+              int32_t cc = fl[item * nfl + b];
+              if (cc < 0 || dir[cc]) continue;
+              const int32_t q = cols.at((int32_t)r, cc);
+              if (q >= 0) v[q] += ik * B[b];  // not a face dof outside the tet pattern
+            }
+          }
         }
-        out.ptr[r + 1] = (int64_t)(c.size() - c0);
+        std::vector<int32_t>().swap(bcol[k]);
       }
     }
-  }
-  for (int64_t r = 0; r < nloc_dofs; ++r) out.ptr[r + 1] += out.ptr[r];
-  out.col.resize(out.ptr[nloc_dofs]);
-  out.val.resize(out.ptr[nloc_dofs]);
-#pragma omp parallel
-  {
-    std::vector<int32_t> seen(nloc_dofs, -1), at(nloc_dofs);
-#pragma omp for schedule(dynamic, 1)
-    for (int64_t k = 0; k < nblk; ++k) {
-      const int32_t* c = bcol[k].data();
-      for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
-        const int32_t len = (int32_t)(out.ptr[r + 1] - out.ptr[r]);
-        cplx* v = &out.val[out.ptr[r]];
-        for (int32_t q = 0; q < len; ++q) {
-          out.col[out.ptr[r] + q] = c[q];
-          v[q] = cplx(0, 0);
-          seen[c[q]] = (int32_t)r;
-          at[c[q]] = q;
-        }
-        c += len;
-        if (dir[r]) {
-          v[0] = 1.0;
-          continue;
-        }
-        for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
-          int64_t item = rt_idx[p] / nl;
-          int a = (int)(rt_idx[p] % nl);
-          int64_t t = tet_list[item];
-          cplx k2 = D.k[t] * D.k[t];
-          const double* K = &D.Ke[(size_t)t * nl * nl + a * nl];
-          const double* M = &D.Me[(size_t)t * nl * nl + a * nl];
-          for (int b = 0; b < nl; ++b) {
-            int32_t cc = tl[item * nl + b];
-            if (dir[cc]) continue;
-            v[at[cc]] += -K[b] + k2 * M[b];
-          }
-        }
-        for (int64_t p = rf_ptr[r]; p < rf_ptr[r + 1]; ++p) {
-          int64_t item = rf_idx[p] / nfl;
-          int a = (int)(rf_idx[p] % nfl);
-          cplx ik = cplx(0, 1) * D.k[faces[item].owner];
-          const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
-          for (int b = 0; b < nfl; ++b) {
-            int32_t cc = fl[item * nfl + b];
-            // not a face dof outside the tet pattern
-            if (cc >= 0 && !dir[cc] && seen[cc] == (int32_t)r) v[at[cc]] += ik * B[b];
-          }
-        }
-      }
-      std::vector<int32_t>().swap(bcol[k]);
-    }
+  };
+  if ((int64_t)omp_get_max_threads() * nloc_dofs * (int64_t)sizeof(int64_t) <= kMarkBytes) {
+    fill([&] { return ColumnMarks(nloc_dofs); });
+  } else {
+    int64_t most = 1;  // candidates for the columns of a row
+    for (int64_t r = 0; r < nloc_dofs; ++r) most = std::max(most, (rt_ptr[r + 1] - rt_ptr[r]) * nl);
+    fill([&] { return ColumnTable(std::min(most, nloc_dofs)); });
   }
 }
 
