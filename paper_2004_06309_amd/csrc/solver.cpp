@@ -1292,6 +1292,9 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
     st.factor_scratch_bytes = std::max(st.factor_scratch_bytes, sb);
     fsec += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   }
+  int64_t entries = 0;
+  for (auto& S : c.sym) entries += S.fwd_entries + S.bwd_entries;
+  const bool flow = on_device && entries <= kFlowEntries && (snmin < 0 || snmin == kSnJobsMin);
   FlowHost fh;
   fh.c64 = c64;
   for (int32_t k = 0; k < nb; ++k) {
@@ -1304,7 +1307,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
                 on_device, prec, split_min, snb, fb, c.fine[k], np, fs, num_all.empty() ? nullptr : &pre);
     npert += np;
     fsec += fs;
-    if (on_device) fh.add(fb, k);
+    if (flow) fh.add(fb, k);
     st.factor_entries += fb.nf + fb.nb;
     st.levels_fwd = std::max(st.levels_fwd, (int32_t)fb.lev_f.size() - 1);
     st.levels_bwd = std::max(st.levels_bwd, (int32_t)fb.lev_b.size() - 1);
@@ -1312,7 +1315,7 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
     st.factor_flops += fb.flops;
     npos_all += fb.npos;
   }
-  if (on_device && st.factor_entries <= kFlowEntries && (snmin < 0 || snmin == kSnJobsMin)) fh.build(c.flow_fine);
+  if (flow) fh.build(c.flow_fine);
   if (nb > 1) {
     // one output vector in subdomain order, as the prolongation map expects
     c.xall.alloc(2 * (size_t)npos_all);
