@@ -169,12 +169,17 @@ void galerkin(const Csr& A, const CsrReal& Z, const CsrReal& ZT, Csr& E) {
   E.n = E.m = nc;
   std::vector<std::vector<int32_t>> ec(nc);
   std::vector<std::vector<cplx>> ev(nc);
+  Caught caught;
 #pragma omp parallel
   {
-    std::vector<cplx> acc(nc, cplx(0, 0));
-    std::vector<int32_t> mark(nc, -1), list;
+    std::vector<cplx> acc;
+    std::vector<int32_t> mark, list;
+    caught([&] {
+      acc.assign(nc, cplx(0, 0));
+      mark.assign(nc, -1);
+    });
 #pragma omp for schedule(dynamic, 64)
-    for (int64_t l = 0; l < nc; ++l) {
+    for (int64_t l = 0; l < nc; ++l) caught([&] {
       list.clear();
       for (int64_t p = ZT.ptr[l]; p < ZT.ptr[l + 1]; ++p) {
         int64_t j = ZT.col[p];
@@ -197,8 +202,9 @@ void galerkin(const Csr& A, const CsrReal& Z, const CsrReal& ZT, Csr& E) {
       ec[l] = list;
       ev[l].resize(list.size());
       for (size_t i = 0; i < list.size(); ++i) ev[l][i] = acc[list[i]];
-    }
+    });
   }
+  caught.rethrow();
   E.ptr.assign(nc + 1, 0);
   for (int64_t l = 0; l < nc; ++l) E.ptr[l + 1] = E.ptr[l] + (int64_t)ec[l].size();
   E.col.resize(E.ptr[nc]);

@@ -63,13 +63,18 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
   std::sort(bfk.begin(), bfk.end());
 
   subs.assign(n_sub, SubdomainHost());
+  Caught caught;
 #pragma omp parallel
   {
-    std::vector<int32_t> layer(nt, -1);
-    std::vector<int32_t> lev(n, -1);  // a dof's first layer, then its place in the subdomain
-    std::vector<uint8_t> vmark(nv, 0);
+    std::vector<int32_t> layer, lev;  // lev: a dof's first layer, then its place in the subdomain
+    std::vector<uint8_t> vmark;
+    caught([&] {
+      layer.assign(nt, -1);
+      lev.assign(n, -1);
+      vmark.assign(nv, 0);
+    });
 #pragma omp for schedule(dynamic, 1)
-    for (int32_t i = 0; i < n_sub; ++i) {
+    for (int32_t i = 0; i < n_sub; ++i) caught([&] {
       SubdomainHost& S = subs[i];
       std::vector<int64_t> cur = part_tets[i];
       for (int64_t t : cur) layer[t] = 0;
@@ -159,8 +164,9 @@ void build_subdomains(const Discretization& D, const int32_t* part, int32_t n_su
       for (int64_t t : cur) layer[t] = -1;
       assemble_local(D, S.tets, imp, S.dofs, g2l.data(), S.A);
       for (int64_t d : dl) lev[d] = -1;
-    }
+    });
   }
+  caught.rethrow();
   // partition of unity
   std::vector<double> chi_sum(n, 0.0);
   for (auto& S : subs)

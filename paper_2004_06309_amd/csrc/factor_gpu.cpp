@@ -112,31 +112,20 @@ void factor_batch_device(const std::vector<const Csr*>& As, const std::vector<co
   std::vector<std::vector<int64_t>> sptr(nm);
   RawVec<int32_t> spos(nnz0[nm]), sval(nnz0[nm]);  // all matrices' scatter lists
   std::vector<int32_t> ep(std::max<int64_t>(rows0[nm], 1));
-  std::string errmsg;
-  int errcode = 0;
+  Caught caught;
 #pragma omp parallel for schedule(dynamic, 1)
-  for (int i = 0; i < nm; ++i) {
-    try {
-      // moduli only of entries that may be the largest
-      double lim = 0;
-      for (const cplx& v : As[i]->val)
-        if (!(std::norm(v) < lim)) {
-          anorm[i] = std::max(anorm[i], std::abs(v));
-          lim = anorm[i] * anorm[i] * (1 - 1e-12);
-        }
-      scatter_lists(*As[i], *Ss[i], nnz0[i], sptr[i], spos.data() + nnz0[i], sval.data() + nnz0[i]);
-      extend_add_map(*Ss[i], ep.data() + rows0[i]);
-    } catch (const Error& e) {
-#pragma omp critical
-      {
-        if (!errcode) {
-          errcode = e.code;
-          errmsg = e.what();
-        }
+  for (int i = 0; i < nm; ++i) caught([&] {
+    // moduli only of entries that may be the largest
+    double lim = 0;
+    for (const cplx& v : As[i]->val)
+      if (!(std::norm(v) < lim)) {
+        anorm[i] = std::max(anorm[i], std::abs(v));
+        lim = anorm[i] * anorm[i] * (1 - 1e-12);
       }
-    }
-  }
-  if (errcode) fail(errcode, errmsg);
+    scatter_lists(*As[i], *Ss[i], nnz0[i], sptr[i], spos.data() + nnz0[i], sval.data() + nnz0[i]);
+    extend_add_map(*Ss[i], ep.data() + rows0[i]);
+  });
+  caught.rethrow();
   for (int i = 0; i < nm; ++i)
     if (!(anorm[i] > 0)) fail(HELM_ESINGULAR, "zero local matrix");
 

@@ -394,6 +394,7 @@ namespace {
 // Places of the columns of one row at a time, as marks over all columns ...
 class ColumnMarks {
  public:
+  ColumnMarks() = default;
   explicit ColumnMarks(int64_t n) : slot_(n, Slot{-1, -1}) {}
   // Notes the place of a column unless it has one; whether it had none.
   bool add(int32_t row, int32_t col, int32_t at) {
@@ -419,6 +420,7 @@ class ColumnMarks {
 constexpr int64_t kMarkBytes = 256 << 20;
 class ColumnTable {
  public:
+  ColumnTable() = default;
   explicit ColumnTable(int64_t most) {
     size_t n = 16;
     while ((int64_t)n < 2 * most) n *= 2;
@@ -454,9 +456,23 @@ class ColumnTable {
   };
   static uint64_t key(int32_t row, int32_t col) { return (uint64_t)(uint32_t)row << 32 | (uint32_t)col; }
   size_t home(int32_t col) const { return (uint32_t)col & mask_; }
-  size_t mask_;
+  size_t mask_ = 0;
   std::vector<Slot> slot_;
 };
+
+// f(columns, k) for every block k < n, the threads' columns from make().
+template <class Make, class F>
+void over_blocks(int64_t n, Make make, F&& f) {
+  Caught caught;
+#pragma omp parallel
+  {
+    decltype(make()) cols;
+    caught([&] { cols = make(); });
+#pragma omp for schedule(dynamic, 1)
+    for (int64_t k = 0; k < n; ++k) caught([&] { f(cols, k); });
+  }
+  caught.rethrow();
+}
 
 }  // namespace
 
@@ -511,81 +527,73 @@ void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_lis
   std::vector<uint8_t> dir(nloc_dofs);
   for (int64_t r = 0; r < nloc_dofs; ++r) dir[r] = D.dir_mask[dofs[r]];
   std::vector<std::vector<int32_t>> bcol(nblk);
-  // columns of every row, then the entries; make() gives a thread its columns of a row
-  auto fill = [&](auto make) {
-#pragma omp parallel
-    {
-      auto cols = make();
-#pragma omp for schedule(dynamic, 1)
-      for (int64_t k = 0; k < nblk; ++k) {
-        std::vector<int32_t>& c = bcol[k];
-        for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
-          const size_t c0 = c.size();
-          if (dir[r]) {
-            c.push_back((int32_t)r);
-          } else {
-            for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
-              const int32_t* cc = &tl[rt_idx[p] / nl * nl];
-              for (int b = 0; b < nl; ++b)
-                if (!dir[cc[b]] && cols.add((int32_t)r, cc[b], 0)) c.push_back(cc[b]);
-            }
-            std::sort(c.begin() + c0, c.end());
-          }
-          out.ptr[r + 1] = (int64_t)(c.size() - c0);
+  // columns of the rows of block k, then their entries
+  auto pattern = [&](auto& cols, int64_t k) {
+    std::vector<int32_t>& c = bcol[k];
+    for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
+      const size_t c0 = c.size();
+      if (dir[r]) {
+        c.push_back((int32_t)r);
+      } else {
+        for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
+          const int32_t* cc = &tl[rt_idx[p] / nl * nl];
+          for (int b = 0; b < nl; ++b)
+            if (!dir[cc[b]] && cols.add((int32_t)r, cc[b], 0)) c.push_back(cc[b]);
+        }
+        std::sort(c.begin() + c0, c.end());
+      }
+      out.ptr[r + 1] = (int64_t)(c.size() - c0);
+    }
+  };
+  auto entries = [&](auto& cols, int64_t k) {
+    const int32_t* c = bcol[k].data();
+    for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
+      const int32_t len = (int32_t)(out.ptr[r + 1] - out.ptr[r]);
+      cplx* v = &out.val[out.ptr[r]];
+      for (int32_t q = 0; q < len; ++q) {
+        out.col[out.ptr[r] + q] = c[q];
+        v[q] = cplx(0, 0);
+        cols.add((int32_t)r, c[q], q);
+      }
+      c += len;
+      if (dir[r]) {
+        v[0] = 1.0;
+        continue;
+      }
+      for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
+        int64_t item = rt_idx[p] / nl;
+        int a = (int)(rt_idx[p] % nl);
+        int64_t t = tet_list[item];
+        cplx k2 = D.k[t] * D.k[t];
+        const double* K = &D.Ke[(size_t)t * nl * nl + a * nl];
+        const double* M = &D.Me[(size_t)t * nl * nl + a * nl];
+        for (int b = 0; b < nl; ++b) {
+          int32_t cc = tl[item * nl + b];
+          if (dir[cc]) continue;
+          v[cols.at((int32_t)r, cc)] += -K[b] + k2 * M[b];
+        }
+      }
+      for (int64_t p = rf_ptr[r]; p < rf_ptr[r + 1]; ++p) {
+        int64_t item = rf_idx[p] / nfl;
+        int a = (int)(rf_idx[p] % nfl);
+        cplx ik = cplx(0, 1) * D.k[faces[item].owner];
+        const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
+        for (int b = 0; b < nfl; ++b) {
+          int32_t cc = fl[item * nfl + b];
+          if (cc < 0 || dir[cc]) continue;
+          const int32_t q = cols.at((int32_t)r, cc);
+          if (q >= 0) v[q] += ik * B[b];  // not a face dof outside the tet pattern
         }
       }
     }
+    std::vector<int32_t>().swap(bcol[k]);
+  };
+  auto fill = [&](auto make) {
+    over_blocks(nblk, make, pattern);
     for (int64_t r = 0; r < nloc_dofs; ++r) out.ptr[r + 1] += out.ptr[r];
     out.col.resize(out.ptr[nloc_dofs]);
     out.val.resize(out.ptr[nloc_dofs]);
-#pragma omp parallel
-    {
-      auto cols = make();
-#pragma omp for schedule(dynamic, 1)
-      for (int64_t k = 0; k < nblk; ++k) {
-        const int32_t* c = bcol[k].data();
-        for (int64_t r = k * kBlk; r < std::min(nloc_dofs, (k + 1) * kBlk); ++r) {
-          const int32_t len = (int32_t)(out.ptr[r + 1] - out.ptr[r]);
-          cplx* v = &out.val[out.ptr[r]];
-          for (int32_t q = 0; q < len; ++q) {
-            out.col[out.ptr[r] + q] = c[q];
-            v[q] = cplx(0, 0);
-            cols.add((int32_t)r, c[q], q);
-          }
-          c += len;
-          if (dir[r]) {
-            v[0] = 1.0;
-            continue;
-          }
-          for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
-            int64_t item = rt_idx[p] / nl;
-            int a = (int)(rt_idx[p] % nl);
-            int64_t t = tet_list[item];
-            cplx k2 = D.k[t] * D.k[t];
-            const double* K = &D.Ke[(size_t)t * nl * nl + a * nl];
-            const double* M = &D.Me[(size_t)t * nl * nl + a * nl];
-            for (int b = 0; b < nl; ++b) {
-              int32_t cc = tl[item * nl + b];
-              if (dir[cc]) continue;
-              v[cols.at((int32_t)r, cc)] += -K[b] + k2 * M[b];
-            }
-          }
-          for (int64_t p = rf_ptr[r]; p < rf_ptr[r + 1]; ++p) {
-            int64_t item = rf_idx[p] / nfl;
-            int a = (int)(rf_idx[p] % nfl);
-            cplx ik = cplx(0, 1) * D.k[faces[item].owner];
-            const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
-            for (int b = 0; b < nfl; ++b) {
-              int32_t cc = fl[item * nfl + b];
-              if (cc < 0 || dir[cc]) continue;
-              const int32_t q = cols.at((int32_t)r, cc);
-              if (q >= 0) v[q] += ik * B[b];  // not a face dof outside the tet pattern
-            }
-          }
-        }
-        std::vector<int32_t>().swap(bcol[k]);
-      }
-    }
+    over_blocks(nblk, make, entries);
   };
   if ((int64_t)omp_get_max_threads() * nloc_dofs * (int64_t)sizeof(int64_t) <= kMarkBytes) {
     fill([&] { return ColumnMarks(nloc_dofs); });

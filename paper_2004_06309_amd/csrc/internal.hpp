@@ -1,9 +1,11 @@
 // Internal types of libhelm (host side).
 #pragma once
 
+#include <atomic>
 #include <complex>
 #include <cstdint>
 #include <memory>
+#include <exception>
 #include <stdexcept>
 #include <string>
 #include <type_traits>
@@ -21,6 +23,29 @@ struct Error : std::runtime_error {
   Error(int c, const std::string& m) : std::runtime_error(m), code(c) {}
 };
 [[noreturn]] inline void fail(int code, const std::string& msg) { throw Error(code, msg); }
+
+// Takes the first exception (an allocation that failed, mostly) out of a parallel
+// region, where it would end the process; what comes after it is skipped.
+class Caught {
+ public:
+  template <class F>
+  void operator()(F&& f) noexcept {
+    if (failed_.load(std::memory_order_relaxed)) return;
+    try {
+      f();
+    } catch (...) {
+      if (!failed_.exchange(true)) first_ = std::current_exception();
+    }
+  }
+  // After the region.
+  void rethrow() const {
+    if (first_) std::rethrow_exception(first_);
+  }
+
+ private:
+  std::atomic<bool> failed_{false};
+  std::exception_ptr first_;
+};
 
 // Vector whose elements start unwritten: large arrays are first touched by the
 // threads that fill them (clearing them first is a serial pass of page faults,

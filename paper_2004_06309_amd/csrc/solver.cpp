@@ -270,12 +270,12 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
   // in the order of the children, counted and then filled by row, every matrix
   // by itself
   std::vector<RawVec<int64_t>> fcon_m(nm);
+  for (int i = 0; i < nm; ++i) fcon_m[i].resize(Ss[i]->rows.size());
   int missing = 0;
 #pragma omp parallel for schedule(dynamic, 1) reduction(+ : missing)
   for (int i = 0; i < nm; ++i) {
     const Symbolic& S = *Ss[i];
     RawVec<int64_t>& fl = fcon_m[i];
-    fl.resize(S.rows.size());
     for (int32_t c = 0; c < S.nsn; ++c) {
       const int32_t p = S.sn_parent[c];
       if (p < 0) continue;
@@ -1004,11 +1004,10 @@ void build_sell(Ctx& c, const std::vector<int32_t>& order) {
 #pragma omp parallel for schedule(static)
   for (int64_t w0 = 0; w0 < n; w0 += 1024) {
     const int64_t w1 = std::min<int64_t>(n, w0 + 1024);
-    std::vector<int32_t> r(order.begin() + w0, order.begin() + w1);
-    std::stable_sort(r.begin(), r.end(), [&](int32_t a, int32_t b) {
+    std::copy(order.begin() + w0, order.begin() + w1, perm.begin() + w0);
+    std::stable_sort(perm.begin() + w0, perm.begin() + w1, [&](int32_t a, int32_t b) {
       return A.ptr[a + 1] - A.ptr[a] > A.ptr[b + 1] - A.ptr[b];
     });
-    std::copy(r.begin(), r.end(), perm.begin() + w0);
   }
   std::vector<int64_t> soff(ns + 1, 0);
   std::vector<int32_t> swidth(ns, 0);
@@ -1223,8 +1222,11 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
   const int64_t snmin = !opts || opts->sn_jobs_min == 0 ? kSnJobsMin : (opts->sn_jobs_min < 0 ? -1 : opts->sn_jobs_min);
   const int cmode = opts ? opts->coarse_launch : 0;
   if (cmode < 0 || cmode > 2) fail(HELM_EINVAL, "coarse_launch must be 0, 1 or 2");
+  Caught caught;
 #pragma omp parallel for schedule(dynamic, 1)
-  for (int32_t i = 0; i < n_sub; ++i) nested_dissection(c.subs[i].A, c.subs[i].coords, leaf, c.sym[i], trows);
+  for (int32_t i = 0; i < n_sub; ++i)
+    caught([&] { nested_dissection(c.subs[i].A, c.subs[i].coords, leaf, c.sym[i], trows); });
+  caught.rethrow();
   helm_precond_stats& st = c.stats;
   st.n_sub = n_sub;
   for (auto& S : c.subs) st.n_local_total += (int64_t)S.dofs.size();
@@ -1388,12 +1390,14 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
       for (auto& col : Zp.col) col = c.Esym.iperm[col];
 #pragma omp parallel for schedule(static)
       for (int64_t i = 0; i < Zp.n; ++i) {
-        std::vector<std::pair<int32_t, double>> e;
-        for (int64_t p = Zp.ptr[i]; p < Zp.ptr[i + 1]; ++p) e.push_back({Zp.col[p], Zp.val[p]});
-        std::sort(e.begin(), e.end());
-        for (size_t q = 0; q < e.size(); ++q) {
-          Zp.col[Zp.ptr[i] + q] = e[q].first;
-          Zp.val[Zp.ptr[i] + q] = e[q].second;
+        // at most four entries, one per vertex of the coarse tet
+        std::array<std::pair<int32_t, double>, 4> e;
+        const int64_t p0 = Zp.ptr[i], ne = Zp.ptr[i + 1] - p0;
+        for (int64_t q = 0; q < ne; ++q) e[q] = {Zp.col[p0 + q], Zp.val[p0 + q]};
+        std::sort(e.begin(), e.begin() + ne);
+        for (int64_t q = 0; q < ne; ++q) {
+          Zp.col[p0 + q] = e[q].first;
+          Zp.val[p0 + q] = e[q].second;
         }
       }
       c.Zp_ptr.upload(Zp.ptr);
@@ -1407,13 +1411,18 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
         std::vector<std::vector<int64_t>> bp(nblk);
         std::vector<std::vector<int32_t>> bc(nblk);
         std::vector<std::vector<double>> bv(nblk);
+        Caught caught;
 #pragma omp parallel
         {
-          std::vector<cplx> acc(nc);
-          std::vector<char> seen(nc, 0);
+          std::vector<cplx> acc;
+          std::vector<char> seen;
           std::vector<int32_t> touched;
+          caught([&] {
+            acc.resize(nc);
+            seen.assign(nc, 0);
+          });
 #pragma omp for schedule(dynamic, 1)
-          for (int64_t b = 0; b < nblk; ++b) {
+          for (int64_t b = 0; b < nblk; ++b) caught([&] {
             for (int64_t i = b * blk; i < std::min(n, (b + 1) * blk); ++i) {
               touched.clear();
               for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) {
@@ -1441,8 +1450,9 @@ void precond_setup(Ctx& c, const int32_t* tet_part, int32_t n_sub, int32_t overl
               for (int32_t k : touched) seen[k] = 0;
               bp[b].push_back((int64_t)bc[b].size());
             }
-          }
+          });
         }
+        caught.rethrow();
         std::vector<int64_t> ap(1, 0);
         std::vector<int32_t> acol;
         std::vector<double> aval;
