@@ -54,8 +54,6 @@ __device__ __forceinline__ int64_t uni64(int64_t x) {
 // (6 % of the panel entries at one million unknowns in 64 subdomains) they fetch
 // 21.3 GB instead of 22.9, and the address arithmetic leaves the vector unit:
 // local solves 3.57 -> 3.45 ms, with complex64 panels 2.02 -> 1.98 ms.
-typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
-typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
 constexpr int kBufNt = 2;                 // cache policy: non-temporal
 constexpr int kBufSkip = 0x7ffffff0;      // an offset no tile reaches
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const void* p, int64_t off, int bytes) {

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kWG, sizeof(T) == 4 ? 4 : 3) void level_mfma_kernel
   }
 }
 
-// Narrow tiles (at most 96 input columns): one wave per tile, all four
+// Narrow tiles (at most 96 input columns, 192 with complex64 panels): one wave per tile, all four
 // 16-row blocks of the tile in that wave, so there is no cross-wave
 // reduction; the accumulators go straight to y / the update vectors (FP64
 // accumulator register j of lane l holds row 4 j + l / 16, FP32 row
@@ -573,8 +573,6 @@ __global__ __launch_bounds__(kWG, 3) void level_fused_kernel(const Tile* __restr
 // buffer's size, out of range reads give zero; non-temporal): the k-step's offset
 // is scalar, a lane's offset constant.  The check is lane offset >= size - scalar
 // offset, so the scalar offset must not pass the size.
-typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
-typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, int bytes) {
   const int64_t a = reinterpret_cast<int64_t>(p);
   const int lo = __builtin_amdgcn_readfirstlane((int)a), hi = __builtin_amdgcn_readfirstlane((int)(a >> 32));

@@ -621,10 +621,10 @@ void build_batch(const std::vector<const Csr*>& As, const std::vector<const Symb
   Dv.x.alloc(2 * std::max<int64_t>(B.npos, 1));
 }
 
-// Tasks a level of dev::flow is cut into at most, about the workgroups the device
-// holds at once (local solves of 168,075 unknowns: 345 us with 768, 328 with
-// 1024, 340 with 1536), and the columns per lane below which a tile is not split
-// further.
+// Tasks a level of dev::flow is cut into at most, a third more than the 768
+// workgroups the device holds at once (three per CU; local solves of 168,075
+// unknowns: 345 us with 768, 328 with 1024, 340 with 1536), and the columns per lane
+// below which a tile is not split further.
 constexpr int64_t kFlowSlots = 1024;
 constexpr double kFlowLaneCols = 12;
 // Panel entries up to which the sweeps take one launch (dev::flow) instead of
@@ -830,10 +830,6 @@ dev::FlowArgs flow_args(const Flow& F, uint32_t* cnt) {
   return a;
 }
 
-// Forward then backward level sweeps; with profiling on, every level launch
-// of the fine batch is timed (the coarse batch is timed as a whole).
-// Coarse-batch solve (forward and backward sweeps) through a view whose
-// work vectors may lie outside the batch (no profiling).
 // The cooperative coarse solve; false (the launch refused, its error
 // cleared) when the device cannot co-schedule its grid at this moment, for
 // instance while another process holds workgroups: the caller then takes the
@@ -844,7 +840,10 @@ bool coop_solve(const BatchDev& b, const dev::Batch& v, const double* in, hipStr
   return false;
 }
 
-// The kernel after it clears F's state in cnt (dev::FlowState).
+// Coarse-batch solve (forward and backward sweeps) through a view whose work
+// vectors may lie outside the batch; the coarse stage is timed as a whole.  In one
+// launch if F is ready: the kernel after it clears F's state in cnt
+// (dev::FlowState).
 void batch_solve_view(const BatchDev& b, const dev::Batch& v, const Flow& F, uint32_t* cnt, const double* in,
                       hipStream_t s) {
   if (F.ready()) {
@@ -861,20 +860,20 @@ void batch_solve_view(const BatchDev& b, const dev::Batch& v, const Flow& F, uin
   for (size_t l = 0; l + 1 < b.lev_b.size(); ++l) dev::bwd_level(v, b.lev_b[l], b.lev_b[l + 1] - b.lev_b[l], b.chunk_b[l], true, s);
 }
 
-void batch_solve(const BatchDev& b, const double* in, hipStream_t s, Profiler* prof, bool fine) {
+// Forward then backward level sweeps of a subdomain batch; with profiling on, every
+// level launch is timed.
+void batch_solve(const BatchDev& b, const double* in, hipStream_t s, Profiler& prof) {
   dev::Batch v = b.view();
-  if (!fine && b.coop > 0 && coop_solve(b, v, in, s)) return;
-  const bool each = prof && prof->on && fine;
   for (size_t l = 0; l + 1 < b.lev_f.size(); ++l) {
-    if (each) prof->begin(s);
-    dev::fwd_level(v, b.lev_f[l], b.ktile_f[l], in, b.chunk_f[l], !fine, s);
+    if (prof.on) prof.begin(s);
+    dev::fwd_level(v, b.lev_f[l], b.ktile_f[l], in, b.chunk_f[l], false, s);
     dev::fwd_sn(v, b.snj_lev[l], b.snj_lev[l + 1] - b.snj_lev[l], in, s);
-    if (each) prof->end(HELM_K_TRSV_FWD, b.bytes_f[l], s);
+    if (prof.on) prof.end(HELM_K_TRSV_FWD, b.bytes_f[l], s);
   }
   for (size_t l = 0; l + 1 < b.lev_b.size(); ++l) {
-    if (each) prof->begin(s);
-    dev::bwd_level(v, b.lev_b[l], b.lev_b[l + 1] - b.lev_b[l], b.chunk_b[l], !fine, s);
-    if (each) prof->end(HELM_K_TRSV_BWD, b.bytes_b[l], s);
+    if (prof.on) prof.begin(s);
+    dev::bwd_level(v, b.lev_b[l], b.lev_b[l + 1] - b.lev_b[l], b.chunk_b[l], false, s);
+    if (prof.on) prof.end(HELM_K_TRSV_BWD, b.bytes_b[l], s);
   }
 }
 
@@ -1175,7 +1174,7 @@ void choose_coarse_launch(Ctx& c, int mode) {
   std::vector<double> in(2 * nc), x1(2 * nc), x2(2 * nc);
   for (int64_t i = 0; i < 2 * nc; ++i) in[i] = std::sin(0.37 * (double)i + 0.1);
   HELM_HIP(hipMemcpy(c.cvec.p, in.data(), sizeof(double) * 2 * nc, hipMemcpyHostToDevice));
-  batch_solve(b, c.cvec.p, nullptr, nullptr, false);
+  batch_solve_view(b, b.view(), Flow(), nullptr, c.cvec.p, nullptr);
   HELM_HIP(hipMemcpy(x1.data(), b.xout(), sizeof(double) * 2 * nc, hipMemcpyDeviceToHost));
   b.coop = gmax;
   const bool launched = coop_solve(b, b.view(), c.cvec.p, nullptr);
@@ -1201,7 +1200,7 @@ void choose_coarse_launch(Ctx& c, int mode) {
   cands.push_back(gmax);
   b.coop = pick_lanes_per_row(cands, [&](int g) {
     b.coop = g;
-    batch_solve(b, c.cvec.p, nullptr, nullptr, false);
+    batch_solve_view(b, b.view(), Flow(), nullptr, c.cvec.p, nullptr);
   });
 }
 
@@ -1613,7 +1612,7 @@ void apply_oras(Ctx& c, const double* r, double* z, const double* q, hipStream_t
       dev::flow(a, c64, false, 0, F.n, r, s);
     }
   } else {
-    for_batches(c, s, [&](BatchDev& b, hipStream_t sk) { batch_solve(b, r, sk, &c.prof, true); });
+    for_batches(c, s, [&](BatchDev& b, hipStream_t sk) { batch_solve(b, r, sk, c.prof); });
   }
   if (p) c.prof.begin(s);
   dev::prolong(c.D.n, c.pro_ptr.p, c.pro_idx.p, c.pro_w.p, c.fine[0].xout(), q, z, s, F.state(F.cnt.p));
@@ -2372,7 +2371,7 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
       if (!ending.empty()) {
         // finish column j of the slots that stop here with the dots of v_{j+1}
         const int ne = (int)ending.size();
-        dev::PtrSetC Ve{}, pe{}, he{}, cwe{}, cve{};
+        dev::PtrSetC Ve{}, pe{}, cwe{}, cve{};
         dev::PtrSet Vwe{}, we{}, pwe{}, hte{}, hce{}, cwpe{}, cvpe{};
         for (int e = 0; e < ne; ++e) {
           const int q = ending[e];
@@ -2382,7 +2381,6 @@ int solve_block(Ctx& c, int nb, const double* const* Bp, double* const* Up, doub
           pwe.p[e] = pw.p[q];
           pe.p[e] = ps.p[q];
           hte.p[e] = hts.p[q];
-          he.p[e] = hs.p[q];
           hce.p[e] = hcs.p[q];
           cwpe.p[e] = cwp.p[q];
           cvpe.p[e] = cvp.p[q];
@@ -3163,7 +3161,7 @@ void Server::finish(std::vector<helm_server_event>& out) {
     for (size_t a = 0; a < ending.size(); ++a) {
       if (grouped[a]) continue;
       const int jj = slot[ending[a]].jj;
-      dev::PtrSetC Vs{}, ps{}, hs{}, cwc{}, cvc{};
+      dev::PtrSetC Vs{}, ps{}, cwc{}, cvc{};
       dev::PtrSet Vw{}, ws{}, pw{}, hts{}, hcs{}, cwp{}, cvp{};
       int na = 0;
       for (size_t b2 = a; b2 < ending.size(); ++b2) {
@@ -3175,7 +3173,6 @@ void Server::finish(std::vector<helm_server_event>& out) {
         ws.p[na] = c.bw[q].p;
         ps.p[na] = c.bpartial.p + 2 * (size_t)q * nt * blk_ld(m);
         pw.p[na] = c.bpartial.p + 2 * (size_t)q * nt * blk_ld(m);
-        hs.p[na] = c.bhtmp.p + 2 * (size_t)q * blk_ld(m);
         hts.p[na] = c.bhtmp.p + 2 * (size_t)q * blk_ld(m);
         hcs.p[na] = c.bhcol.p + 2 * (size_t)q * blk_ld(m);
         cwp.p[na] = c.bcoef_w.p + 2 * (size_t)q * (m + 2);
