@@ -630,14 +630,15 @@ constexpr double kFlowLaneCols = 12;
 // Panel entries up to which the sweeps take one launch (dev::flow) instead of
 // one per level.  Local solves of the thrust model, flow against levels, us:
 //   entries    complex128     complex64
-//     2.6M      78 / 153       83 / 147
-//      38M     226 / 313      199 / 333
-//     118M     400 / 474      322 / 431
-//     246M     760 / 809      543 / 593
-//     418M    1183 / 1154     806 / 757
-//    1295M    3504 / 3446    2139 / 1975
-// (the first four lines' level times taken before both forms read panels
-// through buffer loads, which gave either about 4 %).
+//     1.3M      73 / 141       73 / 145
+//      16M     155 / 267      145 / 300
+//      56M     237 / 339      204 / 357
+//     118M     400 / 470      323 / 423
+//     214M     688 / 702      491 / 546
+//     351M    1029 / 990      731 / 684
+//     486M    1376 / 1305     952 / 842
+//    1295M    3461 / 3341    2144 / 1961
+// The forms meet at about 260M entries of complex128 and 290M of complex64.
 // Beyond the line every level fills the device several times over, two
 // batches hide each other's tails, and plain accesses beat coherent ones.
 constexpr int64_t kFlowEntries = 300000000;
