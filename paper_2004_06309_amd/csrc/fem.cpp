@@ -395,21 +395,25 @@ namespace {
 class ColumnMarks {
  public:
   ColumnMarks() = default;
-  explicit ColumnMarks(int64_t n) : slot_(n, Slot{-1, -1}) {}
-  // Notes the place of a column unless it has one; whether it had none.
-  bool add(int32_t row, int32_t col, int32_t at) {
-    if (slot_[col].row == row) return false;
-    slot_[col] = Slot{row, at};
+  explicit ColumnMarks(int64_t n) : row_(n, -1), at_(n) {}
+  // Notes a column; whether it is new.
+  bool add(int32_t row, int32_t col) {
+    if (row_[col] == row) return false;
+    row_[col] = row;
     return true;
   }
-  // The place of a column, -1 for none.
-  int32_t at(int32_t row, int32_t col) const { return slot_[col].row == row ? slot_[col].at : -1; }
+  // Notes a new column and its place.
+  void add(int32_t row, int32_t col, int32_t at) {
+    row_[col] = row;
+    at_[col] = at;
+  }
+  bool has(int32_t row, int32_t col) const { return row_[col] == row; }
+  // The place of a column that has one.
+  int32_t at(int32_t, int32_t col) const { return at_[col]; }
 
  private:
-  struct Slot {
-    int32_t row, at;
-  };
-  std::vector<Slot> slot_;
+  std::vector<int32_t> row_;
+  RawVec<int32_t> at_;
 };
 
 // ... or in a table of at least twice the columns any row can have, probed
@@ -427,27 +431,18 @@ class ColumnTable {
     mask_ = n - 1;
     slot_.assign(n, Slot{~uint64_t{0}, -1});
   }
-  bool add(int32_t row, int32_t col, int32_t at) {
-    const uint64_t k = key(row, col);
-    size_t i = home(col);
-    while (slot_[i].key != k) {
-      if (slot_[i].key >> 32 != (uint32_t)row) {
-        slot_[i] = Slot{k, at};
-        return true;
-      }
-      i = (i + 1) & mask_;
-    }
-    return false;
+  bool add(int32_t row, int32_t col) {
+    Slot& s = slot_[find(row, col)];
+    if (s.key == key(row, col)) return false;
+    s.key = key(row, col);
+    return true;
   }
-  int32_t at(int32_t row, int32_t col) const {
-    const uint64_t k = key(row, col);
-    size_t i = home(col);
-    while (slot_[i].key != k) {
-      if (slot_[i].key >> 32 != (uint32_t)row) return -1;
-      i = (i + 1) & mask_;
-    }
-    return slot_[i].at;
+  void add(int32_t row, int32_t col, int32_t at) { slot_[find(row, col)] = Slot{key(row, col), at}; }
+  bool has(int32_t row, int32_t col) const {
+    const Slot& s = slot_[find(row, col)];
+    return s.key == key(row, col);
   }
+  int32_t at(int32_t row, int32_t col) const { return slot_[find(row, col)].at; }
 
  private:
   struct Slot {
@@ -455,7 +450,13 @@ class ColumnTable {
     int32_t at;
   };
   static uint64_t key(int32_t row, int32_t col) { return (uint64_t)(uint32_t)row << 32 | (uint32_t)col; }
-  size_t home(int32_t col) const { return (uint32_t)col & mask_; }
+  // The column's slot, or the first that holds no column of the row.
+  size_t find(int32_t row, int32_t col) const {
+    const uint64_t k = key(row, col);
+    size_t i = (uint32_t)col & mask_;
+    while (slot_[i].key != k && slot_[i].key >> 32 == (uint32_t)row) i = (i + 1) & mask_;
+    return i;
+  }
   size_t mask_ = 0;
   std::vector<Slot> slot_;
 };
@@ -538,7 +539,7 @@ void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_lis
         for (int64_t p = rt_ptr[r]; p < rt_ptr[r + 1]; ++p) {
           const int32_t* cc = &tl[rt_idx[p] / nl * nl];
           for (int b = 0; b < nl; ++b)
-            if (!dir[cc[b]] && cols.add((int32_t)r, cc[b], 0)) c.push_back(cc[b]);
+            if (!dir[cc[b]] && cols.add((int32_t)r, cc[b])) c.push_back(cc[b]);
         }
         std::sort(c.begin() + c0, c.end());
       }
@@ -580,9 +581,8 @@ void assemble_local(const Discretization& D, const std::vector<int64_t>& tet_lis
         const double* B = &fB[(size_t)item * nfl * nfl + a * nfl];
         for (int b = 0; b < nfl; ++b) {
           int32_t cc = fl[item * nfl + b];
-          if (cc < 0 || dir[cc]) continue;
-          const int32_t q = cols.at((int32_t)r, cc);
-          if (q >= 0) v[q] += ik * B[b];  // not a face dof outside the tet pattern
+          // not a face dof outside the tet pattern
+          if (cc >= 0 && !dir[cc] && cols.has((int32_t)r, cc)) v[cols.at((int32_t)r, cc)] += ik * B[b];
         }
       }
     }

@@ -270,12 +270,12 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
   // in the order of the children, counted and then filled by row, every matrix
   // by itself
   std::vector<RawVec<int64_t>> fcon_m(nm);
-  for (int i = 0; i < nm; ++i) fcon_m[i].resize(Ss[i]->rows.size());
-  int missing = 0;
-#pragma omp parallel for schedule(dynamic, 1) reduction(+ : missing)
-  for (int i = 0; i < nm; ++i) {
+  Caught caught;
+#pragma omp parallel for schedule(dynamic, 1)
+  for (int i = 0; i < nm; ++i) caught([&] {
     const Symbolic& S = *Ss[i];
     RawVec<int64_t>& fl = fcon_m[i];
+    fl.resize(S.rows.size());
     for (int32_t c = 0; c < S.nsn; ++c) {
       const int32_t p = S.sn_parent[c];
       if (p < 0) continue;
@@ -289,15 +289,15 @@ void layout_batch(const std::vector<const Symbolic*>& Ss, const std::vector<cons
           f = kinvs[i][row];
         } else {
           const int32_t* it = std::lower_bound(Rp, Rp + rp, row);
-          if (it == Rp + rp || *it != row) ++missing, it = Rp;
+          if (it == Rp + rp || *it != row) fail(HELM_EINVAL, "internal: child row missing from parent front");
           f = pw + (it - Rp);
         }
         fl[a] = fr0[i] + frls[i][p] + f;
-        if (!missing) fcon_cnt[fl[a] + 1]++;
+        fcon_cnt[fl[a] + 1]++;
       }
     }
-  }
-  if (missing) fail(HELM_EINVAL, "internal: child row missing from parent front");
+  });
+  caught.rethrow();
   B.fcon_ptr.resize(fr0[nm] + 1);
   B.fcon_ptr[0] = 0;
   for (int64_t f = 0; f < fr0[nm]; ++f) B.fcon_ptr[f + 1] = B.fcon_ptr[f] + fcon_cnt[f + 1];
