@@ -11,8 +11,9 @@ from paper_2004_06309_amd import helm  # noqa: E402
 from paper_2004_06309_amd import workloads as wl  # noqa: E402
 
 # ragged: levels of a few tiles, their rows split over workgroups; one tree:
-# tiles wider than a staging pass; mid/4: levels of more than 2,048 tiles, a
-# wave per narrow tile, and the coarse level's 16-row tiles
+# tiles wider than a staging pass; mid/4: levels of up to 1,570 tiles over both
+# batches, four waves each, and the coarse level's 16-row tiles (levels of more than
+# 2,048 tiles, a wave per narrow tile: test_gpu_block_paths.py)
 SHAPES = {
     "ragged_p2": lambda: wl.small_box(n=(5, 3, 4), order=2, n_parts=(3, 2, 1), overlap=1, coarse=False),
     "one_tree_p2": lambda: wl.small_box(n=(14, 13, 12), order=2, n_parts=(1, 1, 1), overlap=1, coarse=False),
@@ -38,9 +39,10 @@ def test_narrow_blocks_match_single_solves(name, c64, nrhs):
         assert float((U[k] - V[k]).norm() / V[k].norm()) <= 1e-11
 
 
-# The sparse kernels of a block step (products, coarse update, prolongation) over
-# every width, and rows of every kind: real, on an absorbing face (a few imaginary
-# parts), all complex (attenuation).  One step as above.
+# The sparse kernels of a one-level block step (products, prolongation) over every
+# width.  The box is attenuated in either case, so its rows are complex apart from the
+# identity rows of the free surface (real and mixed rows, and a coarse stage:
+# test_gpu_block_paths.py).  One step as above.
 @pytest.mark.parametrize("nrhs", [2, 4, 7, 9, 16])
 @pytest.mark.parametrize("attenuation", [0.0, 0.02])
 def test_block_products_match_single_solves(attenuation, nrhs):

@@ -1,6 +1,6 @@
 """Both single-vector sweeps in one launch (workgroups that wait for the tiles
-they depend on) against one launch per level (which a positive sn_jobs_min
-asks for), and under graph capture."""
+they depend on) against one launch per level (which a sn_jobs_min of the caller's
+own asks for), and under graph capture."""
 import numpy as np
 import pytest
 
@@ -16,7 +16,8 @@ SHAPES = {
     # subdomains of a few leaves, remainders of every tile height
     "ragged_p2": lambda: wl.small_box(n=(5, 3, 4), order=2, n_parts=(3, 2, 1), overlap=1, coarse=False),
     "small_p2_2lvl": lambda: wl.small_box(n=(6, 6, 4), order=2, n_parts=(2, 2, 1), overlap=2),
-    # one deep tree: separators wider than an LDS pass split over row ranges
+    # one deep tree: tiles of up to 998 columns split over row ranges (wider than an
+    # LDS pass: test_gpu_flow_passes.py)
     "one_tree_p2": lambda: wl.small_box(n=(14, 13, 12), order=2, n_parts=(1, 1, 1), overlap=1, coarse=False),
     "mid_quarter_2lvl": lambda: wl.mid(scale=4, n_parts=(4, 4, 1)),
 }
@@ -64,8 +65,8 @@ def test_flow_other_tile_heights(tile_rows):
 
 
 def test_flow_replays_from_a_graph():
-    """The counters go on from where the last sweep left them, so captured and
-    eager applications may alternate."""
+    """Every sweep finds its counters clear, so captured and eager applications may
+    alternate."""
     w = SHAPES["small_p2_2lvl"]()
     h = helm.from_workload(w)
     r = _vec(h.n, 4)

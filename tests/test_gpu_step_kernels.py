@@ -34,7 +34,8 @@ def test_delayed_and_classical_steps_agree(name, nrhs):
     assert float((U - V).norm() / V.norm()) <= 1e-8
 
 
-# Kernel timing turns the early enqueueing off: the same kernels, bit for bit,
+# Kernel timing turns the early enqueueing off (with two levels it is off on both
+# sides): the same kernels, bit for bit,
 # also where the cycle ends at the restart length, at maxit or by convergence.
 @pytest.mark.parametrize("kw", [dict(tol=1e-14, restart=4, maxit=9), dict(tol=1e-3, restart=50, maxit=60)])
 @pytest.mark.parametrize("name", ["one_tile", "two_level", "tiles_256"])
