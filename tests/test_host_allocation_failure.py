@@ -1,8 +1,11 @@
 """Host allocations that fail, in serial code and in threads: a status, never the end
 of the process."""
 import os
+import shutil
 import subprocess
 import sys
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -70,6 +73,7 @@ sys.exit(0 if refused > 100 else "too few requests")
 """
 
 
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host compiler")
 def test_a_refused_allocation_is_a_status(tmp_path):
     """Assembly and setup on the host (two threads), one process per refused request:
     HELM_ENOMEM, or HELM_OK where the request had another way."""
